@@ -232,7 +232,7 @@ pf_status pf_chain_run(const pf_plan* plan, const void* const* inputs, void* con
     hipError_t e = hipSuccess;
     switch (plan->family) {
         case PF_FAMILY_ROW:
-            if (plan->variant == PF_VARIANT_ROW_STREAM) {
+            if (plan->variant == PF_VARIANT_ROW_STREAM || plan->row_held) {
                 if (plan->spec_id == pf::kSpecJit) {
                     void* params[] = {&a};
                     e = pf::jit_launch(plan->jit_fn, plan->grid, plan->block, 0, params, st);

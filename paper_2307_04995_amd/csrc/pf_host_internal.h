@@ -129,6 +129,7 @@ struct pf_plan_s {
     pf::ColArgs col;
     int stencil_ks = 3;       // kernel extent of the depthwise convolution
     int row_log2l = 6;        // row family: log2 of the lanes of a wave that share a row
+    bool row_held = false;       // row family: the row is held packed in the registers of one workgroup (row_held_kernel)
     pf::BcastTerm bcast_host[PF_DEV_MAX_VEC][PF_DEV_MAX_BCAST_TERMS];  // general broadcasting terms, staged on the host
     void* bcast_dev = nullptr;  // ... and their copy in device memory
     bool group_general = false; // group family: groups of any width (general kernels)

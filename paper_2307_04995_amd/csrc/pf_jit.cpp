@@ -312,6 +312,12 @@ hipFunction_t jit_row_stream_kernel(int device, int dtype, bool ragged, const Ji
     return compile(device, "#include \"pf_row_stream.hpp\"\n", name.str(), err);
 }
 
+hipFunction_t jit_row_held_kernel(int device, int dtype, int k, int threads, bool ragged, const JitSpec& spec, std::string* err) {
+    std::ostringstream name;
+    name << "pf::row_held_kernel<" << dtype << ", " << k << ", " << threads << ", " << (ragged ? "true" : "false") << ", " << spec_text(spec) << ">";
+    return compile(device, "#include \"pf_row_stream.hpp\"\n", name.str(), err);
+}
+
 hipFunction_t jit_ew_kernel(int device, int dtype, int k, bool ragged, const JitSpec& spec, std::string* err) {
     std::ostringstream name;
     name << "pf::ew_kernel<" << dtype << ", " << k << ", " << spec_text(spec) << ", " << (ragged ? "true" : "false") << ">";

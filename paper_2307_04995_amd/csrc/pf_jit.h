@@ -39,6 +39,8 @@ hipFunction_t jit_row_kernel_const(int device, int dtype, int kc, int rpw, bool 
                                    const JitSpec& spec, const RowShapeConst& sh, std::string* err);
 hipFunction_t jit_row_reduce_kernel(int device, int dtype, int k, bool ragged, const JitSpec& spec, std::string* err);
 hipFunction_t jit_row_stream_kernel(int device, int dtype, bool ragged, const JitSpec& spec, std::string* err);
+// rows held packed in one workgroup's registers: k vectors per lane, `threads` lanes
+hipFunction_t jit_row_held_kernel(int device, int dtype, int k, int threads, bool ragged, const JitSpec& spec, std::string* err);
 hipFunction_t jit_ew_kernel(int device, int dtype, int k, bool ragged, const JitSpec& spec, std::string* err);
 
 // transpose family: variant 0 rows (k vectors per lane), 1 LDS-staged rows, 2 register-transposed tiles

@@ -285,9 +285,41 @@ pf_status plan_row(pf_plan_s* p, int forced_variant) {
     p->args.rows = (uint64_t)rows;
     if (best_score < 0 && L.core == pf::CORE_ROWPROG)
         return fail(PF_ERR_UNSUPPORTED, "chains with in-line reductions need rows that fit one workgroup's registers (row length %lld)", (long long)n);
+    // Rows held packed (row_held_kernel), threads per row.  256 lanes while a lane holds at most ten vectors, then 512, and
+    // 1024 once 512 lanes would hold more than 25 (softmax of about 100 MB: [1249, 20001] fp16 19.1 us with 256 lanes, 21.1
+    // with 512; [1024, 50257] 40.6 with 512, 41.4 with 1024; [300, 128256] 43.3 and 42.2).
+    auto try_held = [&](int variant) {
+        if (!jit_ok || forced_variant >= 0 || L.n_full != 1 || L.mask_si != 0 || L.core == pf::CORE_ROWPROG || env_int("PF_ROW_HELD", 1) == 0) return false;
+        if (rows > 0x7fffffffLL || n * es > 0x7fffffffLL) return false;
+        const int64_t held = (n * es + 127 + 15) / 16;  // vectors of a row wherever it starts within a 128-byte line
+        const int t = held <= 256 * 10 ? 256 : held <= 512 * 25 ? 512 : 1024;
+        const int k = (int)((held + t - 1) / t);
+        if (t == 1024 && k > 20) return false;  // (128 registers a lane: what 20 vectors and the arithmetic need)
+        std::string err;
+        hipFunction_t fn = pf::jit_row_held_kernel(p->device, L.main_dtype, k, t, p->ragged, make_jit_spec(L), &err);
+        if (!fn || pf::jit_scratch_bytes(fn) != 0) return false;
+        p->jit_fn = fn;
+        p->spec_id = pf::kSpecJit;
+        p->variant = variant;
+        p->row_held = true;
+        p->k = k;
+        p->row.waves_per_row = (uint32_t)t / 64;
+        p->row.rows_per_block = 1;
+        p->row.rows_per_wave = 1;
+        p->block = dim3((uint32_t)t);
+        p->grid = dim3((uint32_t)rows);
+        p->lds_bytes = 3 * 16 * 4;
+        return true;
+    };
+    // Softmax over rows that are not whole vectors, of more than 512 vectors, with rows to fill the device: held packed and
+    // aligned to memory lines they beat the row kernel's element-aligned accesses ([4999, 5001] fp16 28.8 -> 20.7 us,
+    // [1525, 16383] 25.5 -> 19.5, [2499, 5001] fp32 24.5 -> 21.2); shorter ones do not ([8330, 3001] fp16 21.6 against 22.8),
+    // nor do whole ones ([3125, 8000] 19.2 against 19.5).
+    if (best_score >= 0 && p->ragged && L.core == pf::CORE_SOFTMAX && L.n_vec == 0 && L.n_out == 1 && vpr > 512 && rows >= 512 && try_held(PF_VARIANT_ROW_BLOCK))
+        return PF_OK;
     if (best_score < 0) {
-        // Rows longer than a workgroup keeps in registers (or on request): the streaming variant, a workgroup
-        // per row, two walks over the row.
+        // Rows longer than a workgroup keeps in registers widened to fp32 (or on request): held packed where that fits,
+        // else the streaming kernel, a workgroup per row, two walks over the row.
         if (forced_variant >= 0 && forced_variant != PF_VARIANT_ROW_STREAM)
             return fail(PF_ERR_UNSUPPORTED, "variant %d is not possible for row length %lld", forced_variant, (long long)n);
         if (rows > 0x7fffffffLL || n * es > 0x7fffffffLL) return fail(PF_ERR_UNSUPPORTED, "tensor too large for the streaming row variant");
@@ -300,6 +332,7 @@ pf_status plan_row(pf_plan_s* p, int forced_variant) {
         p->block = dim3(512);
         p->grid = dim3((uint32_t)rows);
         p->lds_bytes = (2 * 16 + 8 * 3) * 4;
+        if (try_held(PF_VARIANT_ROW_STREAM)) return PF_OK;
         if (jit_ok) {
             std::string err;
             p->jit_fn = pf::jit_row_stream_kernel(p->device, L.main_dtype, p->ragged, make_jit_spec(L), &err);
