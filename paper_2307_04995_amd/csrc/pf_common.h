@@ -48,6 +48,7 @@ enum UopCode : uint8_t {
     U_RED_SUM,     // rowv[slot] = sum over the row of acc      (row programs: reductions inside the step list; the
     U_RED_MAX,     // rowv[slot] = max over the row of acc       accumulator is left as it is)
     U_RED_MEAN,    // rowv[slot] = mean over the row of acc
+    U_GNORM,       // acc = (acc - mean) * rstd * gamma + beta of its group (pool family: statistics of an earlier launch)
     U_COUNT_
 };
 
@@ -189,6 +190,11 @@ struct PoolGeom {
     uint32_t merge_rows;         // row groups of threads the merger splits the slices over (512 / channels, at least 1)
     uint32_t ragged;             // the channel count is not a whole number of vectors (cv rounds up; RAGGED kernels)
     FastDiv div_cv;
+    // a group normalisation in the prologue (U_GNORM): the statistics launch's partials
+    // [samples][norm_slices][norm_groups][4] = (count, mean, M2, -), the lanes that merge a group's, channels per group
+    const float* norm_partial;
+    uint32_t norm_groups, norm_slices, norm_lanes;
+    FastDiv div_norm_cpg;
 };
 
 // Column family: normalisation of [outer, c, s] over c (s contiguous); all tensors of one storage type.

@@ -485,6 +485,7 @@ struct StaticSpec {
     static constexpr bool kBcast = (FLAGS_ & 1) != 0;
     static constexpr int kVecMode = FLAGS_ & 3;
     static constexpr int NF = NF_, NV = NV_, NT = NT_;
+    static constexpr int kGamma = GAMMA_, kBeta = BETA_;
     using Pro = ProL;
     using Epi = EpiL;
     static PF_DEVICE int n_full(const ChainArgs&) { return NF_; }
@@ -504,6 +505,13 @@ constexpr uint32_t list_operand_mask(int kind) {
     for (int i = 0; i < L::n; ++i)
         if (L::at(i).kind == kind) m |= 1u << L::at(i).slot;
     return m;
+}
+// Whether the list holds a step of this code.
+template <class L>
+constexpr bool list_has(int code) {
+    for (int i = 0; i < L::n; ++i)
+        if (L::at(i).code == code) return true;
+    return false;
 }
 // Whether the list only loads one full operand and applies steps whose results are again exactly representable
 // in the storage type (so they can be kept packed without changing any later result).
@@ -649,6 +657,10 @@ struct NoStore {
 template <class Hook, int DT, int K, class Spec>
 PF_DEVICE void hook_reduce(const Hook&, int, int, LaneState<DT, K, Spec>&) {}
 
+// Group-normalisation hook (U_GNORM): only the pool kernel's hook type overloads this.
+template <class Hook, int DT, int K, class Spec>
+PF_DEVICE void hook_norm(const Hook&, LaneState<DT, K, Spec>&) {}
+
 template <int DT, int K, class Spec>
 PF_DEVICE void apply_uop(int code, int slot, int32_t ival, LaneState<DT, K, Spec>& s, const float* b) {
     constexpr int E = LaneState<DT, K, Spec>::E;
@@ -783,6 +795,7 @@ PF_DEVICE void run_step(const ProgView<L>& pv, int i, LaneState<DT, K, Spec>& s,
             break;
     }
     if (code == U_STORE) store_fn(slot, s);
+    else if (code == U_GNORM) hook_norm(store_fn, s);
     else if (code == U_RED_SUM || code == U_RED_MAX || code == U_RED_MEAN) hook_reduce(store_fn, code, slot, s);
     else apply_uop<DT, K, Spec>(code, slot, pv.ival(i), s, b);
 }

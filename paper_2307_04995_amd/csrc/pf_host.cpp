@@ -270,12 +270,12 @@ pf_status pf_chain_run(const pf_plan* plan, const void* const* inputs, void* con
                 uint32_t t = tiles;
                 void* params[] = {&a, &g, &t};
                 e = pf::jit_launch(plan->jit_fn, plan->grid, plan->block, plan->dyn_lds, params, st);
-                if (e == hipSuccess && plan->variant == PF_VARIANT_GROUP_TWO_PASS)
+                if (e == hipSuccess && plan->variant == PF_VARIANT_GROUP_TWO_PASS && !plan->stats_only)
                     e = pf::jit_launch(plan->jit_fn2, plan->grid2, plan->block2, plan->dyn_lds, params, st);
             } else if (plan->variant == PF_VARIANT_GROUP_TWO_PASS) {
                 const bool gen = plan->group_general;
                 e = pf::launch_group(1, gen, plan->spec_id, L.main_dtype, a, g, plan->k, tiles, plan->grid, plan->block, plan->dyn_lds, st);
-                if (e == hipSuccess)
+                if (e == hipSuccess && !plan->stats_only)
                     e = pf::launch_group(2, gen, plan->spec_id, L.main_dtype, a, g, plan->k, tiles, plan->grid2, plan->block2, plan->dyn_lds, st);
             } else {
                 e = pf::launch_group(0, false, plan->spec_id, L.main_dtype, a, g, plan->k, tiles, plan->grid, plan->block, 0, st);

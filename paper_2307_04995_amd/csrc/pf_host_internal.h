@@ -88,6 +88,7 @@ struct Lowered {
     Shape pre_shape;          // shape of the value entering the core (or the final value if no core)
     Shape post_shape;         // shape of the value leaving the core
     int64_t groups = 0;
+    int norm_op = -1;         // CORE_POOL: index of a group normalisation lowered as a step of the prologue (-1: none)
     int perm[PF_MAX_RANK];
     // one-token attention: chain input index of q, new key row, new value row, key cache, value cache (-1: the
     // caches already hold the new rows); user output index of o, grown key cache, grown value cache (-1: not an output)
@@ -100,7 +101,9 @@ struct Lowered {
 };
 
 // Lowers a checked chain: prologue and epilogue micro-programs around at most one core, operand slots, output slots.
-pf_status lower_chain(const pf_chain_desc* d, const Checked& c, Lowered* L);
+// fold_norm: a group normalisation in front of a pooling becomes a step of the pooling's prologue (its statistics are then
+// the caller's to provide).
+pf_status lower_chain(const pf_chain_desc* d, const Checked& c, Lowered* L, bool fold_norm = false);
 
 }  // namespace pfh
 
@@ -129,6 +132,7 @@ struct pf_plan_s {
     pf::ColArgs col;
     int stencil_ks = 3;       // kernel extent of the depthwise convolution
     int row_log2l = 6;        // row family: log2 of the lanes of a wave that share a row
+    bool stats_only = false;     // group family: the statistics launch alone runs (a pooling normalises with them)
     bool row_held = false;       // row family: the row is held packed in the registers of one workgroup (row_held_kernel)
     pf::BcastTerm bcast_host[PF_DEV_MAX_VEC][PF_DEV_MAX_BCAST_TERMS];  // general broadcasting terms, staged on the host
     void* bcast_dev = nullptr;  // ... and their copy in device memory
@@ -202,7 +206,12 @@ pf_status plan_workspace_alloc(pf_plan_s* p, uint64_t bytes, const char* what);
 pf_status plan_workspace_fill(pf_plan_s* p, void* ptr, int byte, uint64_t bytes, bool must_hold);
 pf::FastDiv make_fastdiv(uint32_t d);
 // Checks, lowers and plans one description as it stands (no recomposition).
-pf_status plan_checked_desc(const pf_chain_desc* desc, int32_t device, int32_t variant, pf_plan** out);
+enum PlanMode {
+    PLAN_WHOLE,
+    PLAN_GROUP_STATISTICS,  // a chain that ends in a group normalisation: its statistics launch alone
+    PLAN_POOL_WITH_NORM     // a group normalisation and the pooling behind it, statistics provided by the former
+};
+pf_status plan_checked_desc(const pf_chain_desc* desc, int32_t device, int32_t variant, pf_plan** out, PlanMode mode = PLAN_WHOLE);
 // One kernel for the whole chain: as its composite operators when it spells them in basic operators, else as written.
 pf_status plan_one_kernel(const pf_chain_desc* desc, int32_t device, int32_t variant, pf_plan** out);
 

@@ -208,6 +208,31 @@ struct Lowerer {
         cur_result_shape = c->shape[partner_value(id)];
         const OpTraits& tr = kOps[o.op];
         if (tr.cls == OC_RESHAPE) return true;  // alias only
+        if (k == L->norm_op) {
+            const int a = root(o.src[0]);
+            if (!load_acc(a)) return false;
+            if (!spill_acc_if_live(1)) return false;
+            consume(a);
+            cur_result_shape.clear();  // (the parameters are indexed by channel, not broadcast)
+            for (int s = 1; s < o.n_src; ++s) {
+                const int p = root(o.src[s]);
+                Loc l;
+                if (p >= d->n_inputs) {
+                    status = fail(PF_ERR_UNSUPPORTED, "normalisation parameters must be chain inputs");
+                    return false;
+                }
+                if (!input_loc(p, &l, true)) return false;
+                if (l.kind != LOC_VEC) {
+                    status = fail(PF_ERR_UNSUPPORTED, "a normalisation parameter is also used as a full-shape operand");
+                    return false;
+                }
+                L->core_vec[s - 1] = l.slot;
+                consume(p);
+            }
+            if (!emit(pf::U_GNORM, pf::K_NONE, 0)) return false;
+            set_acc(id);
+            return maybe_store_output(id);
+        }
         if (tr.cls == OC_REDUCE) {
             // row program: the reduction is a step; the accumulator keeps the reduced value's source
             const int a = root(o.src[0]);
@@ -462,7 +487,7 @@ static bool lower_column_norm(const pf_chain_desc* d, const Checked& c, Lowered*
     return true;
 }
 
-pf_status lower_chain(const pf_chain_desc* d_in, const Checked& c, Lowered* L) {
+pf_status lower_chain(const pf_chain_desc* d_in, const Checked& c, Lowered* L, bool fold_norm) {
     // A permutation that only moves extents of 1 leaves the order of the elements alone: it is a reshape (free),
     // not a layout change that needs a kernel of the transpose family.
     pf_chain_desc local = *d_in;
@@ -512,6 +537,11 @@ pf_status lower_chain(const pf_chain_desc* d_in, const Checked& c, Lowered* L) {
     L->core_op = -1;
     for (int k = 0; k < d->n_ops && !row_prog; ++k) {
         const OpClass cls = kOps[d->ops[k].op].cls;
+        if (fold_norm && cls == OC_GROUPNORM && L->norm_op < 0 && L->core_op < 0) {
+            L->norm_op = k;
+            L->groups = d->ops[k].i[0];
+            continue;
+        }
         if (!is_elementwise(cls) && cls != OC_RESHAPE) {
             if (L->core_op >= 0)
                 return fail(PF_ERR_UNSUPPORTED, "op %d (%s): a chain may hold one reduce / normalise / permute step", k, kOps[d->ops[k].op].name);
@@ -603,6 +633,12 @@ pf_status lower_chain(const pf_chain_desc* d_in, const Checked& c, Lowered* L) {
             default: return fail(PF_ERR_UNSUPPORTED, "unexpected core operator");
         }
         L->eps = o.f[0];
+    }
+    if (L->norm_op >= 0) {
+        const Shape& ns = c.shape[n_in + L->norm_op];
+        if (L->core != pf::CORE_POOL || ns[0] != L->pre_shape[0] || ns.back() != L->pre_shape.back() || numel(ns) != numel(L->pre_shape))
+            return fail(PF_ERR_UNSUPPORTED, "a group normalisation is a step in front of a pooling of its own positions only");
+        L->eps = d->ops[L->norm_op].f[0];
     }
 
     // ---- prologue

@@ -218,6 +218,50 @@ pf_status partition_chain(const pf_chain_desc* user, const Checked& c, const std
     return PF_OK;
 }
 
+// A chain split as [.. group normalisation ..] [.. pooling ..]: the normalised tensor, which only the pooling reads, need
+// not exist.  The first kernel computes the group statistics alone, the second normalises what it pools.  Both read
+// the caller's tensors in their own storage type, so nothing is widened or rounded around them either: two reads of x
+// instead of nine times its bytes ([32, 64, 64, 320] fp16, GroupNorm + SiLU + mean over positions).  Needs kernels
+// specialised for the chain.  PF_ERR_UNSUPPORTED leaves the chain to the general split.
+static pf_status plan_norm_pool(const pf_chain_desc* user, const Checked& c, int32_t device, pf_plan_s* p) {
+    int norm = -1, core2 = -1;
+    for (int k = 0; k < user->n_ops; ++k) {
+        const OpClass cls = kOps[user->ops[k].op].cls;
+        if (is_elementwise(cls) || cls == OC_RESHAPE) continue;
+        if (cls == OC_GROUPNORM && norm < 0) norm = k;
+        else if (cls == OC_REDUCE && norm >= 0 && core2 < 0) core2 = k;
+        else return fail(PF_ERR_UNSUPPORTED, "not a group normalisation and a pooling");
+    }
+    if (core2 < 0 || user->n_outputs != 1) return fail(PF_ERR_UNSUPPORTED, "not a group normalisation and a pooling");
+    Segment seg;
+    pf_status st = build_segment(user, c, 0, norm + 1, &seg);
+    if (st != PF_OK) return st;
+    if (seg.n_out != 1) return fail(PF_ERR_UNSUPPORTED, "a value in front of the normalisation is used behind it");
+    pf_plan *stats = nullptr, *pool = nullptr;
+    st = plan_checked_desc(&seg.sub, device, -1, &stats, PLAN_GROUP_STATISTICS);
+    if (st != PF_OK) return st;
+    st = plan_checked_desc(user, device, -1, &pool, PLAN_POOL_WITH_NORM);
+    if (st == PF_OK && (stats->spec_id == 0 || pool->spec_id != pf::kSpecJit)) st = fail(PF_ERR_UNSUPPORTED, "needs specialised kernels");
+    if (st != PF_OK) {
+        pf_chain_plan_destroy(stats);
+        pf_chain_plan_destroy(pool);
+        return st;
+    }
+    pool->pool.norm_partial = stats->group.ws_partial;
+    pool->pool.norm_slices = stats->group.blocks_per_sample;
+    pf_plan_s::Part first, second;
+    first.plan = stats, second.plan = pool;
+    first.n_in = seg.n_in, first.n_out = 1;
+    for (int i = 0; i < seg.n_in; ++i) first.in_kind[i] = 0, first.in_index[i] = seg.in_value[i];
+    first.out_kind[0] = 1, first.out_index[0] = 0;  // (not written: the statistics stay in the part's workspace)
+    second.n_in = user->n_inputs, second.n_out = 1;
+    for (int i = 0; i < user->n_inputs; ++i) second.in_kind[i] = 0, second.in_index[i] = i;
+    second.out_kind[0] = 1, second.out_index[0] = 0;
+    p->parts.push_back(first);
+    p->parts.push_back(second);
+    return PF_OK;
+}
+
 // Plans every segment of the cheapest partition; a segment the device-side planning refuses is struck out and the
 // search runs again.
 pf_status plan_partitioned(const pf_chain_desc* user, int32_t device, pf_plan** out) {
@@ -251,7 +295,8 @@ pf_status plan_partitioned(const pf_chain_desc* user, int32_t device, pf_plan** 
             arena_bytes += ((uint64_t)numel(c.shape[v]) * sizeof(float) + 255) / 256 * 256;
             return where[v];
         };
-        if (widen) {
+        const bool norm_pool = part.n_parts == 2 && env_int("PF_NORM_POOL", 1) != 0 && plan_norm_pool(user, c, device, p) == PF_OK;
+        if (widen && !norm_pool) {
             for (int k = 0; k < d->n_inputs; ++k) p->widen_in.push_back(pf_plan_s::Cast{k, arena_add(k), (uint64_t)numel(c.shape[k])});
             for (int o = 0; o < d->n_outputs; ++o) {
                 const int v = d->out_value[o];
@@ -260,7 +305,7 @@ pf_status plan_partitioned(const pf_chain_desc* user, int32_t device, pf_plan** 
             }
         }
         bool ok = true;
-        for (int k = 0; k < part.n_parts && ok; ++k) {
+        for (int k = 0; k < part.n_parts && ok && !norm_pool; ++k) {
             Segment seg;
             st = build_segment(d, c, part.first_op[k], part.first_op[k + 1], &seg);
             pf_plan* sub = nullptr;

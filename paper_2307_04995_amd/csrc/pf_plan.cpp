@@ -746,7 +746,7 @@ pf_status plan_perm(pf_plan_s* p, int forced_variant) {
 // ---- group family
 pf_status plan_group(pf_plan_s* p, int forced_variant) {
     // on the static scratch array: the two-launch variant, which waits for nobody and so has no failed wait to report
-    if (planning_static()) forced_variant = PF_VARIANT_GROUP_TWO_PASS;
+    if (planning_static() || p->stats_only) forced_variant = PF_VARIANT_GROUP_TWO_PASS;
     const Lowered& L = p->low;
     const int es = dtype_size(L.main_dtype);
     const int vec = 16 / es;
@@ -762,7 +762,8 @@ pf_status plan_group(pf_plan_s* p, int forced_variant) {
     const int64_t vpg = cpg / vec, cv = (C + vec - 1) / vec;
     // Groups that are a power-of-two number of whole vectors take the kernels' shuffle-tree path; any other width
     // takes the general one (per-element sums, parts merged through LDS).
-    const bool general = ragged_c || cpg % vec != 0 || (vpg & (vpg - 1)) != 0 || vpg > 64 || env_int("PF_GROUP_GENERAL", 0) != 0;
+    const bool general = ragged_c || cpg % vec != 0 || (vpg & (vpg - 1)) != 0 || vpg > 64 || env_int("PF_GROUP_GENERAL", 0) != 0 ||
+                         (p->stats_only && es == 2);  // (statistics for a chain of several kernels: never from packed pairs, see below)
     if (general && G > 512) return fail(PF_ERR_UNSUPPORTED, "more than 512 groups");
     if (samples * hw > 0xffffffffLL || samples > 65535) return fail(PF_ERR_UNSUPPORTED, "tensor too large for the group family");
     for (int i = 0; i < L.pro.n; ++i)
@@ -790,7 +791,8 @@ pf_status plan_group(pf_plan_s* p, int forced_variant) {
     // 2: statistics straight from the packed 16-bit pairs (needs pairs that never straddle groups and nothing but the
     // load in front of the normalisation; the kernel checks the rest at compile time)
     // 3: channel counts that are not whole vectors; 4: both
-    const bool packed_stats = cpg % 2 == 0 && L.main_dtype != PF_F32 && L.pro.n == 1;
+    // (a chain of several kernels kept its statistics in fp32 from widened values, running mean by running mean: it still does)
+    const bool packed_stats = cpg % 2 == 0 && L.main_dtype != PF_F32 && L.pro.n == 1 && !p->stats_only;
     const int gen_parts = !general ? 0 : ragged_c ? (packed_stats ? 4 : 3) : (packed_stats ? 2 : 1);
     g.spin_limit = (uint32_t)env_int("PF_GROUP_SPIN_LIMIT", 1 << 22);  // polls before a wait gives up (tests force it small)
     p->family = PF_FAMILY_GROUP;
@@ -908,11 +910,11 @@ pf_status plan_group(pf_plan_s* p, int forced_variant) {
         p->grid = dim3((uint32_t)tiles);
         p->grid2 = p->grid;
         p->block2 = p->block;
-        p->n_launches = 2;
+        p->n_launches = p->stats_only ? 1 : 2;
         if (jit_ok) {
             p->jit_fn = pf::jit_group_kernel(p->device, L.main_dtype, nv, 1, gen_parts, jspec, &jit_err);
-            p->jit_fn2 = p->jit_fn ? pf::jit_group_kernel(p->device, L.main_dtype, nv, 2, gen_parts, jspec, &jit_err) : nullptr;
-            if (p->jit_fn && p->jit_fn2) p->spec_id = pf::kSpecJit;
+            if (p->jit_fn && !p->stats_only) p->jit_fn2 = pf::jit_group_kernel(p->device, L.main_dtype, nv, 2, gen_parts, jspec, &jit_err);
+            if (p->jit_fn && (p->jit_fn2 || p->stats_only)) p->spec_id = pf::kSpecJit;
         }
         // (tiles of 12 steps exist in plan-time specialised form only)
         if (nv == 12 && p->spec_id != pf::kSpecJit) return fail(PF_ERR_UNSUPPORTED, "plan-time specialisation failed for the two-launch kernels: %s", jit_err.c_str());
@@ -1299,6 +1301,12 @@ pf_status plan_pool(pf_plan_s* p) {
         g.merge_rows = (uint32_t)std::max<int64_t>(1, 512 / ch);
         p->ws_error = g.ws_error;
     }
+    if (L.norm_op >= 0) {
+        g.norm_groups = (uint32_t)L.groups;
+        g.norm_lanes = 1;
+        while (g.norm_lanes < 64u && g.norm_lanes * 2u * g.norm_groups <= 512u) g.norm_lanes *= 2u;
+        g.div_norm_cpg = make_fastdiv((uint32_t)(ch / L.groups));
+    }
     if (jit_possible(p->device)) {
         std::string err;
         p->jit_fn = pf::jit_pool_kernel(p->device, L.main_dtype, nv, L.pool_op, ragged_c, make_jit_spec(L), &err);
@@ -1426,7 +1434,7 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     return PF_OK;
 }
 
-pf_status plan_checked_desc(const pf_chain_desc* desc, int32_t device, int32_t variant, pf_plan** out) {
+pf_status plan_checked_desc(const pf_chain_desc* desc, int32_t device, int32_t variant, pf_plan** out, PlanMode mode) {
     Checked c;
     pf_status s = check_desc(desc, &c);
     if (s != PF_OK) return s;
@@ -1440,7 +1448,10 @@ pf_status plan_checked_desc(const pf_chain_desc* desc, int32_t device, int32_t v
     memset(&p->group, 0, sizeof(p->group));
     memset(&p->permg, 0, sizeof(p->permg));
     memset(&p->attn, 0, sizeof(p->attn));
-    s = lower_chain(desc, c, &p->low);
+    p->stats_only = mode == PLAN_GROUP_STATISTICS;
+    s = lower_chain(desc, c, &p->low, mode == PLAN_POOL_WITH_NORM);
+    if (s == PF_OK && ((p->stats_only && p->low.core != pf::CORE_GROUPNORM) || (mode == PLAN_POOL_WITH_NORM && p->low.norm_op < 0)))
+        s = fail(PF_ERR_UNSUPPORTED, "internal: not the chain this part was meant for");
     if (s == PF_OK && p->low.core != pf::CORE_ATTN_DECODE && p->low.core != pf::CORE_GATHER && p->low.core != pf::CORE_COLNORM) {
         const Lowered& L = p->low;
         p->args.n_full = L.n_full;
@@ -1476,7 +1487,7 @@ pf_status plan_checked_desc(const pf_chain_desc* desc, int32_t device, int32_t v
         for (int k = 0; k < desc->n_inputs; ++k) p->in_bytes[k] = (uint64_t)numel(c.shape[k]) * dtype_size(desc->inputs[k].dtype);
         for (int o = 0; o < desc->n_outputs; ++o) {
             p->out_shape[o] = c.shape[desc->out_value[o]];
-            p->out_bytes[o] = (uint64_t)numel(p->out_shape[o]) * dtype_size(desc->out_dtype[o]);
+            p->out_bytes[o] = p->stats_only ? 0 : (uint64_t)numel(p->out_shape[o]) * dtype_size(desc->out_dtype[o]);
         }
         if (env_int("PF_LOG", 0))
             fprintf(stderr, "[pf_chain] family=%d variant=%d spec=%d k=%d rpw=%u grid=%u block=%u uops=%d+%d full=%d vec=%d tmp=%d mask_si=%u\n",

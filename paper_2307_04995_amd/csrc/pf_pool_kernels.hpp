@@ -9,7 +9,7 @@
 // per-channel partial result; the sample's last workgroup waits for those words, merges them, runs the epilogue
 // and stores -- the device-scope synchronisation of section 5.1.
 #pragma once
-#include "pf_row_kernels.hpp"
+#include "pf_group_kernels.hpp"
 
 namespace pf {
 
@@ -31,6 +31,24 @@ constexpr uint32_t kPoolEmpty = ~0u;
 PF_DEVICE uint32_t pool_word(float x) {
     const uint32_t w = __builtin_bit_cast(uint32_t, x);
     return w == kPoolEmpty ? 0x7fc00000u : w;
+}
+
+// A group normalisation in front of the pooling (U_GNORM in the prologue).  Its statistics come from an earlier launch (the
+// group family's statistics kernel); a workgroup lies in one sample and a lane owns its channels, so mean and scale of
+// the lane's channels are merged once and every element costs a subtraction and a multiply-add.  The normalised
+// tensor, which only the pooling reads, never exists in memory: the chain reads x twice and writes the pooled
+// values, where a normalisation kernel and a pooling kernel with an fp32 tensor between them moved nine times x
+// (GroupNorm + SiLU + mean of [32, 64, 64, 320] fp16).
+template <int VEC>
+struct PoolNorm {
+    float mean[VEC], scale[VEC], shift[VEC];
+    template <int DT, int K, class Spec>
+    PF_DEVICE void operator()(int, const LaneState<DT, K, Spec>&) const {}
+};
+template <int VEC, int DT, class Spec>
+PF_DEVICE void hook_norm(const PoolNorm<VEC>& h, LaneState<DT, 1, Spec>& s) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) s.acc[e] = __builtin_fmaf(s.acc[e] - h.mean[e], h.scale[e], h.shift[e]);
 }
 
 // RAGGED: a channel count that is not a whole number of 16-byte vectors.  A position then starts at element alignment
@@ -62,6 +80,40 @@ __global__ void __launch_bounds__(512) pool_kernel(const ChainArgs a, const Pool
     auto load_full = [&](const void* base, uint64_t elem) {
         return RAGGED ? load_elems<DT>(base, elem, cnt, 0u, elem + (uint64_t)VEC <= total_elems) : load_stream(base, elem * S::ESIZE);
     };
+
+    // ---- mean and scale of the lane's channels
+    constexpr bool kNorm = Spec::kStatic && list_has<typename Spec::Pro>(U_GNORM);
+    PoolNorm<VEC> norm;
+    if constexpr (kNorm) {
+        GroupGeom gg;
+        gg.groups = g.norm_groups;
+        gg.lanes_per_group = g.norm_lanes;
+        gg.blocks_per_sample = g.norm_slices;
+        gg.ws_partial = const_cast<float*>(g.norm_partial);
+        uint32_t grp;
+        float mean, rstd;
+        if (combine_sample(gg, sample, a.eps, &grp, &mean, &rstd)) {
+            lds[grp * 2u] = mean;
+            lds[grp * 2u + 1u] = rstd;
+        }
+        constexpr int gs = Spec::kGamma, bs = Spec::kBeta;
+        float gm[VEC], bt[VEC];
+        const u32x4 graw = RAGGED ? load_vec_operand_elems<DT>(a.vec[gs], 0u, cvi * VEC, g.channels, active ? cnt : 0u)
+                                  : load_vec_operand<DT>(a.vec[gs], 0u, active ? cvi * VEC : 0u, g.channels);
+        const u32x4 braw = RAGGED ? load_vec_operand_elems<DT>(a.vec[bs], 0u, cvi * VEC, g.channels, active ? cnt : 0u)
+                                  : load_vec_operand<DT>(a.vec[bs], 0u, active ? cvi * VEC : 0u, g.channels);
+        S::unpack(graw, gm);
+        S::unpack(braw, bt);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const uint32_t my = fast_div(min(cvi * (uint32_t)VEC + (uint32_t)e, g.channels - 1u), g.div_norm_cpg);
+            norm.mean[e] = lds[my * 2u];
+            norm.scale[e] = lds[my * 2u + 1u] * gm[e];
+            norm.shift[e] = bt[e];
+        }
+        __syncthreads();  // (the area is used again below)
+    }
 
     // ---- the slice in chunks of NV position steps: the primary operand of a chunk first (all its loads in flight),
     // then position by position
@@ -102,7 +154,8 @@ __global__ void __launch_bounds__(512) pool_kernel(const ChainArgs a, const Pool
                         s.vraw[v][0] = RAGGED ? load_vec_operand_elems<DT, Spec::kVecMode>(a.vec[v], pos, s.col[0], g.channels, cnt)
                                               : load_vec_operand<DT, Spec::kVecMode>(a.vec[v], pos, s.col[0], g.channels);
                 }
-            run_program<DT, 1, Spec>(ProgView<typename Spec::Pro>{a.pro}, s, NoStore{});
+            if constexpr (kNorm) run_program<DT, 1, Spec>(ProgView<typename Spec::Pro>{a.pro}, s, norm);
+            else run_program<DT, 1, Spec>(ProgView<typename Spec::Pro>{a.pro}, s, NoStore{});
             if (valid_of(i)) {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) acc[e] = pool_combine<OP>(acc[e], s.acc[e]);
