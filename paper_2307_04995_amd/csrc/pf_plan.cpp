@@ -1253,6 +1253,7 @@ pf_status plan_pool(pf_plan_s* p) {
     g.div_cv = make_fastdiv(g.cv);
     g.pos_per_step = 512u / g.cv;
     g.inv_hw = 1.0f / (float)hw;
+    g.merge_rows = 1;
     for (int f = 0; f < L.n_full; ++f)
         if (L.full_is_epi[f]) g.epi_full_mask |= 1u << f;
     for (int v = 0; v < L.n_vec; ++v)
@@ -1262,6 +1263,10 @@ pf_status plan_pool(pf_plan_s* p) {
     // 21 us, 32: 17.7 us, 16: 17.1 us, 8: 19.5 us, 4: 28 us; with SiLU in front 32 slices are best).
     int nv = 8;
     while (nv > 1 && (int64_t)(nv / 2) * g.pos_per_step >= hw) nv /= 2;
+    // Half the chunk where whole ones would not give every compute unit two ([2, 28, 28, 256] fp16 7.0 -> 6.4 us, [128, 7, 7,
+    // 1280] 10.1 -> 9.7) and for element-aligned positions, whose eight loads and partial stores crowd the registers ([32, 56,
+    // 56, 244] 24.8 -> 19.9); elsewhere eight are as good or better ([32, 56, 56, 240] 13.6 against 14.0).
+    if (nv == 8 && (ragged_c || n * ((hw + 8 * g.pos_per_step - 1) / (8 * g.pos_per_step)) < 2 * n_cu)) nv = 4;
     const int forced_nv = env_int("PF_POOL_NV", 0);
     if (forced_nv == 1 || forced_nv == 2 || forced_nv == 4 || forced_nv == 8) nv = forced_nv;
     const int64_t chunk_pos = (int64_t)nv * g.pos_per_step;

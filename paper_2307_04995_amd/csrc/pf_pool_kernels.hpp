@@ -163,101 +163,91 @@ __global__ void __launch_bounds__(512) pool_kernel(const ChainArgs a, const Pool
         }
     }
 
-    // ---- the position steps of the workgroup, through LDS; lanes 0 .. cv - 1 end up with the slice's result
+    // ---- the position steps of the workgroup, through LDS: a thread per channel
 #pragma unroll
     for (int e = 0; e < VEC; ++e) lds[t * VEC + e] = acc[e];
     __syncthreads();
-    const bool owner = t < g.cv;  // pstep 0: lane t holds channel vector t
-    if (owner) {
-        for (uint32_t q = 1; q < g.pos_per_step; ++q)
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) acc[e] = pool_combine<OP>(acc[e], lds[(q * g.cv + t) * VEC + e]);
+    const uint32_t row_words = g.cv * (uint32_t)VEC;
+    auto slice_value = [&](uint32_t ch) {
+        float m = lds[ch];
+        for (uint32_t q = 1; q < g.pos_per_step; ++q) m = pool_combine<OP>(m, lds[q * row_words + ch]);
+        return m;
+    };
+    // A sample split over several workgroups: every slice but the last publishes its per-channel partial result as
+    // self-describing words (kPoolEmpty = not written in this launch; consecutive lanes, consecutive words); the sample's
+    // LAST slice (dispatched after the others) reads them all, re-reading the ones still empty, puts them back to empty for
+    // the next launch and merges.  The critical path is one coherent store followed by one coherent load: no flag, no wait
+    // for the stores' acknowledgement in between.
+    if (bx + 1u != g.blocks_per_sample) {
+        uint32_t* part = g.ws_partial + (uint64_t)(sample * g.blocks_per_sample + bx) * g.channels;
+        for (uint32_t ch = t; ch < g.channels; ch += 512u)
+            __hip_atomic_store(part + ch, pool_word(slice_value(ch)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
     }
-
-    if (g.blocks_per_sample > 1u) {
-        // ---- a sample split over several workgroups.  Every slice but the last publishes its per-channel partial
-        // result as self-describing words (kPoolEmpty = not written in this launch); the sample's LAST slice
-        // (dispatched after the others) reads them all, re-reading the ones still empty, puts them back to empty for
-        // the next launch and merges.  The critical path is one coherent store followed by one coherent load: no
-        // flag, no wait for the stores' acknowledgement in between.
-        // (the slice's result goes through LDS so that consecutive lanes store consecutive words: a wave then writes
-        // 256 contiguous bytes instead of 64 separate words)
-        __syncthreads();
-        if (owner) {
+    // The merger (a sample that is one slice merges nothing): merge_rows row groups of threads, each a channel per lane
+    // (consecutive lanes, consecutive words); row group r takes the slices r, r + merge_rows, ..., eight of them in flight
+    // at a time.  Every wait is bounded: after spin_limit re-reads the error word is set and the missing slice is left out.
+    const uint32_t others = g.blocks_per_sample - 1u;
+    const uint32_t r = t / g.channels;  // 0 for every thread when a position has 512 channels or more
+    uint32_t* base = g.ws_partial + (uint64_t)sample * g.blocks_per_sample * g.channels;
+    uint32_t spins = 0;
+    float merged[VEC];  // (channels > 512: a thread owns channels t, t + 512, ...: at most VEC of them)
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) lds[t * VEC + e] = acc[e];
-        }
-        __syncthreads();
-        if (bx + 1u != g.blocks_per_sample) {
-            uint32_t* part = g.ws_partial + (uint64_t)(sample * g.blocks_per_sample + bx) * g.channels;
-            for (uint32_t idx = t; idx < g.channels; idx += 512u)
-                __hip_atomic_store(part + idx, pool_word(lds[idx]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return;
-        }
-        // The merger: merge_rows row groups of threads, each a channel per lane (consecutive lanes, consecutive words);
-        // row group r takes the slices r, r + merge_rows, ..., eight of them in flight at a time.  Every wait is
-        // bounded: after spin_limit re-reads the error word is set and the missing slice is left out.
-        const uint32_t others = g.blocks_per_sample - 1u;
-        const uint32_t r = t / g.channels;  // 0 for every thread when a position has 512 channels or more
-        uint32_t* base = g.ws_partial + (uint64_t)sample * g.blocks_per_sample * g.channels;
-        uint32_t spins = 0;
-        float merged[VEC];  // (channels > 512: a thread owns channels t, t + 512, ...: at most VEC of them)
+    for (int k = 0; k < VEC; ++k) {
+        const uint32_t idx = t - r * g.channels + (uint32_t)k * 512u;
+        float m = pool_identity<OP>();
+        if (r < g.merge_rows && idx < g.channels && (k == 0 || g.channels > 512u)) {
+            if (r == 0u) m = slice_value(idx);  // the merger's own slice
+            for (uint32_t b0 = r; b0 < others; b0 += 8u * g.merge_rows) {
+                uint32_t w[8];
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) {
-            const uint32_t idx = t - r * g.channels + (uint32_t)k * 512u;
-            float m = pool_identity<OP>();
-            if (r < g.merge_rows && idx < g.channels && (k == 0 || g.channels > 512u)) {
-                if (r == 0u) m = lds[idx];  // the merger's own slice
-                for (uint32_t b0 = r; b0 < others; b0 += 8u * g.merge_rows) {
-                    uint32_t w[8];
+                for (int u = 0; u < 8; ++u) {
+                    const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
+                    w[u] = b < others ? __hip_atomic_load(base + (uint64_t)b * g.channels + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                      : pool_word(pool_identity<OP>());
+                }
+                // words still empty are re-read together (one trip to memory per round, not one per word)
+                for (;;) {
+                    bool waiting = false;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) waiting = waiting || w[u] == kPoolEmpty;
+                    if (!waiting) break;
+                    if (++spins > g.spin_limit) {
+                        __hip_atomic_store(g.ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(8);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
-                        w[u] = b < others ? __hip_atomic_load(base + (uint64_t)b * g.channels + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                          : pool_word(pool_identity<OP>());
-                    }
-                    // words still empty are re-read together (one trip to memory per round, not one per word)
-                    for (;;) {
-                        bool waiting = false;
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) waiting = waiting || w[u] == kPoolEmpty;
-                        if (!waiting) break;
-                        if (++spins > g.spin_limit) {
-                            __hip_atomic_store(g.ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(8);
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
-                            if (w[u] == kPoolEmpty) w[u] = __hip_atomic_load(base + (uint64_t)b * g.channels + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
-                        if (b >= others || w[u] == kPoolEmpty) continue;
-                        __hip_atomic_store(base + (uint64_t)b * g.channels + idx, kPoolEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        m = pool_combine<OP>(m, __builtin_bit_cast(float, w[u]));
+                        if (w[u] == kPoolEmpty) w[u] = __hip_atomic_load(base + (uint64_t)b * g.channels + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
                 }
-            }
-            merged[k] = m;
-        }
-        __syncthreads();  // (everyone has read its own slice's values)
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) {
-            const uint32_t idx = t - r * g.channels + (uint32_t)k * 512u;
-            if (r < g.merge_rows && idx < g.channels && (k == 0 || g.channels > 512u)) lds[r * g.channels + idx] = merged[k];
-        }
-        __syncthreads();
-        if (owner) {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                float m = lds[t * VEC + e];
-                for (uint32_t q = 1; q < g.merge_rows; ++q) m = pool_combine<OP>(m, lds[q * g.channels + t * VEC + e]);
-                acc[e] = m;
+                for (int u = 0; u < 8; ++u) {
+                    const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
+                    if (b >= others || w[u] == kPoolEmpty) continue;
+                    __hip_atomic_store(base + (uint64_t)b * g.channels + idx, kPoolEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    m = pool_combine<OP>(m, __builtin_bit_cast(float, w[u]));
+                }
             }
+        }
+        merged[k] = m;
+    }
+    __syncthreads();  // (everyone has read its own slice's values)
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) {
+        const uint32_t idx = t - r * g.channels + (uint32_t)k * 512u;
+        if (r < g.merge_rows && idx < g.channels && (k == 0 || g.channels > 512u)) lds[r * g.channels + idx] = merged[k];
+    }
+    __syncthreads();
+    const bool owner = t < g.cv;  // lane t: channel vector t of the result
+    if (owner) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            float m = lds[t * VEC + e];
+            for (uint32_t q = 1; q < g.merge_rows; ++q) m = pool_combine<OP>(m, lds[q * g.channels + t * VEC + e]);
+            acc[e] = m;
         }
     }
     if (!owner) return;
