@@ -5,34 +5,45 @@
 namespace pf {
 
 template <int DT, bool RMS, bool RAGGED>
-static hipError_t launch_colnorm_dt(const ColArgs& a, int kc, dim3 grid, hipStream_t st) {
-    switch (kc) {
-        case 1: hipLaunchKernelGGL((colnorm_kernel<DT, 1, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
-        case 2: hipLaunchKernelGGL((colnorm_kernel<DT, 2, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
-        case 3: hipLaunchKernelGGL((colnorm_kernel<DT, 3, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
-        case 4: hipLaunchKernelGGL((colnorm_kernel<DT, 4, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
-        case 6: hipLaunchKernelGGL((colnorm_kernel<DT, 6, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
-        case 8: hipLaunchKernelGGL((colnorm_kernel<DT, 8, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
-        case 12: hipLaunchKernelGGL((colnorm_kernel<DT, 12, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
-        case 16: hipLaunchKernelGGL((colnorm_kernel<DT, 16, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
-        case 24: hipLaunchKernelGGL((colnorm_kernel<DT, 24, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
-        case 32: hipLaunchKernelGGL((colnorm_kernel<DT, 32, RMS, RAGGED>), grid, dim3(256), 0, st, a); break;
+static hipError_t launch_colnorm_dt(const ColArgs& a, int kc, int threads, dim3 grid, hipStream_t st) {
+#define PF_COL_CASE(T, KC)                                                                                        \
+    case T * 64 + KC: hipLaunchKernelGGL((colnorm_kernel<DT, KC, RMS, RAGGED, T>), grid, dim3(T), 0, st, a); break;
+    switch (threads * 64 + kc) {
+        PF_COL_CASE(256, 1)
+        PF_COL_CASE(256, 2)
+        PF_COL_CASE(256, 3)
+        PF_COL_CASE(256, 4)
+        PF_COL_CASE(256, 6)
+        PF_COL_CASE(256, 8)
+        PF_COL_CASE(256, 12)
+        PF_COL_CASE(256, 16)
+        PF_COL_CASE(256, 24)
+        PF_COL_CASE(256, 32)
+        PF_COL_CASE(512, 2)
+        PF_COL_CASE(512, 3)
+        PF_COL_CASE(512, 4)
+        PF_COL_CASE(1024, 2)
+        PF_COL_CASE(1024, 3)
+        PF_COL_CASE(1024, 4)
+        PF_COL_CASE(1024, 6)
+        PF_COL_CASE(1024, 8)
         default: return hipErrorInvalidValue;
     }
+#undef PF_COL_CASE
     return hipGetLastError();
 }
 
 template <int DT>
-static hipError_t launch_colnorm_kind(const ColArgs& a, int kc, bool rms, bool ragged, dim3 grid, hipStream_t st) {
-    if (ragged) return rms ? launch_colnorm_dt<DT, true, true>(a, kc, grid, st) : launch_colnorm_dt<DT, false, true>(a, kc, grid, st);
-    return rms ? launch_colnorm_dt<DT, true, false>(a, kc, grid, st) : launch_colnorm_dt<DT, false, false>(a, kc, grid, st);
+static hipError_t launch_colnorm_kind(const ColArgs& a, int kc, int threads, bool rms, bool ragged, dim3 grid, hipStream_t st) {
+    if (ragged) return rms ? launch_colnorm_dt<DT, true, true>(a, kc, threads, grid, st) : launch_colnorm_dt<DT, false, true>(a, kc, threads, grid, st);
+    return rms ? launch_colnorm_dt<DT, true, false>(a, kc, threads, grid, st) : launch_colnorm_dt<DT, false, false>(a, kc, threads, grid, st);
 }
 
-hipError_t launch_colnorm(int dtype, const ColArgs& a, int kc, bool rms, bool ragged, dim3 grid, hipStream_t st) {
+hipError_t launch_colnorm(int dtype, const ColArgs& a, int kc, int threads, bool rms, bool ragged, dim3 grid, hipStream_t st) {
     switch (dtype) {
-        case DT_F32: return launch_colnorm_kind<DT_F32>(a, kc, rms, ragged, grid, st);
-        case DT_F16: return launch_colnorm_kind<DT_F16>(a, kc, rms, ragged, grid, st);
-        case DT_BF16: return launch_colnorm_kind<DT_BF16>(a, kc, rms, ragged, grid, st);
+        case DT_F32: return launch_colnorm_kind<DT_F32>(a, kc, threads, rms, ragged, grid, st);
+        case DT_F16: return launch_colnorm_kind<DT_F16>(a, kc, threads, rms, ragged, grid, st);
+        case DT_BF16: return launch_colnorm_kind<DT_BF16>(a, kc, threads, rms, ragged, grid, st);
         default: return hipErrorInvalidValue;
     }
 }

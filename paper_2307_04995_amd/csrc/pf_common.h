@@ -206,6 +206,7 @@ struct ColArgs {
     uint32_t c, s;            // normalised extent; elements after it
     uint32_t s_vecs;          // s in 16-byte vectors
     uint32_t tiles_per_outer; // workgroups per outer index: ceil(s_vecs / 8)
+    uint32_t tiles, tiles_per_die;  // workgroups in all; ceil(tiles / 8)
     float inv_c, eps;
 };
 

@@ -22,9 +22,9 @@ hipError_t launch_group(int phase, bool general, int spec_id, int dtype, const C
 hipError_t launch_attn_decode(int dtype, const AttnArgs& a, int variant, int nv, dim3 grid, hipStream_t st);
 hipError_t launch_stencil(int dtype, const ChainArgs& a, const StencilGeom& g, int variant, int ks, uint32_t lds, dim3 grid, hipStream_t st);
 hipError_t launch_pool(int dtype, const ChainArgs& a, const PoolGeom& g, int op, int nv, dim3 grid, hipStream_t st);
-// kc: 16-byte vectors per lane (the normalised extent is at most 32 * kc); one of 1, 2, 4, 16, 32 (eight vectors per
-// lane compile to 240 registers, twice what sixteen need, so that size is left out)
-hipError_t launch_colnorm(int dtype, const ColArgs& a, int kc, bool rms, bool ragged, dim3 grid, hipStream_t st);
+// kc: 16-byte vectors per lane (the normalised extent is at most threads / 8 * kc); the built combinations are listed in
+// pf_col.hip
+hipError_t launch_colnorm(int dtype, const ColArgs& a, int kc, int threads, bool rms, bool ragged, dim3 grid, hipStream_t st);
 hipError_t launch_gather(int dtype, const GatherArgs& a, int k, dim3 grid, hipStream_t st);
 int group_resident_blocks_per_cu(int spec_id, int dtype, int nv, int block_threads);
 // whole-tensor storage conversion, 16-bit <-> fp32 (n elements)

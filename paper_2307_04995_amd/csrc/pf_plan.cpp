@@ -1337,16 +1337,29 @@ pf_status plan_column(pf_plan_s* p) {
     a.tiles_per_outer = (uint32_t)tiles;
     a.inv_c = 1.0f / (float)L.col_c;
     a.eps = L.eps;
-    // vectors per lane: the smallest instantiated count that holds the column (32 row groups per workgroup)
-    p->k = 32;
+    a.tiles = (uint32_t)(L.col_outer * tiles);
+    a.tiles_per_die = (a.tiles + 7u) / 8u;
+    // Lanes per workgroup.  Few slabs: more lanes share one, so that a compute unit that holds one or two still has its
+    // loads in flight and each lane fewer rows behind each other ([64, 384, 14, 14] fp16, 256 slabs: 17.1 us with 256 lanes,
+    // 11.2 with 512, 10.0 with 1024; [256, 768, 7, 7] 27.0, 20.5, 17.6; 512 slabs of 512 rows 15.4, 14.7, 14.5).  From about
+    // three slabs per unit on 256 lanes are as good (832 slabs of 192 rows: 12.8, 12.8, 14.3) and then better (3136 of 96:
+    // 18.5, 20.9, 31.6).  Short columns do not fill the row groups of more lanes.
+    // (A plan made without a device, whose unit count is unknown, takes 256.)
+    hipDeviceProp_t prop;
+    const int n_cu = (hipGetDeviceProperties(&prop, p->device) == hipSuccess && prop.multiProcessorCount > 0) ? prop.multiProcessorCount : 0;
+    int threads = a.tiles > 2u * (uint32_t)n_cu || L.col_c <= 128 ? 256 : L.col_c <= 256 ? 512 : 1024;
+    const int forced_t = env_int("PF_COL_THREADS", 0);
+    if (forced_t == 256 || (forced_t == 512 && L.col_c <= 256) || forced_t == 1024) threads = forced_t;
+    // vectors per lane: the smallest instantiated count that holds the column (threads / 8 row groups per workgroup)
+    p->k = 8192 / threads;
     for (int kc : {24, 16, 12, 8, 6, 4, 3, 2, 1})
-        if ((int64_t)kc * 32 >= L.col_c) p->k = kc;
+        if ((int64_t)kc * (threads / 8) >= L.col_c && (kc > 1 || threads == 256)) p->k = kc;
     p->family = PF_FAMILY_COLUMN;
     p->variant = 0;
     p->spec_id = 0;
-    p->grid = dim3((uint32_t)(L.col_outer * tiles));
-    p->block = dim3(256);
-    p->lds_bytes = 4 * 8 * (uint32_t)vec * 4;
+    p->grid = dim3(a.tiles_per_die * 8u);
+    p->block = dim3((uint32_t)threads);
+    p->lds_bytes = (uint32_t)(4 * (threads / 64) * 8 * vec + 2 * std::min(1024, p->k * threads / 8)) * 4;
     p->n_launches = 1;
     return PF_OK;
 }
