@@ -285,4 +285,14 @@ struct PermGeom {
     uint32_t t_out_stride_i;  // tile variant: output stride (elements) of the input's innermost dim
 };
 
+// Transpose family, plane variant: [planes, a, b] -> [planes, b, a], a layout-only chain.
+struct PlaneGeom {
+    uint32_t a, b;
+    uint32_t step;               // rows (flat input) or columns (flat output) of a plane per workgroup
+    uint32_t strips, strips_per_die;
+    FastDiv div_strips;          // strips per plane
+    FastDiv div_a;
+    uint64_t total;              // elements of the tensor
+};
+
 }  // namespace pf

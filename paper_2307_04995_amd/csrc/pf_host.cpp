@@ -302,7 +302,9 @@ pf_status pf_chain_run(const pf_plan* plan, const void* const* inputs, void* con
             }
             break;
         case PF_FAMILY_TRANSPOSE:
-            if (plan->spec_id == pf::kSpecJit) {
+            if (plan->perm_plane) {
+                e = pf::launch_perm_plane(L.main_dtype, plan->perm_plane == 2, a.full[0], a.out[0], plan->planeg, plan->grid, plan->lds_bytes, st);
+            } else if (plan->spec_id == pf::kSpecJit) {
                 pf::PermGeom g = plan->permg;
                 void* params[] = {&a, &g};
                 e = pf::jit_launch(plan->jit_fn, plan->grid, plan->block, plan->variant == PF_VARIANT_T_LDS_ROWS ? plan->lds_bytes : 0u, params, st);

@@ -132,6 +132,8 @@ struct pf_plan_s {
     pf::ColArgs col;
     int stencil_ks = 3;       // kernel extent of the depthwise convolution
     int row_log2l = 6;        // row family: log2 of the lanes of a wave that share a row
+    int perm_plane = 0;          // transpose family: 1 / 2 = the plane variant with a flat input / output
+    pf::PlaneGeom planeg;
     bool stats_only = false;     // group family: the statistics launch alone runs (a pooling normalises with them)
     bool row_held = false;       // row family: the row is held packed in the registers of one workgroup (row_held_kernel)
     pf::BcastTerm bcast_host[PF_DEV_MAX_VEC][PF_DEV_MAX_BCAST_TERMS];  // general broadcasting terms, staged on the host

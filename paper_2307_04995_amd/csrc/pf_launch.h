@@ -16,6 +16,7 @@ hipError_t launch_ew(int dtype, const ChainArgs& a, uint32_t total_vecs, uint32_
                      dim3 grid, hipStream_t st);
 hipError_t launch_perm(int spec_id, int dtype, const ChainArgs& a, const PermGeom& g, int variant, int k, bool ragged, dim3 grid,
                        dim3 block, uint32_t lds, hipStream_t st);
+hipError_t launch_perm_plane(int dtype, bool flat_out, const void* in, void* out, const PlaneGeom& g, dim3 grid, uint32_t lds, hipStream_t st);
 // phase 0: fused (resident) kernel; 1: statistics launch; 2: normalisation launch
 hipError_t launch_group(int phase, bool general, int spec_id, int dtype, const ChainArgs& a, const GroupGeom& g, int nv, uint32_t tiles,
                         dim3 grid, dim3 block, uint32_t lds, hipStream_t st);

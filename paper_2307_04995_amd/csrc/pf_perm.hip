@@ -70,6 +70,18 @@ hipError_t launch_perm(int spec_id, int dtype, const ChainArgs& a, const PermGeo
     }
 }
 
+hipError_t launch_perm_plane(int dtype, bool flat_out, const void* in, void* out, const PlaneGeom& g, dim3 grid, uint32_t lds, hipStream_t st) {
+    // (the bits travel untouched: the element size is all that matters of the type)
+    if (dtype == DT_F32) {
+        if (flat_out) hipLaunchKernelGGL((perm_plane_kernel<DT_F32, true>), grid, dim3(256), lds, st, in, out, g);
+        else hipLaunchKernelGGL((perm_plane_kernel<DT_F32, false>), grid, dim3(256), lds, st, in, out, g);
+    } else {
+        if (flat_out) hipLaunchKernelGGL((perm_plane_kernel<DT_F16, true>), grid, dim3(256), lds, st, in, out, g);
+        else hipLaunchKernelGGL((perm_plane_kernel<DT_F16, false>), grid, dim3(256), lds, st, in, out, g);
+    }
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------------------------
 // copy probe: the plain streaming copy every chain is measured against
 // ---------------------------------------------------------------------------------------------
