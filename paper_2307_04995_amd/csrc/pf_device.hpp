@@ -420,14 +420,10 @@ PF_DEVICE float pf_gelu_erf(float x) {
     const float q = 0.5f * poly * t * __builtin_amdgcn_exp2f(-z * z * kLog2e);
     return x * (x < 0.0f ? q : 1.0f - q);
 }
-PF_DEVICE float pf_max_nan(float a, float b) {
-    float r = fmaxf(a, b);
-    return (a != a || b != b) ? __builtin_nanf("") : r;
-}
-PF_DEVICE float pf_min_nan(float a, float b) {
-    float r = fminf(a, b);
-    return (a != a || b != b) ? __builtin_nanf("") : r;
-}
+// maximum and minimum that keep a NaN: one instruction each on this device (v_maximum3_f32 / v_minimum3_f32), where
+// fmaxf and a NaN test are three
+PF_DEVICE float pf_max_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+PF_DEVICE float pf_min_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 
 // ---------------------------------------------------------------------------------------------
 // chain specifications: how a kernel learns what the chain looks like
@@ -465,6 +461,7 @@ struct GenericSpec {
     static constexpr bool kStatic = false;
     static constexpr bool kBcast = true;  // general broadcasting of operands is a run-time property here
     static constexpr int kVecMode = 3;    // ... and so is a broadcast operand with a single element
+    static constexpr bool kVecChannel = false;
     static constexpr int NF = 3, NV = 4, NT = PF_DEV_MAX_TMP;
     using Pro = DynList;
     using Epi = DynList;
@@ -476,7 +473,8 @@ struct GenericSpec {
 };
 
 // FLAGS_: bit 0 = some operand broadcasts the general way (extents of 1 anywhere); bit 1 = some broadcast operand has a
-// single element.  Kernels built without a bit carry none of that case's code: the one-element case in particular
+// single element; bit 2 (stencil family) = every broadcast operand is indexed by channel alone, whatever the position, so
+// it is loaded once.  Kernels built without a bit carry none of that case's code: the one-element case in particular
 // costs more than its branch, because the compiler issues its 2-byte load next to the 16-byte one and waits for both
 // before it goes on, which turns the operand loads of a kernel into one memory round trip after the other.
 template <int NF_, int NV_, int NT_, int CORE_, int GAMMA_, int BETA_, class ProL, class EpiL, int FLAGS_ = 0>
@@ -484,6 +482,7 @@ struct StaticSpec {
     static constexpr bool kStatic = true;
     static constexpr bool kBcast = (FLAGS_ & 1) != 0;
     static constexpr int kVecMode = FLAGS_ & 3;
+    static constexpr bool kVecChannel = (FLAGS_ & 4) != 0;
     static constexpr int NF = NF_, NV = NV_, NT = NT_;
     static constexpr int kGamma = GAMMA_, kBeta = BETA_;
     using Pro = ProL;
@@ -525,6 +524,23 @@ constexpr bool list_keeps_storage_precision() {
         if (!load && !exact) return false;
     }
     return true;
+}
+
+// ... and such a list applied to the packed vector itself, where the type has packed arithmetic (fp16: two elements an
+// instruction, nothing widened and rounded back).
+template <int DT, class L>
+PF_DEVICE u32x4 run_packed(u32x4 raw) {
+    static_assert(DT == DT_F16 && list_keeps_storage_precision<L>(), "a load and steps exact in fp16");
+#pragma unroll
+    for (int i = 1; i < L::n; ++i) {
+        if (L::at(i).code == U_RELU) {
+            const f16x8 zero = {};
+            raw = __builtin_bit_cast(u32x4, __builtin_elementwise_maximum(__builtin_bit_cast(f16x8, raw), zero));
+        } else {  // U_NEG
+            raw ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
+        }
+    }
+    return raw;
 }
 
 // ---------------------------------------------------------------------------------------------

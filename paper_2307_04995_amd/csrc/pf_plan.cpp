@@ -1019,6 +1019,12 @@ pf_status plan_stencil(pf_plan_s* p, const Checked& c, int forced_variant) {
     p->stencil_ks = ksz;
     p->args.n_inner = (uint32_t)ch;
     p->args.rows = (uint64_t)(n * h * w);
+    // broadcast operands indexed by channel alone (a bias) are loaded once per lane, not once per position
+    pf::JitSpec jspec = make_jit_spec(L);
+    bool by_channel = true;
+    for (int v = 0; v < L.n_vec; ++v)
+        if (v != L.core_vec[0] && (p->args.vec[v].numel > (uint32_t)ch || p->args.vec[v].n_terms != 0)) by_channel = false;
+    if (by_channel) jspec.flags |= 4;
     const pf_op_desc& conv = p->desc.ops[L.core_op];
     const int64_t stride = conv.n_i == 1 ? conv.i[0] : 1;
     if (stride > 1) {
@@ -1044,7 +1050,7 @@ pf_status plan_stencil(pf_plan_s* p, const Checked& c, int forced_variant) {
         p->grid = dim3((uint32_t)tiles_x, (uint32_t)((oh + strip - 1) / strip), (uint32_t)n);
         if (jit_possible(p->device)) {
             std::string err;
-            p->jit_fn = pf::jit_stencil_kernel(p->device, L.main_dtype, p->variant, ksz, ragged_c, make_jit_spec(L), &err);
+            p->jit_fn = pf::jit_stencil_kernel(p->device, L.main_dtype, p->variant, ksz, ragged_c, jspec, &err);
             if (p->jit_fn) p->spec_id = pf::kSpecJit;
             else note_interpreter_fallback(p, err);
         }
@@ -1088,7 +1094,7 @@ pf_status plan_stencil(pf_plan_s* p, const Checked& c, int forced_variant) {
     }
     if (jit_ok) {
         std::string err;
-        p->jit_fn = pf::jit_stencil_kernel(p->device, L.main_dtype, variant, ksz, ragged_c, make_jit_spec(L), &err);
+        p->jit_fn = pf::jit_stencil_kernel(p->device, L.main_dtype, variant, ksz, ragged_c, jspec, &err);
         if (p->jit_fn) p->spec_id = pf::kSpecJit;
         else {
             note_interpreter_fallback(p, err);

@@ -22,7 +22,7 @@ PF_DEVICE float pool_identity() { return OP == POOL_MAX ? -__builtin_inff() : 0.
 template <int OP>
 PF_DEVICE float pool_combine(float acc, float x) {
     if (OP != POOL_MAX) return acc + x;
-    return (x != x) ? x : ((acc != acc) ? acc : fmaxf(acc, x));
+    return pf_max_nan(acc, x);
 }
 
 // A partial result as a published word: all-ones means "not written in this launch" (a NaN that arithmetic never

@@ -183,10 +183,16 @@ __global__ void __launch_bounds__(256) dwconv3x3_kernel(const ChainArgs a, const
 // from the tile.  The prologue runs about 1.3 times per input value (halo rows and columns), the loads of a
 // whole strip are in flight together, and no window lives in registers.
 //
+// Bound: the chain load -> LDS -> taps -> store of a workgroup, four workgroups to a compute unit (40 KB of LDS each on
+// [32, 56, 56, 240]); the multiply-adds and the tile's reads are each about a quarter of the time.  RELU + 3 x 3 + bias on that
+// tensor, 96 MB: 24.9 us with the bias fetched per output row (each fetch waited for the row's store in front of it), staging
+// loads behind guards and RELU widened to fp32 and back; 21.0 us now.  5 x 5 on [32, 28, 28, 240]: bf16 35.5 -> 22.2, fp32 on
+// half of it 21.5 -> 17.4.
+//
 // LDS layout: tile[input row 0..7][staging lane 0 .. 256 + 2 cv), entries of 16 bytes (packed storage type, when
 // the prologue keeps storage precision) or 32 bytes (fp32).  Lanes read consecutive entries: no bank conflicts.
 template <int DT, class Spec, int KS, bool RAGGED = false>
-__global__ void __launch_bounds__(256) dwconv_staged_kernel(const ChainArgs a, const StencilGeom g) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Spec::kStatic && KS == 3 ? 4 : 1))) dwconv_staged_kernel(const ChainArgs a, const StencilGeom g) {
     using S = Storage<DT>;
     constexpr int VEC = S::VEC;
     constexpr bool kPacked = DT != DT_F32 && list_keeps_storage_precision<typename Spec::Pro>();
@@ -218,66 +224,89 @@ __global__ void __launch_bounds__(256) dwconv_staged_kernel(const ChainArgs a, c
 
     LaneState<DT, 1, Spec> s;
 
-    // ---- stage: staging lane j of input row h0 - R + r holds image lane t0 - R * cv + j
-    for (uint32_t j = threadIdx.x; j < tw; j += 256u) {
-        const int64_t lane_pos = (int64_t)t0 - (int64_t)R * cv + j;
-        const bool lane_ok = lane_pos >= 0 && lane_pos < (int64_t)g.row_vecs;
-        const uint32_t lp = lane_ok ? (uint32_t)lane_pos : 0u;
-        const uint32_t wcol = fast_div(lp, g.div_cv);
-        const uint32_t cvi = lp - wcol * cv;
-        constexpr bool ragged = RAGGED;
-        const uint32_t cnt = ragged ? elems_below<Storage<DT>::VEC>(cvi * (uint32_t)Storage<DT>::VEC, g.c) : (uint32_t)Storage<DT>::VEC;
-        s.col[0] = cvi * VEC;
-        u32x4 pend_f[kRows][at_least_1(Spec::NF)];
+    // ---- stage: staging lane j of input row h0 - R + r holds image lane t0 - R * cv + j.  Two staging lanes per lane at a
+    // time (256 and the halo, unless a position has more than 128 vectors): their rows are all requested before the first is
+    // worked on.  No branch around a load: what lies outside the image reads a vector that exists and becomes zero in the tile.
+    constexpr bool ragged = RAGGED;
+    constexpr int kPair = 2;
+    for (uint32_t j0 = threadIdx.x; j0 < tw; j0 += 256u * kPair) {
+        uint32_t lp[kPair], cvi_j[kPair], wcol_j[kPair];
+        bool lane_ok[kPair];
+        u32x4 pend_f[kPair][kRows][at_least_1(Spec::NF)];
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const int row = (int)h0 - R + r;
-            const bool ok = lane_ok && row >= 0 && row < (int)g.h;
-            const uint32_t pos = (sample * g.h + (uint32_t)(ok ? row : 0)) * g.w + wcol;
+        for (int u = 0; u < kPair; ++u) {
+            const int64_t lane_pos = (int64_t)t0 - (int64_t)R * cv + j0 + 256u * (uint32_t)u;
+            lane_ok[u] = j0 + 256u * (uint32_t)u < tw && lane_pos >= 0 && lane_pos < (int64_t)g.row_vecs;
+            lp[u] = lane_ok[u] ? (uint32_t)lane_pos : 0u;
+            wcol_j[u] = fast_div(lp[u], g.div_cv);
+            cvi_j[u] = lp[u] - wcol_j[u] * cv;
+            const uint32_t cnt = ragged ? elems_below<Storage<DT>::VEC>(cvi_j[u] * (uint32_t)Storage<DT>::VEC, g.c) : (uint32_t)Storage<DT>::VEC;
 #pragma unroll
-            for (int f = 0; f < Spec::NF; ++f) {
-                pend_f[r][f] = u32x4{0u, 0u, 0u, 0u};
-                if (f < Spec::n_full(a) && ((pro_full >> f) & 1u) && ok)
-                    pend_f[r][f] = stencil_load<DT>(a.full[f], (uint64_t)pos * g.c + cvi * VEC, ragged, cnt, (uint64_t)g.n * g.h * g.w * g.c);
+            for (int r = 0; r < kRows; ++r) {
+                const int row = (int)h0 - R + r;
+                const bool row_ok = row >= 0 && row < (int)g.h;  // (the same for the workgroup)
+                const uint32_t pos = (sample * g.h + (uint32_t)(row_ok ? row : (int)h0)) * g.w + wcol_j[u];
+#pragma unroll
+                for (int f = 0; f < Spec::NF; ++f)
+                    if (f < Spec::n_full(a) && ((pro_full >> f) & 1u))
+                        pend_f[u][r][f] = stencil_load<DT>(a.full[f], (uint64_t)pos * g.c + cvi_j[u] * VEC, ragged, cnt, (uint64_t)g.n * g.h * g.w * g.c);
             }
         }
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const int row = (int)h0 - R + r;
-            const bool ok = lane_ok && row >= 0 && row < (int)g.h;
-            if (ok) {
-                s.row[0] = (sample * g.h + (uint32_t)row) * g.w + wcol;
+        for (int u = 0; u < kPair; ++u) {
+            const uint32_t j = j0 + 256u * (uint32_t)u;
+            if (j >= tw) continue;
+            const uint32_t cnt = ragged ? elems_below<Storage<DT>::VEC>(cvi_j[u] * (uint32_t)Storage<DT>::VEC, g.c) : (uint32_t)Storage<DT>::VEC;
+            s.col[0] = cvi_j[u] * VEC;
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const int row = (int)h0 - R + r;
+                const bool ok = lane_ok[u] && row >= 0 && row < (int)g.h;
+                s.row[0] = (sample * g.h + (uint32_t)(ok ? row : (int)h0)) * g.w + wcol_j[u];
 #pragma unroll
                 for (int f = 0; f < Spec::NF; ++f)
-                    if (f < Spec::n_full(a) && ((pro_full >> f) & 1u)) s.fraw[f][0] = pend_f[r][f];
+                    if (f < Spec::n_full(a) && ((pro_full >> f) & 1u)) s.fraw[f][0] = pend_f[u][r][f];
 #pragma unroll
                 for (int v = 0; v < Spec::NV; ++v)
                     if (v < Spec::n_vec(a) && v != wslot && ((pro_vec >> v) & 1u))
                         s.vraw[v][0] = stencil_load_vec<DT, Spec::kVecMode>(a.vec[v], s.row[0], s.col[0], g.c, ragged, cnt);
-                run_program<DT, 1, Spec>(ProgView<typename Spec::Pro>{a.pro}, s, NoStore{});
-            }
-            u32x4* dst = tile + ((uint32_t)r * tw + j) * EV;
-            if (kPacked) {
-                dst[0] = ok ? S::pack(s.acc) : u32x4{0u, 0u, 0u, 0u};
-            } else {
-#pragma unroll
-                for (int q = 0; q < EV; ++q) {
+                u32x4* dst = tile + ((uint32_t)r * tw + j) * EV;
+                u32x4 packed = {0u, 0u, 0u, 0u};
+                if constexpr (kPacked && DT == DT_F16) {
+                    packed = run_packed<DT, typename Spec::Pro>(pend_f[u][r][Spec::Pro::at(0).slot]);
+                } else {
+                    run_program<DT, 1, Spec>(ProgView<typename Spec::Pro>{a.pro}, s, NoStore{});
+                    if (kPacked) packed = S::pack(s.acc);
+                }
+                if (kPacked) {
                     u32x4 w4;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) w4[e] = ok ? __builtin_bit_cast(uint32_t, s.acc[(q * 4 + e) % VEC]) : 0u;
-                    dst[q] = w4;
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t w = packed[e];
+                        w4[e] = ok ? w : 0u;
+                    }
+                    dst[0] = w4;
+                } else {
+#pragma unroll
+                    for (int q = 0; q < EV; ++q) {
+                        u32x4 w4;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) w4[e] = ok ? __builtin_bit_cast(uint32_t, s.acc[(q * 4 + e) % VEC]) : 0u;
+                        dst[q] = w4;
+                    }
                 }
             }
         }
     }
-    __syncthreads();
 
-    // ---- compute: lane t0 + tid, six output rows, nine taps each from the tile
+    // ---- what the lane's own channels need, requested in front of the barrier: kernel vectors and the epilogue's per-channel
+    // operands.  (Fetched row by row they cost far more than their bytes: memory operations of a wave complete in order, so
+    // waiting for a row's bias waits for the store of the row before as well.)
     const uint32_t t = t0 + threadIdx.x;
-    if (t >= g.row_vecs) return;
-    const uint32_t wcol = fast_div(t, g.div_cv);
-    const uint32_t cvi = t - wcol * cv;
-    constexpr bool ragged = RAGGED;
+    const bool lane_in = t < g.row_vecs;
+    const uint32_t t_safe = lane_in ? t : t0;
+    const uint32_t wcol = fast_div(t_safe, g.div_cv);
+    const uint32_t cvi = t_safe - wcol * cv;
     const uint32_t cnt = ragged ? elems_below<Storage<DT>::VEC>(cvi * (uint32_t)Storage<DT>::VEC, g.c) : (uint32_t)Storage<DT>::VEC;
     s.col[0] = cvi * VEC;
     // fp16 tile entries meet fp16 kernels: the multiply-add takes both halves of the packed registers directly
@@ -287,14 +316,26 @@ __global__ void __launch_bounds__(256) dwconv_staged_kernel(const ChainArgs a, c
     constexpr bool kKeepW = KS == 3;
     constexpr int NW = kKeepW ? KS * KS : 1;
     u32x4 wraw[NW];
-    float wf[(kMix || !kKeepW) ? 1 : NW][VEC];
     auto load_w = [&](int k) { return stencil_load<DT>(a.vec[wslot].ptr, (uint64_t)k * g.c + cvi * VEC, ragged, cnt); };
     if (kKeepW) {
 #pragma unroll
-        for (int k = 0; k < NW; ++k) {
-            wraw[k] = load_w(k);
-            if (!kMix) S::unpack(wraw[k], wf[k % ((kMix || !kKeepW) ? 1 : NW)]);
-        }
+        for (int k = 0; k < NW; ++k) wraw[k] = load_w(k);
+    }
+    u32x4 epi_v[at_least_1(Spec::NV)];
+    if (Spec::kVecChannel) {
+#pragma unroll
+        for (int v = 0; v < Spec::NV; ++v)
+            if (v < Spec::n_vec(a) && v != wslot && ((epi_vec >> v) & 1u))
+                epi_v[v] = stencil_load_vec<DT, Spec::kVecMode>(a.vec[v], 0u, s.col[0], g.c, ragged, cnt);
+    }
+    __syncthreads();
+
+    // ---- compute: lane t0 + tid, six output rows, nine taps each from the tile
+    if (!lane_in) return;
+    float wf[(kMix || !kKeepW) ? 1 : NW][VEC];
+    if (kKeepW && !kMix) {
+#pragma unroll
+        for (int k = 0; k < NW; ++k) S::unpack(wraw[k], wf[k % ((kMix || !kKeepW) ? 1 : NW)]);
     }
     // 5 x 5: the kernel vectors do not fit the registers beside the window, so the loops are turned inside out: a kernel
     // row's five vectors are fetched together (one trip to the cache per kernel row, not one per tap and output row) and
@@ -305,13 +346,22 @@ __global__ void __launch_bounds__(256) dwconv_staged_kernel(const ChainArgs a, c
         for (int i = 0; i < kOut; ++i)
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc_all[i % (kKeepW ? 1 : kOut)][e] = 0.0f;
-#pragma unroll
+        // (Unrolled, the compiler fetches and widens all 25 taps first and needs up to 500 registers, one wave per SIMD.  So the
+        // kernel rows stay a loop where values are widened, and fp16, which needs no widening, goes output row by output row.)
+        constexpr int kUnrollRows = kMix ? KS : 1;
+#pragma unroll kUnrollRows
         for (int dh = 0; dh < KS; ++dh) {
             u32x4 wrow[KS];
 #pragma unroll
             for (int dw = 0; dw < KS; ++dw) wrow[dw] = load_w(dh * KS + dw);
+            float wu_row[kMix ? 1 : KS][VEC];
+            if (!kMix) {
+#pragma unroll
+                for (int dw = 0; dw < KS; ++dw) S::unpack(wrow[dw], wu_row[dw % (kMix ? 1 : KS)]);
+            }
 #pragma unroll
             for (int i = 0; i < kOut; ++i) {
+                if (kMix) __builtin_amdgcn_sched_barrier(0);
                 float(&acc)[VEC] = acc_all[i % (kKeepW ? 1 : kOut)];
 #pragma unroll
                 for (int dw = 0; dw < KS; ++dw) {
@@ -328,8 +378,7 @@ __global__ void __launch_bounds__(256) dwconv_staged_kernel(const ChainArgs a, c
                         }
                         continue;
                     }
-                    float xf[VEC], wu[VEC];
-                    S::unpack(wv, wu);
+                    float xf[VEC];
                     if (kPacked) {
                         S::unpack(src[0], xf);
                     } else {
@@ -344,7 +393,7 @@ __global__ void __launch_bounds__(256) dwconv_staged_kernel(const ChainArgs a, c
                         }
                     }
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) acc[e] = __builtin_fmaf(wu[e], xf[e], acc[e]);
+                    for (int e = 0; e < VEC; ++e) acc[e] = __builtin_fmaf(wu_row[dw % (kMix ? 1 : KS)][e], xf[e], acc[e]);
                 }
             }
         }
@@ -403,8 +452,10 @@ __global__ void __launch_bounds__(256) dwconv_staged_kernel(const ChainArgs a, c
                 s.fraw[f][0] = stencil_load<DT>(a.full[f], (uint64_t)pos * g.c + cvi * VEC, ragged, cnt);
 #pragma unroll
         for (int v = 0; v < Spec::NV; ++v)
-            if (v < Spec::n_vec(a) && v != wslot && ((epi_vec >> v) & 1u))
-                s.vraw[v][0] = stencil_load_vec<DT, Spec::kVecMode>(a.vec[v], pos, s.col[0], g.c, ragged, cnt);
+            if (v < Spec::n_vec(a) && v != wslot && ((epi_vec >> v) & 1u)) {
+                if (Spec::kVecChannel) s.vraw[v][0] = epi_v[v];
+                else s.vraw[v][0] = stencil_load_vec<DT, Spec::kVecMode>(a.vec[v], pos, s.col[0], g.c, ragged, cnt);
+            }
 #pragma unroll
         for (int e = 0; e < VEC; ++e) s.acc[e] = acc[e];
         run_program<DT, 1, Spec>(ProgView<typename Spec::Epi>{a.epi}, s, NoStore{});
@@ -448,6 +499,14 @@ __global__ void __launch_bounds__(256) dwconv_strided_kernel(const ChainArgs a, 
 
     LaneState<DT, 1, Spec> s;
     s.col[0] = cvi * VEC;
+    // the epilogue's per-channel operands, once (fetched per output row, they would wait for the row's store before)
+    u32x4 epi_v[at_least_1(Spec::NV)];
+    if (Spec::kVecChannel) {
+#pragma unroll
+        for (int v = 0; v < Spec::NV; ++v)
+            if (v < Spec::n_vec(a) && v != wslot && ((epi_vec >> v) & 1u))
+                epi_v[v] = stencil_load_vec<DT, Spec::kVecMode>(a.vec[v], 0u, s.col[0], g.c, ragged, cnt);
+    }
 #pragma unroll 1
     for (uint32_t r = 0; r < g.strip_rows; ++r) {
         const uint32_t orow = i0 + r;
@@ -508,8 +567,10 @@ __global__ void __launch_bounds__(256) dwconv_strided_kernel(const ChainArgs a, 
                 s.fraw[f][0] = stencil_load<DT>(a.full[f], (uint64_t)opos * g.c + cvi * VEC, ragged, cnt);
 #pragma unroll
         for (int v = 0; v < Spec::NV; ++v)
-            if (v < Spec::n_vec(a) && v != wslot && ((epi_vec >> v) & 1u))
-                s.vraw[v][0] = stencil_load_vec<DT, Spec::kVecMode>(a.vec[v], opos, s.col[0], g.c, ragged, cnt);
+            if (v < Spec::n_vec(a) && v != wslot && ((epi_vec >> v) & 1u)) {
+                if (Spec::kVecChannel) s.vraw[v][0] = epi_v[v];
+                else s.vraw[v][0] = stencil_load_vec<DT, Spec::kVecMode>(a.vec[v], opos, s.col[0], g.c, ragged, cnt);
+            }
 #pragma unroll
         for (int e = 0; e < VEC; ++e) s.acc[e] = acc[e];
         run_program<DT, 1, Spec>(ProgView<typename Spec::Epi>{a.epi}, s, NoStore{});
