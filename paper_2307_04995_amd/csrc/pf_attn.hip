@@ -22,6 +22,22 @@ namespace pf {
 
 PF_DEVICE float shfl_xor_f(float v, int mask) { return __shfl_xor(v, mask, 64); }
 
+// sums over aligned runs of `lpr` lanes; the usual run lengths by lane permutations inside the vector unit
+template <int N>
+PF_DEVICE void sum_row_lanes(float (&v)[N], uint32_t lpr) {
+    if (lpr == 8u) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = subrow_allreduce<OpSum, 3>(v[i]);
+    } else if (lpr == 16u) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = subrow_allreduce<OpSum, 4>(v[i]);
+    } else {
+        for (uint32_t msk = 1; msk < lpr; msk <<= 1)
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[i] += shfl_xor_f(v[i], (int)msk);
+    }
+}
+
 // Publish a slice's partial result (weighted value sum of column `tid` in o_mine, maximum m, sum of exponentials
 // l_blk); the workgroup whose arrival completes the head's counter merges all slices and writes the output row.
 // lds_o is workgroup scratch of 4 x 256 floats, s_last one shared word.
@@ -150,24 +166,104 @@ PF_DEVICE uint32_t attn_word(float x) {
     const uint32_t w = __builtin_bit_cast(uint32_t, x);
     return w == kAttnEmpty ? 0x7fc00000u : w;
 }
-PF_DEVICE uint32_t attn_wait(const AttnArgs& a, uint32_t* word, uint32_t* spins) {
-    for (;;) {
-        const uint32_t w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (w != kAttnEmpty) return w;
-        if (++*spins > a.spin_limit) {
-            __hip_atomic_store(a.ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return kAttnEmpty;
+// The merge of a head's slices: o = sum_s o_s e^(m_s - M) / sum_s l_s e^(m_s - M), thread (g, c) summing column c over the
+// slices s = g, g + G, ..., U of them in flight at a time and relative to the largest maximum it has seen so far; the groups
+// are brought to one maximum when they are combined.  One trip to memory for up to U G slices (a pass over the maxima first
+// and then the slices one by one cost a trip each: 8 heads of 63 slices, 19.3 -> 13.7 us).
+template <int DT, int U>
+PF_DEVICE void merge_slices_polled(const AttnArgs& a, uint32_t head, uint32_t groups, uint32_t dp, float (*lds_o)[256]) {
+    using S = Storage<DT>;
+    constexpr int VEC = S::VEC;
+    constexpr bool PR = S::PRECISE;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t d = a.d;
+    const uint32_t n_split = gridDim.x;
+    uint32_t* base = reinterpret_cast<uint32_t*>(a.ws_partial) + (uint64_t)head * n_split * a.part_stride;
+    uint32_t spins = 0;
+    const uint32_t g = tid / dp, c = tid - g * dp;
+    const uint32_t lowest = 0xff800000u;  // -inf: a slice that does not exist weighs nothing
+    auto neg_exp = [](float x) { return PR ? expf(x) : __builtin_amdgcn_exp2f(x * kLog2e); };
+    float big = -__builtin_inff(), num = 0.0f, den = 0.0f;
+    for (uint32_t s0 = g; s0 < n_split; s0 += groups * (uint32_t)U) {
+        uint32_t wm[U], wl[U], wo[U];
+        auto read = [&](int u, bool again) {
+            const uint32_t s = s0 + (uint32_t)u * groups;
+            uint32_t* ps = base + (uint64_t)min(s, n_split - 1u) * a.part_stride;
+            if (!again || wm[u] == kAttnEmpty) wm[u] = s < n_split ? __hip_atomic_load(ps + d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : lowest;
+            if (!again || wl[u] == kAttnEmpty) wl[u] = s < n_split ? __hip_atomic_load(ps + d + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+            if (!again || wo[u] == kAttnEmpty) wo[u] = s < n_split && c < d ? __hip_atomic_load(ps + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        };
+        auto empty = [&](int u) { return wm[u] == kAttnEmpty || wl[u] == kAttnEmpty || wo[u] == kAttnEmpty; };
+#pragma unroll
+        for (int u = 0; u < U; ++u) read(u, false);
+        // words still empty are re-read together (one trip to memory per round, not one per word)
+        for (;;) {
+            bool waiting = false;
+#pragma unroll
+            for (int u = 0; u < U; ++u) waiting = waiting || empty(u);
+            if (!waiting) break;
+            if (++spins > a.spin_limit) {
+                __hip_atomic_store(a.ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(4);
+#pragma unroll
+            for (int u = 0; u < U; ++u) read(u, true);
         }
-        __builtin_amdgcn_s_sleep(4);
+        float top = big;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t s = s0 + (uint32_t)u * groups;
+            if (s < n_split && c < d) __hip_atomic_store(base + (uint64_t)s * a.part_stride + c, kAttnEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // (nobody else reads this word)
+            if (!empty(u)) top = fmaxf(top, __builtin_bit_cast(float, wm[u]));
+        }
+        const float keep = big == -__builtin_inff() ? 0.0f : neg_exp(big - top);
+        num *= keep;
+        den *= keep;
+        big = top;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + (uint32_t)u * groups >= n_split || empty(u)) continue;  // (empty: a wait gave up, the slice is left out)
+            const float w = neg_exp(__builtin_bit_cast(float, wm[u]) - big);
+            num = __builtin_fmaf(__builtin_bit_cast(float, wo[u]), w, num);
+            den = __builtin_fmaf(__builtin_bit_cast(float, wl[u]), w, den);
+        }
+    }
+    float* red_num = &lds_o[0][0];  // [groups][dp] (the per-wave partials are no longer needed)
+    float* red_den = &lds_o[1][0];
+    float* red_big = &lds_o[2][0];
+    __syncthreads();  // (also: every thread has read the maxima and sums it needs)
+    red_num[tid] = num;
+    red_den[tid] = den;
+    red_big[tid] = big;
+    // the maxima and sums were read by many threads: put back to "empty" once everybody is past the barrier above
+    for (uint32_t s = tid; s < n_split; s += 256u) {
+        __hip_atomic_store(base + (uint64_t)s * a.part_stride + d, kAttnEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(base + (uint64_t)s * a.part_stride + d + 1u, kAttnEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (tid < d) {
+        float top = red_big[tid];
+        for (uint32_t gg = 1; gg < groups; ++gg) top = fmaxf(top, red_big[gg * dp + tid]);
+        num = 0.0f;
+        den = 0.0f;
+        for (uint32_t gg = 0; gg < groups; ++gg) {
+            const float w = red_den[gg * dp + tid] == 0.0f && red_num[gg * dp + tid] == 0.0f ? 0.0f : neg_exp(red_big[gg * dp + tid] - top);  // (a group without slices)
+            num = __builtin_fmaf(red_num[gg * dp + tid], w, num);
+            den = __builtin_fmaf(red_den[gg * dp + tid], w, den);
+        }
+        const float r = PR ? num / den : num * __builtin_amdgcn_rcpf(den);
+        if (DT == DT_F32) static_cast<float*>(a.o)[(uint64_t)head * d + tid] = r;
+        else {
+            float tmp[VEC] = {r};
+            static_cast<uint16_t*>(a.o)[(uint64_t)head * d + tid] = (uint16_t)(S::pack(tmp)[0] & 0xffffu);
+        }
     }
 }
 
 template <int DT>
 PF_DEVICE void finish_slice_polled(const AttnArgs& a, uint32_t head, uint32_t split, float o_mine, float m, float l_blk, float (*lds_o)[256]) {
-    using S = Storage<DT>;
-    constexpr int VEC = S::VEC;
-    constexpr bool PR = S::PRECISE;
-    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t tid = threadIdx.x;
     const uint32_t d = a.d;
     const uint32_t n_split = gridDim.x;
     uint32_t* words = reinterpret_cast<uint32_t*>(a.ws_partial);
@@ -179,61 +275,13 @@ PF_DEVICE void finish_slice_polled(const AttnArgs& a, uint32_t head, uint32_t sp
     }
     if (split + 1u != n_split) return;
 
-    // ---- the head's last slice merges: o = sum_s o_s e^(m_s - M) / sum_s l_s e^(m_s - M), thread (g, c) summing column c
-    // over the slices s = g, g + G, ... as in the counted merge
-    uint32_t* base = words + (uint64_t)head * n_split * a.part_stride;
-    uint32_t spins = 0;
+    // ---- the head's last slice merges
     uint32_t dp = 1;
     while (dp < d) dp <<= 1;
-    const uint32_t groups = 256u / dp, g = tid / dp, c = tid - g * dp;
-    float big = -__builtin_inff();
-    for (uint32_t s = lane; s < n_split; s += 64u) {  // every wave finds the same maximum
-        const uint32_t w = attn_wait(a, base + (uint64_t)s * a.part_stride + d, &spins);
-        if (w != kAttnEmpty) big = fmaxf(big, __builtin_bit_cast(float, w));
-    }
-    for (int msk = 1; msk < 64; msk <<= 1) big = fmaxf(big, shfl_xor_f(big, msk));
-    float num = 0.0f, den = 0.0f;
-    for (uint32_t s = g; s < n_split; s += groups) {
-        uint32_t* ps = base + (uint64_t)s * a.part_stride;
-        // the three words of a slice are asked for together; what is still empty is waited for afterwards
-        uint32_t wm = __hip_atomic_load(ps + d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t wl = __hip_atomic_load(ps + d + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t wo = c < d ? __hip_atomic_load(ps + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-        if (wm == kAttnEmpty) wm = attn_wait(a, ps + d, &spins);
-        if (wl == kAttnEmpty) wl = attn_wait(a, ps + d + 1u, &spins);
-        if (wo == kAttnEmpty) wo = attn_wait(a, ps + c, &spins);
-        if (c < d) __hip_atomic_store(ps + c, kAttnEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // (nobody else reads this word)
-        if (wm == kAttnEmpty || wl == kAttnEmpty || wo == kAttnEmpty) continue;  // a wait gave up: the slice is left out
-        const float ms = __builtin_bit_cast(float, wm), ls = __builtin_bit_cast(float, wl), os = __builtin_bit_cast(float, wo);
-        const float w = PR ? expf(ms - big) : __builtin_amdgcn_exp2f((ms - big) * kLog2e);
-        num = __builtin_fmaf(os, w, num);
-        den = __builtin_fmaf(ls, w, den);
-    }
-    float* red_num = &lds_o[0][0];  // [groups][dp] (the per-wave partials are no longer needed)
-    float* red_den = &lds_o[2][0];
-    __syncthreads();  // (also: every thread has read the maxima and sums it needs)
-    red_num[tid] = num;
-    red_den[tid] = den;
-    // the maxima and sums were read by many threads: put back to "empty" once everybody is past the barrier above
-    for (uint32_t s = tid; s < n_split; s += 256u) {
-        __hip_atomic_store(base + (uint64_t)s * a.part_stride + d, kAttnEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(base + (uint64_t)s * a.part_stride + d + 1u, kAttnEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (tid < d) {
-        num = 0.0f;
-        den = 0.0f;
-        for (uint32_t gg = 0; gg < groups; ++gg) {
-            num += red_num[gg * dp + tid];
-            den += red_den[gg * dp + tid];
-        }
-        const float r = PR ? num / den : num * __builtin_amdgcn_rcpf(den);
-        if (DT == DT_F32) static_cast<float*>(a.o)[(uint64_t)head * d + tid] = r;
-        else {
-            float tmp[VEC] = {r};
-            static_cast<uint16_t*>(a.o)[(uint64_t)head * d + tid] = (uint16_t)(S::pack(tmp)[0] & 0xffffu);
-        }
-    }
+    const uint32_t groups = 256u / dp;
+    if (n_split <= groups) merge_slices_polled<DT, 1>(a, head, groups, dp, lds_o);
+    else if (n_split <= 2u * groups) merge_slices_polled<DT, 2>(a, head, groups, dp, lds_o);
+    else merge_slices_polled<DT, 8>(a, head, groups, dp, lds_o);
 }
 
 template <int DT, int NV>
@@ -283,14 +331,17 @@ __global__ void __launch_bounds__(256) attn_decode_kernel(const AttnArgs a) {
     float m = -__builtin_inff();
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const uint32_t row = row0 + (uint32_t)i * rps + row_in_step;
         float kf[VEC];
         S::unpack(kraw[i], kf);
-        float dot = 0.0f;
+        sc[i] = 0.0f;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) dot = __builtin_fmaf(kf[e], qf[e], dot);
-        for (uint32_t msk = 1; msk < lpr; msk <<= 1) dot += shfl_xor_f(dot, (int)msk);
-        sc[i] = row < t_total ? dot * a.scale : -__builtin_inff();
+        for (int e = 0; e < VEC; ++e) sc[i] = __builtin_fmaf(kf[e], qf[e], sc[i]);
+    }
+    sum_row_lanes<NV>(sc, lpr);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const uint32_t row = row0 + (uint32_t)i * rps + row_in_step;
+        sc[i] = row < t_total ? sc[i] * a.scale : -__builtin_inff();
         m = fmaxf(m, sc[i]);
     }
     // the slice's maximum: over the row groups of the wave, then over the four waves
@@ -392,14 +443,17 @@ __global__ void __launch_bounds__(256) attn_decode_stream_kernel(const AttnArgs 
         float sc[NV], cm = -__builtin_inff();
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const uint32_t row = row_begin + c * chunk_rows + (uint32_t)i * rps + row_in_step;
             float kf[VEC];
             S::unpack(kr[i], kf);
-            float dot = 0.0f;
+            sc[i] = 0.0f;
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) dot = __builtin_fmaf(kf[e], qf[e], dot);
-            for (uint32_t msk = 1; msk < lpr; msk <<= 1) dot += shfl_xor_f(dot, (int)msk);
-            sc[i] = row < t_total ? dot * a.scale : -__builtin_inff();
+            for (int e = 0; e < VEC; ++e) sc[i] = __builtin_fmaf(kf[e], qf[e], sc[i]);
+        }
+        sum_row_lanes<NV>(sc, lpr);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const uint32_t row = row_begin + c * chunk_rows + (uint32_t)i * rps + row_in_step;
+            sc[i] = row < t_total ? sc[i] * a.scale : -__builtin_inff();
             cm = fmaxf(cm, sc[i]);
         }
         const float m_new = fmaxf(m, cm);

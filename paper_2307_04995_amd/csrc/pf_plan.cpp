@@ -1431,27 +1431,36 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     a.log2_lpr = 0;
     while ((1u << a.log2_lpr) < a.lanes_per_row) ++a.log2_lpr;
     a.scale = L.attn_scale;
-    // Rows per workgroup: 8 steps of 256 / lpr rows when that still gives every compute unit two workgroups,
-    // else 4 (measured on MI355X: fewer, longer slices win until the device runs short of workgroups; one or
-    // two steps per workgroup lose to the per-slice overhead, sixteen to register pressure).
+    // Rows per workgroup: 8 steps of 256 / lpr rows when that still gives every compute unit two workgroups, or one where 4
+    // steps would leave a head more slices than its merge takes in one trip (2 per thread group: 3 x 25 heads, t = 1023, d = 64,
+    // 8 slices of 4 steps 8.7 us against 9.3; 2 x 25, t = 2047, 16 slices 10.3 against 9.6; 8 heads, t = 4000, d = 128, 63
+    // slices 13.8 against 10.5); else 4.  (One or two steps per workgroup lose to the per-slice overhead, sixteen to register
+    // pressure.)
     const int64_t rps = 256 / lpr;
     int nv = 4;
-    if (heads * ((t_total + rps * 8 - 1) / (rps * 8)) >= 2 * (int64_t)n_cu) nv = 8;
+    {
+        int64_t dp = 1;
+        while (dp < d) dp *= 2;
+        const int64_t slices8 = heads * ((t_total + rps * 8 - 1) / (rps * 8)), splits4 = (t_total + rps * 4 - 1) / (rps * 4);
+        if (slices8 >= 2 * (int64_t)n_cu || (slices8 >= n_cu && splits4 > 2 * (256 / dp))) nv = 8;
+    }
     const int forced_nv = env_int("PF_ATTN_NV", 0);
     if (forced_nv == 1 || forced_nv == 2 || forced_nv == 4 || forced_nv == 8) nv = forced_nv;
-    // Streaming variant: a workgroup walks `chunks` chunks of 2 steps each with the next chunk's loads in flight.
-    // Measured on MI355X: it wins (10-13 %) when slices get long -- many heads (one slice per head: no device-scope
-    // merge at all) or long caches -- and ties or loses below eight chunks per slice, where the one-pass kernel's
-    // deeper load burst counts for more.  Slices are cut so that every compute unit still gets about three workgroups.
+    // Streaming variant: a workgroup walks `chunks` chunks of 2 steps each with the next chunk's loads in flight.  Taken where
+    // that leaves a head one slice (many heads: no device-scope merge at all).  With more slices the one-pass kernel's deeper
+    // load burst counts for more, now that a merge reads many slices in one trip (8 x 25 heads, t = 4095: 43.7 us streamed, 39.9
+    // in one pass; 4 x 25, t = 8191: 43.5 and 41.9; 4 x 32, t = 2047, d = 128: 31.2 and 29.5; 16 x 25, t = 1023: 24.0 and 21.8).
     int64_t chunks = 1;
+    bool one_slice = false;
     {
         const int64_t all_chunks = (t_total + rps * 2 - 1) / (rps * 2);
         const int64_t target_splits = std::max<int64_t>(1, (3 * (int64_t)n_cu + heads - 1) / heads);
         const int64_t c = (all_chunks + target_splits - 1) / target_splits;
         const int forced_chunks = env_int("PF_ATTN_CHUNKS", 0);
         chunks = forced_chunks > 0 ? forced_chunks : c;
+        one_slice = chunks >= all_chunks;
     }
-    int variant = forced_variant >= 0 ? forced_variant : (chunks >= 8 && !forced_nv ? PF_VARIANT_ATTN_STREAM : PF_VARIANT_ATTN_ONE_PASS);
+    int variant = forced_variant >= 0 ? forced_variant : (chunks >= 8 && one_slice && !forced_nv ? PF_VARIANT_ATTN_STREAM : PF_VARIANT_ATTN_ONE_PASS);
     if (variant != PF_VARIANT_ATTN_ONE_PASS && variant != PF_VARIANT_ATTN_STREAM)
         return fail(PF_ERR_UNSUPPORTED, "unknown attention variant %d", variant);
     if (variant == PF_VARIANT_ATTN_STREAM) {
