@@ -406,6 +406,15 @@ __global__ void __launch_bounds__(T) row_held_kernel(const ChainArgs a) {
     };
     auto sum_over_row = [&](float v, int area) { return row_allreduce<OpSum>(v, W, wave, 0u, lane, red[area]); };
 
+    // (a vector's elements are added pairwise before they join the lane's running sum: the rounding of a row's sum, which every
+    // element of a softmax shares, stays below that of the streaming walk)
+    auto vector_sum = [&]() {
+        float v = 0.0f;
+#pragma unroll
+        for (int e = 0; e < VEC; e += 4) v += (s.acc[e] + s.acc[e + 1]) + (s.acc[e + 2] + s.acc[e + 3]);
+        return v;
+    };
+
     float row_max = 0.0f, mc = 0.0f, row_inv = 0.0f, mean = 0.0f, rstd = 0.0f, value = 0.0f;
     const float cs = a.core_scale, c2 = cs * kLog2e;
     if (core == CORE_SOFTMAX || core == CORE_REDUCE_MAX) {
@@ -433,8 +442,8 @@ __global__ void __launch_bounds__(T) row_held_kernel(const ChainArgs a) {
             for (int k = 0; k < K; ++k) {
                 counted(k, -__builtin_inff(), kFill);
 #pragma unroll
-                for (int e = 0; e < VEC; ++e)
-                    sum += PR ? expf((s.acc[e] - row_max) * cs) : __builtin_amdgcn_exp2f(__builtin_fmaf(s.acc[e], c2, mc));
+                for (int e = 0; e < VEC; ++e) s.acc[e] = PR ? expf((s.acc[e] - row_max) * cs) : __builtin_amdgcn_exp2f(__builtin_fmaf(s.acc[e], c2, mc));
+                sum += vector_sum();
             }
             row_inv = pf_rcp<PR>(sum_over_row(sum, 1));
         }
@@ -445,7 +454,8 @@ __global__ void __launch_bounds__(T) row_held_kernel(const ChainArgs a) {
         for (int k = 0; k < K; ++k) {
             counted(k, 0.0f, kFill);
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) sum += sq ? s.acc[e] * s.acc[e] : s.acc[e];
+            for (int e = 0; e < VEC; ++e) s.acc[e] = sq ? s.acc[e] * s.acc[e] : s.acc[e];
+            sum += vector_sum();
         }
         value = sum_over_row(sum, 0);
         if (core == CORE_REDUCE_MEAN) value = value / (float)n;
