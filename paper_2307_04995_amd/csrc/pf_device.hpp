@@ -462,6 +462,7 @@ struct GenericSpec {
     static constexpr bool kBcast = true;  // general broadcasting of operands is a run-time property here
     static constexpr int kVecMode = 3;    // ... and so is a broadcast operand with a single element
     static constexpr bool kVecChannel = false;
+    static constexpr bool kFewBlocks = false;
     static constexpr int NF = 3, NV = 4, NT = PF_DEV_MAX_TMP;
     using Pro = DynList;
     using Epi = DynList;
@@ -474,7 +475,7 @@ struct GenericSpec {
 
 // FLAGS_: bit 0 = some operand broadcasts the general way (extents of 1 anywhere); bit 1 = some broadcast operand has a
 // single element; bit 2 (stencil family) = every broadcast operand is indexed by channel alone, whatever the position, so
-// it is loaded once.  Kernels built without a bit carry none of that case's code: the one-element case in particular
+// it is loaded once; bit 3 (stencil family) = at most one workgroup per compute unit.  Kernels built without a bit carry none of that case's code: the one-element case in particular
 // costs more than its branch, because the compiler issues its 2-byte load next to the 16-byte one and waits for both
 // before it goes on, which turns the operand loads of a kernel into one memory round trip after the other.
 template <int NF_, int NV_, int NT_, int CORE_, int GAMMA_, int BETA_, class ProL, class EpiL, int FLAGS_ = 0>
@@ -483,6 +484,7 @@ struct StaticSpec {
     static constexpr bool kBcast = (FLAGS_ & 1) != 0;
     static constexpr int kVecMode = FLAGS_ & 3;
     static constexpr bool kVecChannel = (FLAGS_ & 4) != 0;
+    static constexpr bool kFewBlocks = (FLAGS_ & 8) != 0;
     static constexpr int NF = NF_, NV = NV_, NT = NT_;
     static constexpr int kGamma = GAMMA_, kBeta = BETA_;
     using Pro = ProL;

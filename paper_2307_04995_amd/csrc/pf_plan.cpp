@@ -593,8 +593,12 @@ pf_status plan_perm(pf_plan_s* p, int forced_variant) {
             int64_t step = 128 / es;
             auto lds_of = [&](int64_t st) { return flat_out ? flat_len * (st + 1) * es : (st * flat_len + 2 * vec) * es; };
             if (lds_of(step) > 64 * 1024 && ((flat_out ? n_b : n_a) * es) % 16 == 0) step /= 2;
+            // Strips enough: a flat output pays off with two to a compute unit ([32, 56, 56, 100] 20.7 -> 11.0 us; 384 strips of
+            // [64, 14, 14, 384] 8.4 against 8.6, ten of [1, 30, 30, 320] 6.9 against 10.7), half lines likewise; a flat input
+            // always ([2, 96, 15, 15] 9.1 -> 7.2).
             const int64_t planes = numel(in) / (n_a * n_b), per_plane = (flat_rows + step - 1) / step;
-            if (lds_of(step) <= 64 * 1024 && planes * per_plane <= 0x7fffffffLL) {
+            const bool enough = planes * per_plane >= 512 || (!flat_out && step * es == 128);
+            if (enough && lds_of(step) <= 64 * 1024 && planes * per_plane <= 0x7fffffffLL) {
                 pf::PlaneGeom& pg = p->planeg;
                 pg.a = (uint32_t)n_a;
                 pg.b = (uint32_t)n_b;
@@ -1025,6 +1029,11 @@ pf_status plan_stencil(pf_plan_s* p, const Checked& c, int forced_variant) {
     for (int v = 0; v < L.n_vec; ++v)
         if (v != L.core_vec[0] && (p->args.vec[v].numel > (uint32_t)ch || p->args.vec[v].n_terms != 0)) by_channel = false;
     if (by_channel) jspec.flags |= 4;
+    // a launch that leaves compute units idle: registers do not limit what is resident
+    {
+        hipDeviceProp_t prop;
+        if (hipGetDeviceProperties(&prop, p->device) == hipSuccess && (uint64_t)p->grid.x * p->grid.y * p->grid.z <= (uint64_t)prop.multiProcessorCount) jspec.flags |= 8;
+    }
     const pf_op_desc& conv = p->desc.ops[L.core_op];
     const int64_t stride = conv.n_i == 1 ? conv.i[0] : 1;
     if (stride > 1) {
@@ -1303,10 +1312,12 @@ pf_status plan_pool(pf_plan_s* p) {
     // 21 us, 32: 17.7 us, 16: 17.1 us, 8: 19.5 us, 4: 28 us; with SiLU in front 32 slices are best).
     int nv = 8;
     while (nv > 1 && (int64_t)(nv / 2) * g.pos_per_step >= hw) nv /= 2;
-    // Half the chunk where whole ones would not give every compute unit two ([2, 28, 28, 256] fp16 7.0 -> 6.4 us, [128, 7, 7,
-    // 1280] 10.1 -> 9.7) and for element-aligned positions, whose eight loads and partial stores crowd the registers ([32, 56,
-    // 56, 244] 24.8 -> 19.9); elsewhere eight are as good or better ([32, 56, 56, 240] 13.6 against 14.0).
-    if (nv == 8 && (ragged_c || n * ((hw + 8 * g.pos_per_step - 1) / (8 * g.pos_per_step)) < 2 * n_cu)) nv = 4;
+    // Half the chunk where whole ones would not give every compute unit two and the twice as many slices are still merged in one
+    // round of eight per row group, and not where a sample is a slice or a few ([2, 28, 28, 256] fp16 7.0 -> 6.4 us; three slices for two [7, 10, 10, 416] 7.1 -> 8.0; in two rounds [10, 28,
+    // 28, 336] 7.7 -> 8.6), and for element-aligned positions, whose eight loads and partial stores crowd the registers ([32,
+    // 56, 56, 244] 24.8 -> 19.9); elsewhere eight are as good or better ([32, 56, 56, 240] 13.6 against 14.0).
+    const int64_t slices8 = (hw + 8 * g.pos_per_step - 1) / (8 * g.pos_per_step), slices4 = (hw + 4 * g.pos_per_step - 1) / (4 * g.pos_per_step);
+    if (nv == 8 && (ragged_c || (slices8 >= 4 && n * slices8 < 2 * n_cu && slices4 - 1 <= 8 * std::max<int64_t>(1, 512 / ch)))) nv = 4;
     const int forced_nv = env_int("PF_POOL_NV", 0);
     if (forced_nv == 1 || forced_nv == 2 || forced_nv == 4 || forced_nv == 8) nv = forced_nv;
     const int64_t chunk_pos = (int64_t)nv * g.pos_per_step;

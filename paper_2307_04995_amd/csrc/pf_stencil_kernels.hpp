@@ -321,6 +321,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Spec::
 #pragma unroll
         for (int k = 0; k < NW; ++k) wraw[k] = load_w(k);
     }
+    u32x4 wnext[kKeepW ? 1 : KS];
+    if (!kKeepW) {
+#pragma unroll
+        for (int dw = 0; dw < KS; ++dw) wnext[dw % (kKeepW ? 1 : KS)] = load_w(dw);
+    }
     u32x4 epi_v[at_least_1(Spec::NV)];
     if (Spec::kVecChannel) {
 #pragma unroll
@@ -346,14 +351,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Spec::
         for (int i = 0; i < kOut; ++i)
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc_all[i % (kKeepW ? 1 : kOut)][e] = 0.0f;
-        // (Unrolled, the compiler fetches and widens all 25 taps first and needs up to 500 registers, one wave per SIMD.  So the
-        // kernel rows stay a loop where values are widened, and fp16, which needs no widening, goes output row by output row.)
-        constexpr int kUnrollRows = kMix ? KS : 1;
+        // (Unrolled, the compiler fetches and widens all 25 taps first and needs up to 470 registers for bf16, one wave per SIMD:
+        // its kernel rows stay a loop unless the launch leaves units idle anyway ([91, 7, 7, 128] 9.2 unrolled, 10.1 as a loop).
+        // fp16, which needs no widening, goes output row by output row; fp32 needs 208 registers and is best left alone.)
+        constexpr int kUnrollRows = kMix || DT == DT_F32 || Spec::kFewBlocks ? KS : 1;
 #pragma unroll kUnrollRows
         for (int dh = 0; dh < KS; ++dh) {
+            // (the next kernel row's vectors are on their way while this one's are used)
             u32x4 wrow[KS];
 #pragma unroll
-            for (int dw = 0; dw < KS; ++dw) wrow[dw] = load_w(dh * KS + dw);
+            for (int dw = 0; dw < KS; ++dw) {
+                wrow[dw] = wnext[dw % (kKeepW ? 1 : KS)];
+                wnext[dw % (kKeepW ? 1 : KS)] = load_w((dh + 1 < KS ? dh + 1 : dh) * KS + dw);
+            }
             float wu_row[kMix ? 1 : KS][VEC];
             if (!kMix) {
 #pragma unroll

@@ -40,7 +40,7 @@ def _run(shape, perm, dtype, planes, seed, **flags):
 @pytest.mark.parametrize("a,b", [(2, 3), (64, 7), (65, 49), (384, 196), (63, 197), (100, 64), (33, 72), (7, 8), (129, 500), (40, 1001), (1001, 40), (500, 24), (13, 1021),
                                  (2, 1030)])
 def test_planes(a, b, dtype):
-    for planes in (1, 3):
+    for planes in (1, 3) if a * b > 6000 else (1, 3, 300):
         _run((planes, a, b), [0, 2, 1], dtype, planes, 8000 + a)
 
 
@@ -48,7 +48,12 @@ def test_feature_maps_and_what_stays_on_tiles():
     # [n, c, h, w] <-> [n, h, w, c] with 14 x 14 positions, 19 planes: strips are not a multiple of the dies
     strips = _run((19, 72, 14, 14), [0, 2, 3, 1], "f16", 19, 8101)
     assert strips == (19 * 2 + 7) // 8 * 8
-    assert _run((19, 14, 14, 72), [0, 3, 1, 2], "f16", 19, 8102) == (19 * 2 + 7) // 8 * 8
+    # (a flat output takes 512 strips at least: 260 planes of two)
+    assert _run((260, 14, 14, 72), [0, 3, 1, 2], "f16", 260, 8102) == (260 * 2 + 7) // 8 * 8
+    _run((19, 14, 14, 72), [0, 3, 1, 2], "f16", 19, 8106)
+    for shape in ((520, 33, 16), (260, 3, 72), (172, 101, 136), (520, 900, 24)):   # flat outputs: remainders of both kinds
+        for dtype in ("f16", "f32"):
+            _run(shape, [0, 2, 1], dtype, shape[0], 8107)
     _run((3, 1500, 1201), [0, 2, 1], "f16", 3, 8103)     # rows too long for a strip in LDS
     _run((5, 6, 7, 9), [3, 1, 2, 0], "f32", 1, 8104)     # not a swap of adjacent dimensions
     _run((4, 3, 50, 11), [1, 0, 3, 2], "bf16", 1, 8105)  # the planes change places as well
