@@ -475,7 +475,8 @@ struct GenericSpec {
 
 // FLAGS_: bit 0 = some operand broadcasts the general way (extents of 1 anywhere); bit 1 = some broadcast operand has a
 // single element; bit 2 (stencil family) = every broadcast operand is indexed by channel alone, whatever the position, so
-// it is loaded once; bit 3 (stencil family) = at most one workgroup per compute unit.  Kernels built without a bit carry none of that case's code: the one-element case in particular
+// it is loaded once; bit 3 (stencil family) = at most one workgroup per compute unit; bit 4 (held rows) = no score of a
+// softmax is as large as 2^20.  Kernels built without a bit carry none of that case's code: the one-element case in particular
 // costs more than its branch, because the compiler issues its 2-byte load next to the 16-byte one and waits for both
 // before it goes on, which turns the operand loads of a kernel into one memory round trip after the other.
 template <int NF_, int NV_, int NT_, int CORE_, int GAMMA_, int BETA_, class ProL, class EpiL, int FLAGS_ = 0>
@@ -485,6 +486,7 @@ struct StaticSpec {
     static constexpr int kVecMode = FLAGS_ & 3;
     static constexpr bool kVecChannel = (FLAGS_ & 4) != 0;
     static constexpr bool kFewBlocks = (FLAGS_ & 8) != 0;
+    static constexpr bool kSmallScores = (FLAGS_ & 16) != 0;
     static constexpr int NF = NF_, NV = NV_, NT = NT_;
     static constexpr int kGamma = GAMMA_, kBeta = BETA_;
     using Pro = ProL;

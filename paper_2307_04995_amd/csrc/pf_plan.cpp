@@ -295,8 +295,12 @@ pf_status plan_row(pf_plan_s* p, int forced_variant) {
         const int t = held <= 256 * 10 ? 256 : held <= 512 * 25 ? 512 : 1024;
         const int k = (int)((held + t - 1) / t);
         if (t == 1024 && k > 20) return false;  // (128 registers a lane: what 20 vectors and the arithmetic need)
+        // fp16 values as they are loaded reach 65504: with the scale in front of the softmax they stay below 2^20, where rounding
+        // them to fp32 moves an exponent by less than 2^-4
+        pf::JitSpec jspec = make_jit_spec(L);
+        if (L.core == pf::CORE_SOFTMAX && L.main_dtype == PF_F16 && L.pro.n == 1 && L.core_scale * 1.4426951f * 65504.0f < 1048576.0f) jspec.flags |= 16;
         std::string err;
-        hipFunction_t fn = pf::jit_row_held_kernel(p->device, L.main_dtype, k, t, p->ragged, make_jit_spec(L), &err);
+        hipFunction_t fn = pf::jit_row_held_kernel(p->device, L.main_dtype, k, t, p->ragged, jspec, &err);
         if (!fn || pf::jit_scratch_bytes(fn) != 0) return false;
         p->jit_fn = fn;
         p->spec_id = pf::kSpecJit;

@@ -417,6 +417,14 @@ __global__ void __launch_bounds__(T) row_held_kernel(const ChainArgs a) {
 
     float row_max = 0.0f, mc = 0.0f, row_inv = 0.0f, mean = 0.0f, rstd = 0.0f, value = 0.0f;
     const float cs = a.core_scale, c2 = cs * kLog2e;
+    // The maximum is subtracted before the multiplication: in x * c2 - max * c2 the rounding of max * c2, a common factor of the
+    // row that the division takes out, is an exponent of its own where the maximum is large (2^328 in a bf16 row masked
+    // throughout with -1e10).  Where the planner knows that it is not (kSmallScores) one fused step does both: [1024, 50257]
+    // fp16 39.1 us against 40.9.
+    auto exp_below_max = [&](float x) {
+        if (PR) return expf((x - row_max) * cs);
+        return __builtin_amdgcn_exp2f(Spec::kSmallScores ? __builtin_fmaf(x, c2, mc) : (x - row_max) * c2);
+    };
     if (core == CORE_SOFTMAX || core == CORE_REDUCE_MAX) {
         float m = -__builtin_inff(), nan_seen = 0.0f;
 #pragma unroll
@@ -433,8 +441,6 @@ __global__ void __launch_bounds__(T) row_held_kernel(const ChainArgs a) {
             nan_seen = row_allreduce<OpMax>(nan_seen, W, wave, 0u, lane, red[1]);
             value = nan_seen > 0.0f ? __builtin_nanf("") : row_max;
         } else {
-            // 16-bit types: exp2(c2 * x - mc) is one fused step from the packed value.  Any mc cancels in the division, so
-            // rounding c2 * max costs no accuracy.
             mc = -row_max * c2;
             keep();
             float sum = 0.0f;
@@ -442,7 +448,7 @@ __global__ void __launch_bounds__(T) row_held_kernel(const ChainArgs a) {
             for (int k = 0; k < K; ++k) {
                 counted(k, -__builtin_inff(), kFill);
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) s.acc[e] = PR ? expf((s.acc[e] - row_max) * cs) : __builtin_amdgcn_exp2f(__builtin_fmaf(s.acc[e], c2, mc));
+                for (int e = 0; e < VEC; ++e) s.acc[e] = exp_below_max(s.acc[e]);
                 sum += vector_sum();
             }
             row_inv = pf_rcp<PR>(sum_over_row(sum, 1));
@@ -504,10 +510,7 @@ __global__ void __launch_bounds__(T) row_held_kernel(const ChainArgs a) {
         value_of(k, store_fn);
         if (core == CORE_SOFTMAX) {
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const float t = PR ? expf((s.acc[e] - row_max) * cs) : __builtin_amdgcn_exp2f(__builtin_fmaf(s.acc[e], c2, mc));
-                s.acc[e] = t * row_inv;
-            }
+            for (int e = 0; e < VEC; ++e) s.acc[e] = exp_below_max(s.acc[e]) * row_inv;
         } else {
             float gm[VEC], bt[VEC];
 #pragma unroll

@@ -95,3 +95,38 @@ def test_large_common_offset_and_in_place():
     plan.run([buf, gd, bd], [buf])
     torch.cuda.synchronize()
     assert torch.equal(buf.cpu(), outs[0])
+
+
+@pytest.mark.parametrize("rows,n", [(4, 50257), (4, 50264)])
+@pytest.mark.parametrize("value", [-1e10, 1e10, float(torch.finfo(torch.bfloat16).min), float(torch.finfo(torch.bfloat16).max)])
+def test_rows_masked_throughout(value, rows, n):
+    # a row of one large value (everything masked with -1e10 or the type's lowest value) is 1 / n per element: the exponent is
+    # zero whatever the maximum's product with log2 e rounds to
+    for scale in (None, 0.5):
+        s, t = _softmax(rows, n, "bf16", scale)
+        t[0][0, :], t[0][rows - 1, :] = value, value
+        t[0][1, n // 2:] = value
+        outs, info, _ = check_chain(s, t, what=f"bf16 softmax of rows of {value}, scale {scale}")
+        assert info.block[0] * info.vectors_per_lane * 16 >= n * 2
+        for r in (0, rows - 1):
+            assert torch.equal(outs[0][r], torch.full((n,), 1.0 / n).to(torch.bfloat16))
+    # the same from a mask that is added in front, to rows of one value each (what fp32 makes of -1e10 + logits is another matter)
+    s = wl.ChainSpec(inputs=[("bf16", (rows, n)), ("bf16", (n,))])
+    s.out(s.op("softmax", s.op("add", 0, 1)), "bf16")
+    x = (torch.arange(rows).reshape(rows, 1) % 3).expand(rows, n).to(torch.bfloat16).contiguous()
+    outs, _, _ = check_chain(s, [x, torch.full((n,), value, dtype=torch.bfloat16)], what=f"bf16 softmax behind a mask of {value}")
+    assert torch.equal(outs[0], torch.full((rows, n), 1.0 / n).to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("scale", [None, 10.0, 12.0, 1e5])
+def test_the_largest_fp16_scores(scale):
+    # 65504 times the scale, on both sides of 2^20 (a scale of 11.1); neighbours of the maximum and a second value far below it
+    rows, n = 3, 50257
+    s, t = _softmax(rows, n, "f16", scale)
+    t[0][:] = -65504.0
+    t[0][0, :] = 65504.0
+    t[0][1, n - 40000:] = 65504.0
+    t[0][2, 5::7] = 65472.0
+    outs, _, _ = check_chain(s, t, what=f"fp16 softmax of the largest values, scale {scale}")
+    for row, count in ((0, n), (1, 40000), (2, len(range(5, n, 7)))):
+        assert torch.equal(outs[0][row], torch.where(t[0][row] > 0, 1.0 / count, 0.0).to(torch.float16))
