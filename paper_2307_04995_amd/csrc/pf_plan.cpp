@@ -1446,6 +1446,9 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     a.log2_lpr = 0;
     while ((1u << a.log2_lpr) < a.lanes_per_row) ++a.log2_lpr;
     a.scale = L.attn_scale;
+    // A plan that owns its workspace merges by polling self-describing words (a bounded wait, reported through the plan);
+    // a call that plans and runs in one go has no plan to report through and keeps the counted, wait-free merge.
+    const bool polled = !planning_static() && env_int("PF_ATTN_POLLED", 1) != 0;
     // Rows per workgroup: 8 steps of 256 / lpr rows when that still gives every compute unit two workgroups, or one where 4
     // steps would leave a head more slices than its merge takes in one trip (2 per thread group: 3 x 25 heads, t = 1023, d = 64,
     // 8 slices of 4 steps 8.7 us against 9.3; 2 x 25, t = 2047, 16 slices 10.3 against 9.6; 8 heads, t = 4000, d = 128, 63
@@ -1457,7 +1460,7 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
         int64_t dp = 1;
         while (dp < d) dp *= 2;
         const int64_t slices8 = heads * ((t_total + rps * 8 - 1) / (rps * 8)), splits4 = (t_total + rps * 4 - 1) / (rps * 4);
-        if (slices8 >= 2 * (int64_t)n_cu || (slices8 >= n_cu && splits4 > 2 * (256 / dp))) nv = 8;
+        if (slices8 >= 2 * (int64_t)n_cu || (polled && slices8 >= n_cu && splits4 > 2 * (256 / dp))) nv = 8;
     }
     const int forced_nv = env_int("PF_ATTN_NV", 0);
     if (forced_nv == 1 || forced_nv == 2 || forced_nv == 4 || forced_nv == 8) nv = forced_nv;
@@ -1465,6 +1468,8 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     // that leaves a head one slice (many heads: no device-scope merge at all).  With more slices the one-pass kernel's deeper
     // load burst counts for more, now that a merge reads many slices in one trip (8 x 25 heads, t = 4095: 43.7 us streamed, 39.9
     // in one pass; 4 x 25, t = 8191: 43.5 and 41.9; 4 x 32, t = 2047, d = 128: 31.2 and 29.5; 16 x 25, t = 1023: 24.0 and 21.8).
+    // The counted merge takes a trip per slice and, in a static call, its partial results have a fixed array to fit in (2 MB:
+    // 4 x 32 heads, t = 4096, d = 128 fill 0.5 MB streamed, 2.5 MB in one pass): there slices of eight chunks on are streamed.
     int64_t chunks = 1;
     bool one_slice = false;
     {
@@ -1475,7 +1480,7 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
         chunks = forced_chunks > 0 ? forced_chunks : c;
         one_slice = chunks >= all_chunks;
     }
-    int variant = forced_variant >= 0 ? forced_variant : (chunks >= 8 && one_slice && !forced_nv ? PF_VARIANT_ATTN_STREAM : PF_VARIANT_ATTN_ONE_PASS);
+    int variant = forced_variant >= 0 ? forced_variant : (chunks >= 8 && (one_slice || !polled) && !forced_nv ? PF_VARIANT_ATTN_STREAM : PF_VARIANT_ATTN_ONE_PASS);
     if (variant != PF_VARIANT_ATTN_ONE_PASS && variant != PF_VARIANT_ATTN_STREAM)
         return fail(PF_ERR_UNSUPPORTED, "unknown attention variant %d", variant);
     if (variant == PF_VARIANT_ATTN_STREAM) {
@@ -1498,9 +1503,6 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     a.part_stride = (uint32_t)((d + 2 + 31) / 32 * 32);
     const uint64_t part_bytes = ((uint64_t)heads * splits * a.part_stride * sizeof(float) + 255) / 256 * 256;
     const uint64_t cnt_bytes = ((uint64_t)heads * sizeof(uint32_t) + 255) / 256 * 256;
-    // A plan that owns its workspace merges by polling self-describing words (a bounded wait, reported through the plan);
-    // a call that plans and runs in one go has no plan to report through and keeps the counted, wait-free merge.
-    const bool polled = !planning_static() && env_int("PF_ATTN_POLLED", 1) != 0;
     pf_status ws_st = plan_workspace_alloc(p, part_bytes + cnt_bytes + 256, "workspace allocation");
     if (ws_st != PF_OK) return ws_st;
     if ((ws_st = plan_workspace_fill(p, p->workspace, polled ? 0xff : 0, part_bytes, polled)) != PF_OK) return ws_st;

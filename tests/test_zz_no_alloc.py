@@ -110,3 +110,14 @@ def test_refusals_name_the_other_entry_points():
     outs = [torch.empty_like(dev[0]) for _ in spec.outputs]
     st = pf.pf_chain_run_static(desc, 0, [t.data_ptr() for t in dev], [o.data_ptr() for o in outs], 0)
     assert st == pf.PF_ERR_UNSUPPORTED and "pf_chain_plan" in pf.pf_last_error()
+
+
+def test_attention_over_a_long_cache_fits_the_scratch_array():
+    """4001 rows of 256 fp32 for each of 16 heads: 48 slices a head when they are walked, 126 (2.2 MB of partial results, more
+    than the array) when each is held in registers at once."""
+    spec, ins = wl.x2_decode_attention(b=1, h=16, t=4000, d=256, dtype="f32")
+    got = run_static(spec, ins)
+    with env(PF_ATTN_POLLED="0"):
+        ref = run_planned(spec, ins)
+    assert np.array_equal(wl.raw_bits(got[0]), wl.raw_bits(ref[0]))
+    compare(got[0], oracle_run(spec, ins)[0], "f32", "static attention, long cache")
