@@ -1456,31 +1456,37 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     // pressure.)
     const int64_t rps = 256 / lpr;
     int nv = 4;
+    int64_t dp = 1;
+    while (dp < d) dp *= 2;
+    const int64_t groups = 256 / dp;  // thread groups of the merge
     {
-        int64_t dp = 1;
-        while (dp < d) dp *= 2;
         const int64_t slices8 = heads * ((t_total + rps * 8 - 1) / (rps * 8)), splits4 = (t_total + rps * 4 - 1) / (rps * 4);
-        if (slices8 >= 2 * (int64_t)n_cu || (polled && slices8 >= n_cu && splits4 > 2 * (256 / dp))) nv = 8;
+        if (slices8 >= 2 * (int64_t)n_cu || (polled && slices8 >= n_cu && splits4 > 2 * groups)) nv = 8;
     }
     const int forced_nv = env_int("PF_ATTN_NV", 0);
     if (forced_nv == 1 || forced_nv == 2 || forced_nv == 4 || forced_nv == 8) nv = forced_nv;
-    // Streaming variant: a workgroup walks `chunks` chunks of 2 steps each with the next chunk's loads in flight.  Taken where
-    // that leaves a head one slice (many heads: no device-scope merge at all).  With more slices the one-pass kernel's deeper
-    // load burst counts for more, now that a merge reads many slices in one trip (8 x 25 heads, t = 4095: 43.7 us streamed, 39.9
-    // in one pass; 4 x 25, t = 8191: 43.5 and 41.9; 4 x 32, t = 2047, d = 128: 31.2 and 29.5; 16 x 25, t = 1023: 24.0 and 21.8).
-    // The counted merge takes a trip per slice and, in a static call, its partial results have a fixed array to fit in (2 MB:
-    // 4 x 32 heads, t = 4096, d = 128 fill 0.5 MB streamed, 2.5 MB in one pass): there slices of eight chunks on are streamed.
+    // Streaming variant: a workgroup walks `chunks` chunks of 2 steps each with the next chunk's loads in flight.  Taken from
+    // eight chunks on where that leaves a head one slice (many heads: no device-scope merge at all), where the merge is the
+    // counted one, and where one pass would leave a head more slices than the merge has in flight in one trip, eight per thread
+    // group: a further trip for every 8 groups behind the last slice costs more than the one-pass kernel's deeper load burst
+    // gains.  us streamed and in one pass, fp16 -- d = 64, a trip is 32 slices: 200 heads, t = 4095 (16 slices) 42.7, 40.5;
+    // t = 8191 (32) 78.7, 77.9; t = 16383 (64) 151.7, 153.6; d = 128, 16 slices a trip: 4 x 32 heads, t = 2047 (16) 31.2, 29.5;
+    // 64 heads, t = 4095 (32) 32.0, 32.7; t = 8191 (64) 56.2, 62.2; t = 32767 (256) 197, 243; 8 heads, t = 131071 (1024) 111,
+    // 214.  Below eight chunks the streamed slices are short and can be more than those of one pass (one head, t = 65535,
+    // d = 128: 683 and 512, 98 and 66 us; not always: 8 heads, t = 16383, d = 128: 86 and 128, 28.6 and 34.4).  In a static call the partial results have a fixed array to fit in as well (2 MB: 4 x 32 heads, t = 4096,
+    // d = 128 fill 0.5 MB streamed, 2.5 MB in one pass).
     int64_t chunks = 1;
-    bool one_slice = false;
+    bool stream = false;
     {
         const int64_t all_chunks = (t_total + rps * 2 - 1) / (rps * 2);
         const int64_t target_splits = std::max<int64_t>(1, (3 * (int64_t)n_cu + heads - 1) / heads);
         const int64_t c = (all_chunks + target_splits - 1) / target_splits;
         const int forced_chunks = env_int("PF_ATTN_CHUNKS", 0);
         chunks = forced_chunks > 0 ? forced_chunks : c;
-        one_slice = chunks >= all_chunks;
+        const int64_t splits_one_pass = (t_total + rps * nv - 1) / (rps * nv);
+        stream = chunks >= 8 && !forced_nv && (chunks >= all_chunks || !polled || splits_one_pass > 8 * groups);
     }
-    int variant = forced_variant >= 0 ? forced_variant : (chunks >= 8 && (one_slice || !polled) && !forced_nv ? PF_VARIANT_ATTN_STREAM : PF_VARIANT_ATTN_ONE_PASS);
+    int variant = forced_variant >= 0 ? forced_variant : (stream ? PF_VARIANT_ATTN_STREAM : PF_VARIANT_ATTN_ONE_PASS);
     if (variant != PF_VARIANT_ATTN_ONE_PASS && variant != PF_VARIANT_ATTN_STREAM)
         return fail(PF_ERR_UNSUPPORTED, "unknown attention variant %d", variant);
     if (variant == PF_VARIANT_ATTN_STREAM) {

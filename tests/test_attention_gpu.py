@@ -165,3 +165,14 @@ def test_bounded_wait_of_the_merging_slice_gives_up_instead_of_hanging():
     with env(PF_ATTN_POLLED="0"):
         _, info, _ = check_chain(spec, ins, what="attention, counted merge")
     assert info.n_launches == 1
+
+
+@pytest.mark.parametrize("h,t,d,splits,stream", [(50, 8191, 64, 32, False), (50, 8192, 64, 15, True), (24, 9000, 128, 32, True), (1, 20000, 128, 313, False)])
+def test_slices_of_long_caches_are_merged_in_one_trip_or_walked(h, t, d, splits, stream):
+    # one workgroup merges a head's slices, 8 per thread group (256 / d) a trip: beyond that slices are longer, unless the
+    # streamed ones would be more still (one head)
+    pf = _pf()
+    spec, ins = wl.x2_decode_attention(b=1, h=h, t=t, d=d, dtype="f16")
+    _, info, _ = check_chain(spec, ins, what=f"attention, t={t}, {h} heads")
+    assert info.variant == (pf.PF_VARIANT_ATTN_STREAM if stream else pf.PF_VARIANT_ATTN_ONE_PASS)
+    assert info.grid[0] == splits
