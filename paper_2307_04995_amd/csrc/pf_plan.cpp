@@ -1316,12 +1316,15 @@ pf_status plan_pool(pf_plan_s* p) {
     // 21 us, 32: 17.7 us, 16: 17.1 us, 8: 19.5 us, 4: 28 us; with SiLU in front 32 slices are best).
     int nv = 8;
     while (nv > 1 && (int64_t)(nv / 2) * g.pos_per_step >= hw) nv /= 2;
-    // Half the chunk where whole ones would not give every compute unit two and the twice as many slices are still merged in one
-    // round of eight per row group, and not where a sample is a slice or a few ([2, 28, 28, 256] fp16 7.0 -> 6.4 us; three slices for two [7, 10, 10, 416] 7.1 -> 8.0; in two rounds [10, 28,
-    // 28, 336] 7.7 -> 8.6), and for element-aligned positions, whose eight loads and partial stores crowd the registers ([32,
-    // 56, 56, 244] 24.8 -> 19.9); elsewhere eight are as good or better ([32, 56, 56, 240] 13.6 against 14.0).
+    // Half the chunk where whole ones would not give every compute unit two and the twice as many slices are still merged in
+    // one round of eight per row group, and not where a sample is a slice or a few ([2, 28, 28, 256] fp16 7.0 -> 6.4 us; three
+    // slices for two [7, 10, 10, 416] 7.1 -> 8.0; in two rounds [10, 28, 28, 336] 7.7 -> 8.6); elsewhere eight are as good or
+    // better ([32, 56, 56, 240] 13.6 against 14.0).  Also for element-aligned positions, whose eight loads and partial stores
+    // crowd the registers: [32, 56, 56, 244] 24.8 -> 19.9, and where the halves of what was one slice have to be merged as well
+    // ([4, 9, 10, 244] 8.7 -> 7.9, [128, 15, 15, 100] 10.3 -> 9.9, [32, 9, 10, 130] fp32 10.3 -> 8.7).  A static call keeps the
+    // whole chunk: it runs one slice per sample and refuses two.
     const int64_t slices8 = (hw + 8 * g.pos_per_step - 1) / (8 * g.pos_per_step), slices4 = (hw + 4 * g.pos_per_step - 1) / (4 * g.pos_per_step);
-    if (nv == 8 && (ragged_c || (slices8 >= 4 && n * slices8 < 2 * n_cu && slices4 - 1 <= 8 * std::max<int64_t>(1, 512 / ch)))) nv = 4;
+    if (nv == 8 && !planning_static() && (ragged_c || (slices8 >= 4 && n * slices8 < 2 * n_cu && slices4 - 1 <= 8 * std::max<int64_t>(1, 512 / ch)))) nv = 4;
     const int forced_nv = env_int("PF_POOL_NV", 0);
     if (forced_nv == 1 || forced_nv == 2 || forced_nv == 4 || forced_nv == 8) nv = forced_nv;
     const int64_t chunk_pos = (int64_t)nv * g.pos_per_step;

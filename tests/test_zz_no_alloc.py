@@ -121,3 +121,17 @@ def test_attention_over_a_long_cache_fits_the_scratch_array():
         ref = run_planned(spec, ins)
     assert np.array_equal(wl.raw_bits(got[0]), wl.raw_bits(ref[0]))
     compare(got[0], oracle_run(spec, ins)[0], "f32", "static attention, long cache")
+
+
+@pytest.mark.parametrize("dtype,c,side", [("f16", 244, 10), ("bf16", 100, 16), ("f32", 130, 10), ("f16", 1001, 2)])
+def test_pooling_of_small_ragged_samples(dtype, c, side):
+    """A sample that eight position steps cover is one workgroup's in a static call: nothing to merge.  (A plan cuts such a sample
+    in two where the channels are not whole vectors.)"""
+    spec = wl.ChainSpec(inputs=[(dtype, (4, side, side, c))])
+    spec.out(spec.op("reduce_mean", 0, i=[1, 2]), dtype)
+    ins = [wl.random_tensor((4, side, side, c), dtype, 9700 + c)]
+    got = run_static(spec, ins)
+    with env(PF_POOL_NV="8"):
+        ref = run_planned(spec, ins)
+    assert np.array_equal(wl.raw_bits(got[0]), wl.raw_bits(ref[0]))
+    compare(got[0], oracle_run(spec, ins)[0], dtype, f"static pooling {c} channels")
