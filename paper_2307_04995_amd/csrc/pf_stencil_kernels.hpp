@@ -191,11 +191,25 @@ __global__ void __launch_bounds__(256) dwconv3x3_kernel(const ChainArgs a, const
 //
 // LDS layout: tile[input row 0..7][staging lane 0 .. 256 + 2 cv), entries of 16 bytes (packed storage type, when
 // the prologue keeps storage precision) or 32 bytes (fp32).  Lanes read consecutive entries: no bank conflicts.
+//
+// Registers: where LDS holds four workgroups of a unit (a packed tile, or fp32 entries) and one operand is staged, four waves
+// per SIMD are asked for, 128 registers a lane.  A 16-bit tile of widened values is 64 KB and more, two workgroups, and several
+// operands do not fit 128 registers: held to them, both spilled (x + y, SiLU, 3 x 3 on [32, 56, 56, 240] fp16 94 us, 50 without).
+template <int DT, class Spec, int KS>
+struct StagedShape {
+    static constexpr bool kPacked = DT != DT_F32 && list_keeps_storage_precision<typename Spec::Pro>();
+    static constexpr int kOperands = Spec::kStatic ? __builtin_popcount(list_operand_mask<typename Spec::Pro>(K_FULL)) : Spec::NF;
+    static constexpr int kWaves = Spec::kStatic && KS == 3 && kOperands == 1 && (kPacked || DT == DT_F32) ? 4 : 1;
+    // staging lanes of a lane whose loads are in flight together (5 x 5 keeps no kernel vectors beside them: x + y in front on
+    // [16, 28, 28, 96] fp16 9.7 us with one, 9.2 with two, bf16 11.0 and 10.3)
+    static constexpr int kStaged = kOperands == 1 || (Spec::kStatic && KS == 5) ? 2 : 1;
+};
+
 template <int DT, class Spec, int KS, bool RAGGED = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Spec::kStatic && KS == 3 ? 4 : 1))) dwconv_staged_kernel(const ChainArgs a, const StencilGeom g) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(StagedShape<DT, Spec, KS>::kWaves))) dwconv_staged_kernel(const ChainArgs a, const StencilGeom g) {
     using S = Storage<DT>;
     constexpr int VEC = S::VEC;
-    constexpr bool kPacked = DT != DT_F32 && list_keeps_storage_precision<typename Spec::Pro>();
+    constexpr bool kPacked = StagedShape<DT, Spec, KS>::kPacked;
     constexpr int EV = (kPacked || DT == DT_F32) ? 1 : 2;  // 16-byte vectors per tile entry
     static_assert(KS == 3 || KS == 5, "kernel extents 3 and 5");
     constexpr int R = KS / 2;                      // halo rows above and below, halo image columns left and right
@@ -226,9 +240,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Spec::
 
     // ---- stage: staging lane j of input row h0 - R + r holds image lane t0 - R * cv + j.  Two staging lanes per lane at a
     // time (256 and the halo, unless a position has more than 128 vectors): their rows are all requested before the first is
-    // worked on.  No branch around a load: what lies outside the image reads a vector that exists and becomes zero in the tile.
+    // worked on; one at a time where several operands' eight rows fill the registers beside 3 x 3 kernels.  No branch around a
+    // load: what lies outside the image reads a vector that exists and becomes zero in the tile.
     constexpr bool ragged = RAGGED;
-    constexpr int kPair = 2;
+    constexpr int kPair = StagedShape<DT, Spec, KS>::kStaged;
     for (uint32_t j0 = threadIdx.x; j0 < tw; j0 += 256u * kPair) {
         uint32_t lp[kPair], cvi_j[kPair], wcol_j[kPair];
         bool lane_ok[kPair];
