@@ -1033,11 +1033,6 @@ pf_status plan_stencil(pf_plan_s* p, const Checked& c, int forced_variant) {
     for (int v = 0; v < L.n_vec; ++v)
         if (v != L.core_vec[0] && (p->args.vec[v].numel > (uint32_t)ch || p->args.vec[v].n_terms != 0)) by_channel = false;
     if (by_channel) jspec.flags |= 4;
-    // a launch that leaves compute units idle: registers do not limit what is resident
-    {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, p->device) == hipSuccess && (uint64_t)p->grid.x * p->grid.y * p->grid.z <= (uint64_t)prop.multiProcessorCount) jspec.flags |= 8;
-    }
     const pf_op_desc& conv = p->desc.ops[L.core_op];
     const int64_t stride = conv.n_i == 1 ? conv.i[0] : 1;
     if (stride > 1) {
@@ -1107,6 +1102,13 @@ pf_status plan_stencil(pf_plan_s* p, const Checked& c, int forced_variant) {
     }
     if (jit_ok) {
         std::string err;
+        if (variant == PF_VARIANT_STENCIL_DIRECT) jspec.flags &= ~4;  // (loads its operands at every position)
+        // A launch that leaves compute units idle: registers do not limit what is resident.  Read by the 5 x 5 kernels that widen
+        // 16-bit values alone (others would be compiled twice).
+        if (ksz == 5 && L.main_dtype != PF_F32 && !(exact_pro && L.main_dtype == PF_F16)) {
+            hipDeviceProp_t prop;
+            if (hipGetDeviceProperties(&prop, p->device) == hipSuccess && (uint64_t)g.tiles <= (uint64_t)prop.multiProcessorCount) jspec.flags |= 8;
+        }
         p->jit_fn = pf::jit_stencil_kernel(p->device, L.main_dtype, variant, ksz, ragged_c, jspec, &err);
         if (p->jit_fn) p->spec_id = pf::kSpecJit;
         else {

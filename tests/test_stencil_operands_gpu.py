@@ -55,3 +55,14 @@ def test_nan_infinities_and_signed_zeros_in_front(dtype):
         t[0][0, 2, 3, 1], t[0][0, 8, 8, 2], t[0][0, 5, 5, 3] = float("nan"), -float("nan"), -0.0
         t[0][0, 9, 1, 4] = float("inf")      # (RELU of -inf is 0, of +inf an infinity or, beside a zero weight, none)
         check_chain(s, t, what=f"{pre} {dtype}")
+
+
+@pytest.mark.parametrize("k,stride,dtype,pre", [(3, 1, "f16", "silu"), (3, 2, "f16", "silu"), (5, 2, "bf16", "silu"), (5, 1, "f32", "silu"), (5, 1, "f16", "neg")])
+def test_one_kernel_serves_small_and_large_tensors(k, stride, dtype, pre):
+    from paper_2307_04995_amd import binding as pf
+    s, _ = _chain(dtype, (1, 12, 12, 64), k, stride, [pre, "neg"], "channel", seed=30)
+    pf.Plan(s, 0).close()
+    compiled = pf.pf_jit_compile_count() + pf.pf_jit_cache_hits()
+    s.inputs[0] = (dtype, (64, 112, 112, 64))
+    pf.Plan(s, 0).close()
+    assert pf.pf_jit_compile_count() + pf.pf_jit_cache_hits() == compiled
