@@ -602,7 +602,9 @@ pf_status plan_perm(pf_plan_s* p, int forced_variant) {
             // always ([2, 96, 15, 15] 9.1 -> 7.2).
             const int64_t planes = numel(in) / (n_a * n_b), per_plane = (flat_rows + step - 1) / step;
             const bool enough = planes * per_plane >= 512 || (!flat_out && step * es == 128);
-            if (enough && lds_of(step) <= 64 * 1024 && planes * per_plane <= 0x7fffffffLL) {
+            // (a launch holds fewer than 2^32 lanes, strips are dealt to eight dies: with more than that the tiles take over, four to
+            // a workgroup)
+            if (enough && lds_of(step) <= 64 * 1024 && planes * per_plane <= (1LL << 24) - 8) {
                 pf::PlaneGeom& pg = p->planeg;
                 pg.a = (uint32_t)n_a;
                 pg.b = (uint32_t)n_b;

@@ -484,3 +484,12 @@ def test_column_family_sizes_its_slab_to_the_column():
         info = pf.pf_chain_plan_get_info(h)
         pf.pf_chain_plan_destroy(h)
         assert info.family != pf.PF_FAMILY_COLUMN or info.n_kernels > 1
+
+
+def test_plane_swaps_of_very_many_planes_stay_within_a_launch():
+    # a launch holds fewer than 2^32 lanes: 2^24 workgroups of 256, less what the strips are rounded up by
+    for shape in ((20_000_000, 3, 5), (1 << 24, 5, 3), ((1 << 24) - 7, 5, 3), ((1 << 24) - 8, 5, 3), (70_000, 3, 5)):
+        s = wl.ChainSpec(inputs=[("f16", shape)])
+        s.out(s.op("permute", 0, i=[0, 2, 1]), "f16")
+        info, _ = _plan_info(s)
+        assert list(info.grid)[0] * list(info.block)[0] < 1 << 32, shape

@@ -57,3 +57,16 @@ def test_feature_maps_and_what_stays_on_tiles():
     _run((3, 1500, 1201), [0, 2, 1], "f16", 3, 8103)     # rows too long for a strip in LDS
     _run((5, 6, 7, 9), [3, 1, 2, 0], "f32", 1, 8104)     # not a swap of adjacent dimensions
     _run((4, 3, 50, 11), [1, 0, 3, 2], "bf16", 1, 8105)  # the planes change places as well
+
+
+def test_more_planes_than_a_launch_has_strips():
+    from paper_2307_04995_amd import binding as pf
+    planes = (1 << 24) + 5000
+    s = wl.ChainSpec(inputs=[("f16", (planes, 3, 5))])
+    s.out(s.op("permute", 0, i=[0, 2, 1]), "f16")
+    x = torch.randint(-30000, 30000, (planes, 3, 5), dtype=torch.int16, device="cuda")
+    out = torch.zeros((planes, 5, 3), dtype=torch.int16, device="cuda")
+    plan = pf.Plan(s, 0)
+    plan.run([x.view(torch.float16)], [out.view(torch.float16)])
+    assert torch.equal(out, x.transpose(1, 2))
+    plan.close()
