@@ -531,32 +531,20 @@ __global__ void __launch_bounds__(256) perm_plane_kernel(const void* in, void* o
             }
         }
         __syncthreads();
-        // the output stretch, on the grid of aligned vectors: its first and last vector may belong to neighbours in part
-        const uint64_t first = plane_elem + (uint64_t)s0 * g.a;
-        const uint32_t off = (uint32_t)(first % VEC);
-        const uint64_t vec0 = first / VEC;
-        const uint32_t n = off + cols * g.a, nv = (n + VEC - 1u) / VEC;
+        // the output stretch: whole vectors from an aligned one on, as `cols` is a number of whole vectors
+        const uint64_t vec0 = (plane_elem + (uint64_t)s0 * g.a) / VEC;
+        const uint32_t nv = pieces * g.a;
         for (uint32_t v = tid; v < nv; v += 256u) {
-            const uint32_t lo = v == 0u ? off : 0u, hi = min(VEC, n - v * VEC);
-            const uint32_t f = v * VEC + lo - off;
-            uint32_t col = fast_div(f, g.div_a), row = f - col * g.a;
+            uint32_t col = fast_div(v * VEC, g.div_a), row = v * VEC - col * g.a;
             elem e[VEC];
-            // (no branch around a read: elements in front of the stretch read its first, those behind it a column that is not used)
 #pragma unroll
             for (uint32_t k = 0; k < VEC; ++k) {
                 e[k] = tile[row * pitch + col];
-                row += k >= lo ? 1u : 0u;
-                const bool wrap = row == g.a;
+                const bool wrap = ++row == g.a;
                 row = wrap ? 0u : row;
                 col += wrap ? 1u : 0u;
             }
-            if (lo == 0u && hi == VEC) {
-                store_stream(out, (vec0 + v) * 16u, PlaneElem<DT>::pack(e));
-            } else {
-#pragma unroll
-                for (uint32_t k = 0; k < VEC; ++k)
-                    if (k >= lo && k < hi) static_cast<elem*>(out)[(vec0 + v) * VEC + k] = e[k];
-            }
+            store_stream(out, (vec0 + v) * 16u, PlaneElem<DT>::pack(e));
         }
     }
 }

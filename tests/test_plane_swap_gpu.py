@@ -51,7 +51,7 @@ def test_feature_maps_and_what_stays_on_tiles():
     # (a flat output takes 512 strips at least: 260 planes of two)
     assert _run((260, 14, 14, 72), [0, 3, 1, 2], "f16", 260, 8102) == (260 * 2 + 7) // 8 * 8
     _run((19, 14, 14, 72), [0, 3, 1, 2], "f16", 19, 8106)
-    for shape in ((520, 33, 16), (260, 3, 72), (172, 101, 136), (520, 900, 24)):   # flat outputs: remainders of both kinds
+    for shape in ((520, 33, 16), (260, 3, 72), (172, 101, 136), (520, 900, 24)):   # flat outputs: a last strip that is not full, a partial step of the walk
         for dtype in ("f16", "f32"):
             _run(shape, [0, 2, 1], dtype, shape[0], 8107)
     _run((3, 1500, 1201), [0, 2, 1], "f16", 3, 8103)     # rows too long for a strip in LDS
