@@ -399,6 +399,17 @@ template <bool PRECISE>
 PF_DEVICE float pf_sigmoid(float x) {
     return pf_rcp<PRECISE>(1.0f + pf_exp<PRECISE>(-x));
 }
+// The same as exact as with expf and an IEEE division (over all arguments 2.0 ulp at most and 0.235 in the mean square, both;
+// the quick form 58 and 1.7), in 19 steps for some 32.  e^-x = 2^n 2^d: the fused steps lose nothing of
+// x log2 e - n, however large x is, and keep what is infinite or NaN (n is clamped, d is not).  One Newton step follows the
+// reciprocal; an infinite denominator is the fix-up's.
+PF_DEVICE float pf_sigmoid_reduced(float x) {
+    const float n = __builtin_amdgcn_fmed3f(__builtin_rintf(x * -kLog2e), -160.0f, 160.0f);
+    const float d = __builtin_fmaf(x, -1.9259630e-8f, __builtin_fmaf(x, -kLog2e, -n));  // (log2 e - kLog2e)
+    const float a = 1.0f + __builtin_ldexpf(__builtin_amdgcn_exp2f(d), (int)n);
+    const float y = __builtin_amdgcn_rcpf(a);
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-a, y, 1.0f), y, y), a, 1.0f);
+}
 template <bool PRECISE>
 PF_DEVICE float pf_tanh(float x) {
     if (PRECISE) return tanhf(x);
@@ -463,6 +474,7 @@ struct GenericSpec {
     static constexpr int kVecMode = 3;    // ... and so is a broadcast operand with a single element
     static constexpr bool kVecChannel = false;
     static constexpr bool kFewBlocks = false;
+    static constexpr bool kPrecise = false;
     static constexpr int NF = 3, NV = 4, NT = PF_DEV_MAX_TMP;
     using Pro = DynList;
     using Epi = DynList;
@@ -476,7 +488,8 @@ struct GenericSpec {
 // FLAGS_: bit 0 = some operand broadcasts the general way (extents of 1 anywhere); bit 1 = some broadcast operand has a
 // single element; bit 2 (stencil family) = every broadcast operand is indexed by channel alone, whatever the position, so
 // it is loaded once; bit 3 (stencil family) = at most one workgroup per compute unit; bit 4 (held rows) = no score of a
-// softmax is as large as 2^20.  Kernels built without a bit carry none of that case's code: the one-element case in particular
+// softmax is as large as 2^20; bit 5 (parts of a chain of several kernels) = element-wise steps on 16-bit storage as exact as
+// on fp32.  Kernels built without a bit carry none of that case's code: the one-element case in particular
 // costs more than its branch, because the compiler issues its 2-byte load next to the 16-byte one and waits for both
 // before it goes on, which turns the operand loads of a kernel into one memory round trip after the other.
 template <int NF_, int NV_, int NT_, int CORE_, int GAMMA_, int BETA_, class ProL, class EpiL, int FLAGS_ = 0>
@@ -487,6 +500,7 @@ struct StaticSpec {
     static constexpr bool kVecChannel = (FLAGS_ & 4) != 0;
     static constexpr bool kFewBlocks = (FLAGS_ & 8) != 0;
     static constexpr bool kSmallScores = (FLAGS_ & 16) != 0;
+    static constexpr bool kPrecise = (FLAGS_ & 32) != 0;
     static constexpr int NF = NF_, NV = NV_, NT = NT_;
     static constexpr int kGamma = GAMMA_, kBeta = BETA_;
     using Pro = ProL;
@@ -685,7 +699,7 @@ template <int DT, int K, class Spec>
 PF_DEVICE void apply_uop(int code, int slot, int32_t ival, LaneState<DT, K, Spec>& s, const float* b) {
     constexpr int E = LaneState<DT, K, Spec>::E;
     constexpr int VEC = LaneState<DT, K, Spec>::VEC;
-    constexpr bool PR = Storage<DT>::PRECISE;
+    constexpr bool PR = Storage<DT>::PRECISE || Spec::kPrecise;
     switch (code) {
         case U_MOV:
 #pragma unroll
@@ -733,11 +747,11 @@ PF_DEVICE void apply_uop(int code, int slot, int32_t ival, LaneState<DT, K, Spec
             break;
         case U_SIGMOID:
 #pragma unroll
-            for (int e = 0; e < E; ++e) s.acc[e] = pf_sigmoid<PR>(s.acc[e]);
+            for (int e = 0; e < E; ++e) s.acc[e] = Spec::kPrecise ? pf_sigmoid_reduced(s.acc[e]) : pf_sigmoid<PR>(s.acc[e]);
             break;
         case U_SILU:
 #pragma unroll
-            for (int e = 0; e < E; ++e) s.acc[e] = s.acc[e] * pf_sigmoid<PR>(s.acc[e]);
+            for (int e = 0; e < E; ++e) s.acc[e] = s.acc[e] * (Spec::kPrecise ? pf_sigmoid_reduced(s.acc[e]) : pf_sigmoid<PR>(s.acc[e]));
             break;
         case U_GELU_ERF:
 #pragma unroll

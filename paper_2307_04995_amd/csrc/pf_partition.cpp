@@ -221,8 +221,10 @@ pf_status partition_chain(const pf_chain_desc* user, const Checked& c, const std
 // A chain split as [.. group normalisation ..] [.. pooling ..]: the normalised tensor, which only the pooling reads, need
 // not exist.  The first kernel computes the group statistics alone, the second normalises what it pools.  Both read
 // the caller's tensors in their own storage type, so nothing is widened or rounded around them either: two reads of x
-// instead of nine times its bytes ([32, 64, 64, 320] fp16, GroupNorm + SiLU + mean over positions).  Needs kernels
-// specialised for the chain.  PF_ERR_UNSUPPORTED leaves the chain to the general split.
+// instead of nine times its bytes ([32, 64, 64, 320] fp16, GroupNorm + SiLU + mean over positions).  Their element-wise steps
+// stay as exact as the fp32 kernels' that the general split runs (StaticSpec::kPrecise: the 16-bit kernels' quick forms, which
+// a rounding to 16 bits would hide where it follows at once, are off by 1e-3 of a tanh near zero): that call 262 us split, 46.8
+// with the quick forms, 70.0 with the library's, 57.2 with pf_sigmoid_reduced.  Needs kernels specialised for the chain.  PF_ERR_UNSUPPORTED leaves the chain to the general split.
 static pf_status plan_norm_pool(const pf_chain_desc* user, const Checked& c, int32_t device, pf_plan_s* p) {
     int norm = -1, core2 = -1;
     for (int k = 0; k < user->n_ops; ++k) {

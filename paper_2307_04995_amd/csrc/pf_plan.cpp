@@ -889,7 +889,8 @@ pf_status plan_group(pf_plan_s* p, int forced_variant) {
     // resident variant: catalogue entry, one full operand, per-channel broadcast operands only, and a grid the
     // device holds at once
     const bool jit_ok = p->spec_id == 0 && jit_possible(p->device);
-    const pf::JitSpec jspec = make_jit_spec(L);
+    pf::JitSpec jspec = make_jit_spec(L);
+    if (p->stats_only && L.main_dtype != PF_F32) jspec.flags |= 32;
     std::string jit_err;
     hipFunction_t fused_fn = nullptr;
     bool resident_ok = L.n_full == 1 && g.vec_per_channel && forced_variant != PF_VARIANT_GROUP_TWO_PASS;
@@ -1376,7 +1377,9 @@ pf_status plan_pool(pf_plan_s* p) {
     }
     if (jit_possible(p->device)) {
         std::string err;
-        p->jit_fn = pf::jit_pool_kernel(p->device, L.main_dtype, nv, L.pool_op, ragged_c, make_jit_spec(L), &err);
+        pf::JitSpec jspec = make_jit_spec(L);
+        if (L.norm_op >= 0 && L.main_dtype != PF_F32) jspec.flags |= 32;
+        p->jit_fn = pf::jit_pool_kernel(p->device, L.main_dtype, nv, L.pool_op, ragged_c, jspec, &err);
         if (p->jit_fn) p->spec_id = pf::kSpecJit;
         else note_interpreter_fallback(p, err);
     }

@@ -99,3 +99,45 @@ def test_repeated_runs_and_replays_of_a_graph():
         compare(out.cpu(), oracle_run(s, [x] + t[1:])[0], "f16", f"eager run {rep}")
     assert plan.poll_error() == 0
     plan.close()
+
+
+@pytest.mark.parametrize("mid", ["tanh", "sigmoid", "silu", "gelu_erf", "exp"])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_steps_in_between_are_as_exact_as_in_fp32(dtype, mid):
+    # Between normalisation and pooling the values are fp32 and no tensor of 16 bits: near zero, where tanh by way of 2 sigmoid(2 x)
+    # - 1 keeps 1e-7 of 1, and with the result scaled up so that its rounding to the storage type (half a step, 2^-11 or 2^-8 of
+    # the value) is all the error there is, beside 1e-5 for the fp32 steps and, for GELU, the 3e-7 |x| of its approximation.
+    s, t = _chain((2, 12, 12, 64), 8, dtype, mid="none")
+    t[1] = torch.full((64,), 2.0 ** -15 if mid in ("tanh", "gelu_erf", "silu") else 1.0).to(t[1].dtype)
+    t[2] = torch.zeros_like(t[2])
+    s = wl.ChainSpec(inputs=s.inputs)
+    v = s.op(mid, s.op("groupnorm", 0, 1, 2, f=[1e-5], i=[8]))
+    v = s.op("reduce_max", v, i=[1, 2])
+    s.out(s.op("scale", v, f=[2.0 ** 14]), dtype) if mid in ("tanh", "gelu_erf", "silu") else s.out(v, dtype)
+    outs, info = gpu_run(s, t)
+    assert info.n_launches == 2
+    want = oracle_run(s, t)[0]
+    got = wl.widen(outs[0])
+    bar = (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) + 1e-5
+    assert (abs(got - want) / abs(want)).max() <= bar
+    # ... and against the chain as kernels of its own on fp32 copies: the same value, or the next one where it lies halfway
+    with env(PF_NORM_POOL="0"):
+        split, info = gpu_run(s, t)
+    assert info.n_launches > 2
+    assert (abs(got - wl.widen(split[0])) / abs(want)).max() <= 2.0 * bar
+    assert (got != wl.widen(split[0])).mean() < 0.02
+
+
+@pytest.mark.parametrize("mid", ["sigmoid", "silu", "tanh"])
+def test_infinities_and_nan_in_between(mid):
+    # a residual of +-inf, NaN and the lowest value joins behind the normalisation
+    shape = (1, 4, 4, 64)
+    s, t = _chain(shape, 8, "f16", mid="none", seed=40)
+    y = wl.random_tensor(shape, "f16", 6300)
+    y[0, 1, 1, 3], y[0, 2, 2, 9], y[0, 0, 3, 17], y[0, 3, 0, 33], y[0, 3, 1, 40] = float("inf"), -float("inf"), float("nan"), 9.0, -65504.0
+    s = wl.ChainSpec(inputs=s.inputs + [("f16", shape)])
+    v = s.op("add", s.op("groupnorm", 0, 1, 2, f=[1e-5], i=[8]), 3)
+    s.out(s.op("reduce_sum", s.op(mid, v), i=[1, 2]), "f16")
+    outs, info = gpu_run(s, t + [y])
+    assert info.n_launches == 2
+    compare(outs[0], oracle_run(s, t + [y])[0], "f16", f"infinities in front of {mid}")
