@@ -416,8 +416,17 @@ __global__ void __launch_bounds__(MAXT) row_kernel(const ChainArgs a, const RowG
                     sum += acc[e];
                 }
             } else {
+                // One fused step does both multiplication and subtraction.  The rounding of mc, a common factor of the row that the
+                // division takes out, would be an exponent of its own where the maximum is large (2^328 in a bf16 row masked
+                // throughout with -1e10): from 2^20 on the maximum is subtracted first.
                 const float c2 = cs * kLog2e;
-                const float mc = -m * c2;
+                float mc = -m * c2;
+                if (!(__builtin_fabsf(mc) < 1048576.0f)) {
+                    asm volatile("");  // (a branch that few rows take, not a selection per element)
+#pragma unroll
+                    for (int e = 0; e < EC; ++e) acc[e] -= m;
+                    mc = 0.0f;
+                }
 #pragma unroll
                 for (int e = 0; e < EC; ++e) {
                     acc[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[e], c2, mc));

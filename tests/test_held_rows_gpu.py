@@ -97,7 +97,7 @@ def test_large_common_offset_and_in_place():
     assert torch.equal(buf.cpu(), outs[0])
 
 
-@pytest.mark.parametrize("rows,n", [(4, 50257), (4, 50264)])
+@pytest.mark.parametrize("rows,n", [(4, 50257), (4, 50264), (520, 4097)])
 @pytest.mark.parametrize("value", [-1e10, 1e10, float(torch.finfo(torch.bfloat16).min), float(torch.finfo(torch.bfloat16).max)])
 def test_rows_masked_throughout(value, rows, n):
     # a row of one large value (everything masked with -1e10 or the type's lowest value) is 1 / n per element: the exponent is

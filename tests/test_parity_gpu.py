@@ -518,3 +518,16 @@ def test_pointer_arrays_marshalled_once_give_the_same_result():
     assert torch.equal(a, b)
     compare(b.cpu(), oracle_run(spec, ins)[0], "f32", "run_set")
     plan.close()
+
+
+@pytest.mark.parametrize("n", [8, 24, 64, 197, 512, 1024, 4000, 8192, 20001])
+@pytest.mark.parametrize("value", [-1e10, 1e10, float(torch.finfo(torch.bfloat16).min)])
+def test_softmax_of_rows_masked_throughout(value, n):
+    # 1 / n per element, whatever the product of the maximum with log2 e rounds to; rows of ordinary values beside them
+    s = wl.ChainSpec(inputs=[("bf16", (37, n))])
+    s.out(s.op("softmax", s.op("scale", 0, f=[0.5])), "bf16")
+    x = wl.random_tensor((37, n), "bf16", 9800 + n, scale=3.0)
+    x[::3, :] = value
+    x[1, n // 2:] = value
+    outs, _, _ = check_chain(s, [x], what=f"softmax of rows of {value}, n {n}")
+    assert torch.equal(outs[0][::3], torch.full((13, n), 1.0 / n).to(torch.bfloat16))
