@@ -1583,6 +1583,10 @@ pf_status plan_checked_desc(const pf_chain_desc* desc, int32_t device, int32_t v
             default: s = plan_row(p, variant); break;
         }
     }
+    // A launch holds fewer than 2^32 lanes (the device counts them in 32 bits): more are not refused by the run-time, which
+    // starts what is left of the number modulo 2^32.
+    if (s == PF_OK && (uint64_t)p->grid.x * p->block.x > 0xffffffffull)
+        s = fail(PF_ERR_UNSUPPORTED, "tensor too large for one launch (%u workgroups of %u lanes)", p->grid.x, p->block.x);
     if (s == PF_OK) {
         for (int k = 0; k < desc->n_inputs; ++k) p->in_bytes[k] = (uint64_t)numel(c.shape[k]) * dtype_size(desc->inputs[k].dtype);
         for (int o = 0; o < desc->n_outputs; ++o) {

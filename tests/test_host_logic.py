@@ -493,3 +493,13 @@ def test_plane_swaps_of_very_many_planes_stay_within_a_launch():
         s.out(s.op("permute", 0, i=[0, 2, 1]), "f16")
         info, _ = _plan_info(s)
         assert list(info.grid)[0] * list(info.block)[0] < 1 << 32, shape
+
+
+def test_launches_of_more_lanes_than_the_device_counts_are_refused():
+    # 20 million slabs of a normalisation over a strided dimension are 20 million workgroups of 256 lanes: more than 2^32, of which
+    # the rest modulo 2^32 would have run.  What fits is planned.
+    for outer, want in ((20_000_000, pf.PF_ERR_UNSUPPORTED), (10_000_000, pf.PF_OK)):
+        s = wl.ChainSpec(inputs=[("f16", (outer, 4, 8)), ("f16", (4,)), ("f16", (4,))])
+        v = s.op("layernorm", s.op("permute", 0, i=[0, 2, 1]), 1, 2, f=[1e-5])
+        s.out(s.op("permute", v, i=[0, 2, 1]), "f16")
+        assert _plan_status(s) == want, outer
