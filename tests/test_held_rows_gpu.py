@@ -130,3 +130,15 @@ def test_the_largest_fp16_scores(scale):
     outs, _, _ = check_chain(s, t, what=f"fp16 softmax of the largest values, scale {scale}")
     for row, count in ((0, n), (1, 40000), (2, len(range(5, n, 7)))):
         assert torch.equal(outs[0][row], torch.where(t[0][row] > 0, 1.0 / count, 0.0).to(torch.float16))
+
+
+@pytest.mark.parametrize("n", [33001, 33000])
+def test_a_causal_mask_that_stays_a_step(n):
+    # the value in front of the mask is an output too, so the mask is a step of its own and nothing is skipped: columns are counted
+    # from the row's first element, which lies inside the first vector
+    s = wl.ChainSpec(inputs=[("bf16", (5, n))])
+    h = s.op("scale", 0, f=[0.5])
+    s.out(s.op("softmax", s.op("causal_mask", h)), "bf16")
+    s.out(h, "bf16")
+    _, info, _ = check_chain(s, [wl.random_tensor((5, n), "bf16", 5601, scale=2.0)], what=f"masked softmax and what is in front of it, n {n}")
+    assert info.block[0] * info.vectors_per_lane * 16 >= n * 2
