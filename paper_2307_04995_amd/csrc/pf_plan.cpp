@@ -1419,14 +1419,26 @@ pf_status plan_pool(pf_plan_s* p) {
     // chunks of equal length, at most eight steps
     int64_t chunks = (best_spb + 7) / 8;
     int nv = (int)((best_spb + chunks - 1) / chunks);
-    if (!jit_possible(p->device)) {  // (the interpreted kernels exist for these)
+    const int forced_nv = env_int("PF_POOL_NV", 0), forced_chunks = env_int("PF_POOL_CHUNKS", 0);
+    auto force = [&]() {
+        if (forced_nv == 1 || forced_nv == 2 || forced_nv == 4 || forced_nv == 8) nv = forced_nv, chunks = (best_spb + nv - 1) / nv;
+        if (forced_chunks > 0) chunks = forced_chunks;
+    };
+    force();
+    p->spec_id = 0;
+    if (jit_possible(p->device)) {
+        std::string err;
+        pf::JitSpec jspec = make_jit_spec(L);
+        if (L.norm_op >= 0 && L.main_dtype != PF_F32) jspec.flags |= 32;
+        p->jit_fn = pf::jit_pool_kernel(p->device, L.main_dtype, nv, L.pool_op, ragged_c, chunks > 1, jspec, &err);
+        if (p->jit_fn) p->spec_id = pf::kSpecJit;
+        else note_interpreter_fallback(p, err);
+    }
+    if (p->spec_id == 0) {  // interpreted kernels exist for 1, 2, 4 and 8 steps
         nv = best_spb >= 8 ? 8 : best_spb > 2 ? 4 : (int)best_spb;
         chunks = (best_spb + nv - 1) / nv;
+        force();
     }
-    const int forced_nv = env_int("PF_POOL_NV", 0);
-    if (forced_nv == 1 || forced_nv == 2 || forced_nv == 4 || forced_nv == 8) nv = forced_nv, chunks = (best_spb + nv - 1) / nv;
-    const int forced_chunks = env_int("PF_POOL_CHUNKS", 0);
-    if (forced_chunks > 0) chunks = forced_chunks;
     const int64_t chunk_pos = (int64_t)nv * g.pos_per_step;
     g.chunks = (uint32_t)chunks;
     g.pos_per_block = (uint32_t)(chunks * chunk_pos);
@@ -1436,7 +1448,6 @@ pf_status plan_pool(pf_plan_s* p) {
     p->family = PF_FAMILY_POOL;
     p->variant = 0;
     p->k = nv;
-    p->spec_id = 0;
     p->block = dim3(512);
     p->grid = dim3((uint32_t)blocks);
     p->lds_bytes = 512 * vec * 4 + 4;
@@ -1466,14 +1477,6 @@ pf_status plan_pool(pf_plan_s* p) {
         for (int64_t lo = 0; lo < ch; lo += slab_ch) grps = std::max(grps, (std::min(lo + slab_ch, ch) - 1) / cpg - lo / cpg + 1);
         while (g.norm_log2 < 6u && (grps << (g.norm_log2 + 1)) <= 512) ++g.norm_log2;  // (at most: see plan_norm_pool)
         g.div_norm_cpg = make_fastdiv((uint32_t)(ch / L.groups));
-    }
-    if (jit_possible(p->device)) {
-        std::string err;
-        pf::JitSpec jspec = make_jit_spec(L);
-        if (L.norm_op >= 0 && L.main_dtype != PF_F32) jspec.flags |= 32;
-        p->jit_fn = pf::jit_pool_kernel(p->device, L.main_dtype, nv, L.pool_op, ragged_c, chunks > 1, jspec, &err);
-        if (p->jit_fn) p->spec_id = pf::kSpecJit;
-        else note_interpreter_fallback(p, err);
     }
     return PF_OK;
 }

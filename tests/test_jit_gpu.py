@@ -170,6 +170,23 @@ def test_a_plan_that_falls_back_to_the_interpreter_says_so(tmp_path):
     assert info3.spec_id == 0 and info3.interpreter_fallback == 0
 
 
+@pytest.mark.parametrize("nv,chunked", [(3, False), (5, False), (6, False), (7, False), (5, True)])
+@pytest.mark.parametrize("dtype,c", [("f16", 64), ("f32", 30)])
+def test_a_pooling_that_falls_back_runs_the_steps_the_interpreter_has(tmp_path, dtype, c, nv, chunked):
+    """Specialised poolings walk a slice in chunks of any length up to eight steps, interpreted ones in 1, 2, 4 or 8."""
+    # (64 positions to a step; a structure of its own for every case, so that no kernel is waiting in the cache)
+    steps = 2 * nv - 1 if chunked else nv
+    shape = (2, 64, steps, c)
+    spec = wl.ChainSpec(inputs=[(dtype, shape)])
+    spec.out(spec.op("tanh", spec.op("reduce_mean", spec.op("neg", spec.op("gelu_erf", spec.op("neg", 0))), i=[1, 2])), dtype)
+    ins = [wl.random_tensor(shape, dtype, 920 + nv)]
+    with env(PF_JIT_INCLUDE=str(tmp_path)):
+        _, info, _ = check_chain(spec, ins, what=f"pooling of {steps} steps, interpreter fallback")
+    assert info.spec_id == 0 and info.interpreter_fallback == 1 and info.vectors_per_lane in (1, 2, 4, 8)
+    _, info, _ = check_chain(spec, ins, what=f"pooling of {steps} steps")
+    assert info.spec_id == SPEC_JIT and info.vectors_per_lane == nv and info.workspace_bytes == 0
+
+
 def _shape_const_cases():
     cases = []
     cases.append(("C1 block variant, rows not a whole workgroup count", lambda: wl.c1_bias_res_layernorm_gelu(rows=37, n=768, dtype="f32")))
