@@ -186,7 +186,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
     float acc[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[e] = pool_identity<OP>();
-    auto work_on = [&](const u32x4& x, uint32_t step) {
+    // (the state is passed, not captured: the interpreter's accesses by operand number, made through a closure, put it into scratch
+    // memory)
+    auto work_on = [&](LaneState<DT, 1, Spec>& s, const u32x4& x, uint32_t step) {
         const uint32_t pos = (uint32_t)pos0 + pstep + step * g.pos_per_step;
         s.row[0] = pos;
         s.fraw[0][0] = x;
@@ -214,38 +216,32 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
             for (int e = 0; e < VEC; ++e) acc[e] = pool_combine<OP>(acc[e], s.acc[e]);
         }
     };
-    // Every chunk but the last: a vector's place is refilled from the next chunk as soon as it has been worked on, so memory and
-    // arithmetic overlap inside a wave.  (The last chunk has a copy of the code without the refill: the barrier behind it waits
-    // for whatever is in flight, needed or not.)
     uint32_t step = 0;
-    if constexpr (CHUNKED) {
-        for (; (step + (uint32_t)NV) * g.pos_per_step < p_count; step += (uint32_t)NV) {
-            if constexpr (Spec::kStatic) {
+    if constexpr (Spec::kStatic) {
+        // Every chunk but the last: a vector's place is refilled from the next chunk as soon as it has been worked on, so memory and
+        // arithmetic overlap inside a wave.  (The last chunk has a copy of the code without the refill: the barrier behind it waits
+        // for whatever is in flight, needed or not.)
+        if constexpr (CHUNKED) {
+            for (; (step + (uint32_t)NV) * g.pos_per_step < p_count; step += (uint32_t)NV) {
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
-                    work_on(raw[i], step + (uint32_t)i);
+                    work_on(s, raw[i], step + (uint32_t)i);
                     raw[i] = load_step(step + (uint32_t)(NV + i));
-                }
-            } else {  // (the interpreter's code once a chunk, not once a vector)
-#pragma unroll 1
-                for (int i = 0; i < NV; ++i) {
-                    work_on(raw[0], step + (uint32_t)i);
-#pragma unroll
-                    for (int k = 0; k + 1 < NV; ++k) raw[k] = raw[k + 1];
-                    raw[NV - 1] = load_step(step + (uint32_t)(NV + i));
                 }
             }
         }
-    }
-    if constexpr (Spec::kStatic) {
 #pragma unroll
-        for (int i = 0; i < NV; ++i) work_on(raw[i], step + (uint32_t)i);
+        for (int i = 0; i < NV; ++i) work_on(s, raw[i], step + (uint32_t)i);
     } else {
-#pragma unroll 1
-        for (int i = 0; i < NV; ++i) {
-            work_on(raw[0], step + (uint32_t)i);
+        // The interpreter: one copy of the steps, a chunk's loads together in front of them.  (Vectors that change places in a
+        // rolled loop wait for the newest load at every step.)
+        for (;;) {
 #pragma unroll
-            for (int k = 0; k + 1 < NV; ++k) raw[k] = raw[k + 1];
+            for (int i = 0; i < NV; ++i) work_on(s, raw[i], step + (uint32_t)i);
+            step += (uint32_t)NV;
+            if (step * g.pos_per_step >= p_count) break;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) raw[i] = load_step(step + (uint32_t)i);
         }
     }
 
