@@ -336,7 +336,8 @@ pf_status pf_chain_plan_poll_error(const pf_plan *plan, int32_t *flag);
  * ends.  A chain that needs more returns PF_ERR_NOMEM and nothing is launched.
  * Also refused, with PF_ERR_UNSUPPORTED (all of these need memory or code put on the device when a plan is made):
  * chains that run as several kernels, layout-only chains with CONCAT / SLICE, broadcast inputs with extents of 1
- * inside their shape, poolings split over several workgroups per sample.  Kernels are the library's built-in ones
+ * inside their shape, poolings split over several workgroups per sample (more than 8 * (512 / v) positions of v
+ * 16-byte channel vectors, unless there are at least four samples to every compute unit).  Kernels are the library's built-in ones
  * (nothing is compiled: a chain outside the catalogue runs on the run-time-interpreted kernels), GroupNorm runs as
  * its two-launch variant, which waits for no other workgroup.
  * desc, inputs, outputs, stream: as for pf_chain_plan and pf_chain_run; `device` is made current for the call and the

@@ -1443,6 +1443,11 @@ pf_status plan_pool(pf_plan_s* p) {
     g.chunks = (uint32_t)chunks;
     g.pos_per_block = (uint32_t)(chunks * chunk_pos);
     g.blocks_per_sample = (uint32_t)((hw + chunks * chunk_pos - 1) / (chunks * chunk_pos));
+    // A static call takes samples that one workgroup is enough for: eight steps of whole positions, or samples of any length where
+    // there are four to every compute unit.  (One workgroup on [1, 512, 512, 64] fp16 is 6 ms.)
+    if (planning_static() && (g.blocks_per_sample > 1 || (hw > 8 * (512 / cv) && n < 4 * (int64_t)n_cu)))
+        return fail(PF_ERR_UNSUPPORTED, "a pooling split over several workgroups per sample waits on the device, and a wait that gives up is reported "
+                                        "through the plan: use pf_chain_plan + pf_chain_run");
     const uint64_t blocks = (uint64_t)g.blocks_per_sample * g.slabs * n;
     if (blocks > 0x7fffffffull) return fail(PF_ERR_UNSUPPORTED, "tensor too large for the pool family");
     p->family = PF_FAMILY_POOL;
@@ -1456,9 +1461,6 @@ pf_status plan_pool(pf_plan_s* p) {
     p->args.rows = (uint64_t)(n * hw);
     if (g.blocks_per_sample > 1) {
         const uint64_t part_bytes = ((uint64_t)blocks * g.cv * vec * sizeof(float) + 255) / 256 * 256;
-        if (planning_static())
-            return fail(PF_ERR_UNSUPPORTED, "a pooling split over several workgroups per sample waits on the device, and a wait that gives up is reported "
-                                            "through the plan: use pf_chain_plan + pf_chain_run");
         if (hipSetDevice(p->device) != hipSuccess) return fail(PF_ERR_HIP, "cannot select device %d", p->device);
         pf_status ws_st = plan_workspace_alloc(p, part_bytes + 256, "workspace allocation");
         if (ws_st != PF_OK) return ws_st;

@@ -135,3 +135,22 @@ def test_pooling_of_small_ragged_samples(dtype, c, side):
         ref = run_planned(spec, ins)
     assert np.array_equal(wl.raw_bits(got[0]), wl.raw_bits(ref[0]))
     compare(got[0], oracle_run(spec, ins)[0], dtype, f"static pooling {c} channels")
+
+
+def test_poolings_of_long_samples_are_refused_unless_samples_are_many():
+    """A static call gives a sample one workgroup: eight steps of 512 vectors at most, or any length where samples fill the device."""
+    from paper_2307_04995_amd import binding as pf
+    many = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    # (128 vectors to a position, four positions to a step)
+    for n, hw, taken in ((2, 32, True), (2, 33, False), (1, 4096, False), (many - 1, 33, False), (many, 33, True)):
+        shape = (n, 1, hw, 1024)
+        spec = wl.ChainSpec(inputs=[("f16", shape)])
+        spec.out(spec.op("reduce_mean", 0, i=[1, 2]), "f16")
+        x = wl.random_tensor(shape, "f16", 9800 + hw)
+        if taken:
+            compare(run_static(spec, [x])[0], oracle_run(spec, [x])[0], "f16", f"static pooling {shape}")
+            continue
+        dev, out = x.cuda(), torch.empty((n, 1, 1, 1024), dtype=torch.float16, device="cuda")
+        st = pf.pf_chain_run_static(pf.make_desc(spec), 0, [dev.data_ptr()], [out.data_ptr()], torch.cuda.current_stream().cuda_stream)
+        assert st == pf.PF_ERR_UNSUPPORTED and "pf_chain_plan" in pf.pf_last_error(), shape
+        torch.cuda.synchronize()
