@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
     const bool active = pstep < g.pos_per_step && cvi * (uint32_t)VEC < g.channels;
     const uint32_t slab_channels = min(g.cv * (uint32_t)VEC, g.channels - slab_cv * (uint32_t)VEC);
     const uint32_t p_begin = bx * g.pos_per_block;
-    const uint32_t p_count = min(g.hw, p_begin + g.pos_per_block) - p_begin;
+    const uint32_t p_count = min(g.hw - p_begin, g.pos_per_block);  // (p_begin + pos_per_block may be past 2^32)
     const uint32_t pro_full = Spec::kStatic ? list_operand_mask<typename Spec::Pro>(K_FULL) : ~g.epi_full_mask;
     const uint32_t pro_vec = Spec::kStatic ? list_operand_mask<typename Spec::Pro>(K_VEC) : ~g.epi_vec_mask;
     const uint32_t epi_full = Spec::kStatic ? list_operand_mask<typename Spec::Epi>(K_FULL) : g.epi_full_mask;

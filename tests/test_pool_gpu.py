@@ -154,3 +154,19 @@ def test_bounded_wait_of_the_merging_workgroup_gives_up_instead_of_hanging():
     plan.close()
     # a plan with the default limit on the same shape is exact again (the flags were left in whatever state: new plan, new flags)
     check_chain(spec, [x.cpu()], what="pooling after a forced give-up")
+
+
+def test_positions_up_to_the_last_below_two_to_the_32():
+    # the end of the last slice, a whole number of steps, lies past 2^32
+    pf = _pf()
+    shape = (1, 65535, 65537, 1)
+    x = torch.ones(shape, dtype=torch.float16, device="cuda")
+    x.view(-1)[-1] = 7.0
+    for op, want in (("reduce_max", 7.0), ("reduce_mean", 1.0)):
+        plan = pf.Plan(_pool_chain("f16", shape, op), 0)
+        out = torch.zeros((1, 1, 1, 1), dtype=torch.float16, device="cuda")
+        plan.run([x], [out])
+        torch.cuda.synchronize()
+        assert out.item() == want, op
+        assert plan.poll_error() == 0
+        plan.close()
