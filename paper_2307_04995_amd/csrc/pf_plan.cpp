@@ -1390,11 +1390,22 @@ pf_status plan_pool(pf_plan_s* p) {
     // Channel slabs and slices of the positions: the pair that a model of the launch finds quickest, in steps of a workgroup
     // (with two to a unit 0.4 us for a plain pooling, 1.0 behind a normalisation).  A round of workgroups waits for its first
     // bytes (four steps) and works off its own; several slices add an exchange and its trips of eight words a lane (four
-    // each).  Slabs of whole memory lines: narrower ones, and one workgroup to a unit instead of two, were tried in the model
-    // and lose ([33, 32, 32, 24] bf16 7.6 against 6.5, [32, 56, 56, 240] fp16 14.4 against 12.0).
+    // each).  One workgroup to a unit instead of two was tried in the model and loses ([32, 56, 56, 240] fp16 14.4 against 12.0).
+    // A slab that does not begin and end with a memory line shares its first and last one with its neighbours, which run on
+    // other dies: a step then costs 14 vectors more, unless the launch leaves units idle and waits for latencies alone.  us, with
+    // one slab per 512 channels, with slabs that cost nothing, now: [103, 23, 23, 280] fp16 9.7 12.1 9.2, [6, 64, 64, 112] fp32
+    // 6.7 8.2 6.6, [109, 28, 28, 1072] fp16 + residual, SiLU 76 87 70.
+    // Positions at element alignment: a load is behind the branch for the tensor's last vector and waits for the one before, so a
+    // step is a trip to memory (three of the others), and four workgroups to a unit cover more of them than two.  us, the same
+    // three: [64, 28, 28, 331] fp16 13.0 18.4 11.6, [30, 81, 81, 251] fp16 24.5 29.2 24.0.  (Neither behind a normalisation, whose
+    // statistics every workgroup merges first, nor where there are no four steps to a unit.)
     const int64_t min_slabs = (cv * vec + 511) / 512;
-    const int64_t resident = 2 * (int64_t)n_cu;
-    int64_t best_slabs = 0, best_spb = 0, best_cost = 0;
+    const int64_t whole_pps = std::max<int64_t>(1, 512 / cv);
+    const bool serial = ragged_c && L.norm_op < 0 && n * ((hw + whole_pps - 1) / whole_pps) > 4 * (int64_t)n_cu;
+    const int64_t resident = (serial ? 4 : 2) * (int64_t)n_cu;
+    const double step_cost = serial ? 3.0 : 1.0, first_cost = serial ? 8.0 : 4.0, shared_vecs = L.norm_op >= 0 ? 0.0 : ragged_c ? 10.0 : 14.0;
+    double best_cost = 0.0;
+    int64_t best_slabs = 0, best_spb = 0;
     for (int64_t slabs = min_slabs; slabs <= std::max<int64_t>(min_slabs, cv / 8); ++slabs) {
         const int64_t scv = (cv + slabs - 1) / slabs;
         if ((cv + scv - 1) / scv != slabs) continue;
@@ -1408,7 +1419,9 @@ pf_status plan_pool(pf_plan_s* p) {
             const int64_t exchange = slices > 1 ? 1 + (slices - 1 + per_trip - 1) / per_trip : 0;
             // (two workgroups to a unit merge the statistics of a normalisation in front twice: [19, 32, 32, 160] bf16 16.2, 14.4 with one)
             const int64_t twice = L.norm_op >= 0 && units * slices > n_cu ? 3 : 0;
-            const int64_t cost = rounds * (spb + 4 + twice) + 4 * exchange;
+            const bool shares = slabs > 1 && units * slices > n_cu && ((ch * es) % 128 != 0 || scv % 8 != 0);
+            const double step = step_cost * (shares ? 1.0 + shared_vecs / (double)scv : 1.0);
+            const double cost = (double)rounds * ((double)spb * step + first_cost + (double)twice) + 4.0 * (double)exchange;
             if (best_slabs == 0 || cost < best_cost) best_cost = cost, best_slabs = slabs, best_spb = spb;
         }
     }
@@ -1416,8 +1429,10 @@ pf_status plan_pool(pf_plan_s* p) {
     g.cv = (uint32_t)((cv + best_slabs - 1) / best_slabs);
     g.div_cv = make_fastdiv(g.cv);
     g.pos_per_step = 512u / g.cv;
-    // chunks of equal length, at most eight steps
-    int64_t chunks = (best_spb + 7) / 8;
+    // chunks of equal length, at most eight steps (four where more than two workgroups share a unit's registers)
+    const int64_t best_pps = 512 / g.cv, best_blocks = n * best_slabs * ((hw + best_spb * best_pps - 1) / (best_spb * best_pps));
+    const int64_t most = serial && best_blocks > 2 * (int64_t)n_cu ? 4 : 8;
+    int64_t chunks = (best_spb + most - 1) / most;
     int nv = (int)((best_spb + chunks - 1) / chunks);
     const int forced_nv = env_int("PF_POOL_NV", 0), forced_chunks = env_int("PF_POOL_CHUNKS", 0);
     auto force = [&]() {

@@ -170,3 +170,11 @@ def test_positions_up_to_the_last_below_two_to_the_32():
         assert out.item() == want, op
         assert plan.poll_error() == 0
         plan.close()
+
+
+@pytest.mark.parametrize("shape,dtype", [((103, 23, 23, 280), "f16"), ((64, 28, 28, 331), "f16"), ((122, 20, 20, 156), "bf16")])
+def test_positions_stay_whole_where_slabs_would_share_memory_lines(shape, dtype):
+    # Slabs that do not begin and end with a memory line cost more than the merge of a few slices where the launch fills the
+    # device.  (One slice to a slab needs no workspace.)
+    _, info, _ = check_chain(_pool_chain(dtype, shape, "reduce_mean"), [wl.random_tensor(shape, dtype, 2301)], what=f"mean over the positions of {shape} {dtype}")
+    assert info.workspace_bytes > 0 and info.grid[0] % shape[0] == 0
