@@ -1445,7 +1445,14 @@ pf_status plan_pool(pf_plan_s* p) {
         std::string err;
         pf::JitSpec jspec = make_jit_spec(L);
         if (L.norm_op >= 0 && L.main_dtype != PF_F32) jspec.flags |= 32;
-        p->jit_fn = pf::jit_pool_kernel(p->device, L.main_dtype, nv, L.pool_op, ragged_c, chunks > 1, jspec, &err);
+        // (the kernel leaves room for two workgroups to a unit; where its vectors do not fit the registers then, half as many: see
+        // the kernel)
+        for (;;) {
+            p->jit_fn = pf::jit_pool_kernel(p->device, L.main_dtype, nv, L.pool_op, ragged_c, chunks > 1, jspec, &err);
+            if (!p->jit_fn || nv == 1 || nv == forced_nv || pf::jit_scratch_bytes(p->jit_fn) == 0) break;
+            nv = (nv + 1) / 2;
+            chunks = (best_spb + nv - 1) / nv;
+        }
         if (p->jit_fn) p->spec_id = pf::kSpecJit;
         else note_interpreter_fallback(p, err);
     }

@@ -178,3 +178,15 @@ def test_positions_stay_whole_where_slabs_would_share_memory_lines(shape, dtype)
     # device.  (One slice to a slab needs no workspace.)
     _, info, _ = check_chain(_pool_chain(dtype, shape, "reduce_mean"), [wl.random_tensor(shape, dtype, 2301)], what=f"mean over the positions of {shape} {dtype}")
     assert info.workspace_bytes > 0 and info.grid[0] % shape[0] == 0
+
+
+def test_a_prologue_that_does_not_fit_the_registers_walks_shorter_chunks(capfd):
+    # (registers for two workgroups to a compute unit: eight vectors of element-aligned positions, a residual and two broadcast operands spill)
+    shape, vec = (1, 512, 512, 3), (3,)
+    spec = wl.ChainSpec(inputs=[("bf16", shape), ("bf16", vec), ("bf16", vec), ("bf16", shape)])
+    v = spec.op("add", spec.op("neg", spec.op("add", spec.op("mul", 0, 1), 2)), 3)
+    spec.out(spec.op("reduce_mean", spec.op("silu", v), i=[1, 2]), "bf16")
+    with env(PF_LOG="1", PF_JIT_CACHE=None):
+        check_chain(spec, [wl.random_tensor(t, "bf16", 2401 + k) for k, (_, t) in enumerate(spec.inputs)], what="a long prologue")
+    made = [line for line in capfd.readouterr().err.splitlines() if line.startswith("[pf_jit]") and "pool_kernel<" in line]
+    assert made and " 0 bytes of scratch" in made[-1], made
