@@ -50,6 +50,16 @@ def test_shapes(shape, groups, dtype):
     assert info.n_kernels == 2 and info.n_launches == 2
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+# positions of more than 512 channels are several channel slabs: groups of 37 and 66 lie across their boundaries, whole vectors and ragged
+@pytest.mark.parametrize("shape,groups", [((1, 56, 56, 1184), 32), ((2, 9, 9, 1110), 30), ((3, 14, 5, 1122), 17)])
+def test_groups_across_channel_slabs(shape, groups, dtype):
+    s, t = _chain(shape, groups, dtype, seed=30)
+    with env(PF_NORM_POOL_SLAB="0"):
+        _, info, _ = check_chain(s, t, what=f"groupnorm > silu > mean {shape} / {groups} {dtype}")
+    assert info.n_launches == 2
+
+
 @pytest.mark.parametrize("dtype", ["f16", "f32"])
 @pytest.mark.parametrize("pre,mid,op,post", [("bias", "none", "reduce_max", "none"), ("residual", "relu", "reduce_mean", "sigmoid"), ("none", "none", "reduce_mean", "add"),
                                              ("residual", "silu", "reduce_max", "add")])
