@@ -181,14 +181,13 @@ struct PoolGeom {
     uint32_t pos_per_step;       // positions a workgroup covers per step (512 / cv)
     uint32_t pos_per_block;      // positions one workgroup owns
     uint32_t blocks_per_sample;  // ... and how many share a (sample, slab)
-    uint32_t chunks;             // chunks (of NV position steps) a workgroup walks
     uint32_t epi_full_mask, epi_vec_mask;  // operands that belong to the epilogue (read in the result's layout)
     float inv_hw;                // 1 / positions (mean)
     uint32_t* ws_partial;        // [samples][slabs][blocks_per_sample][cv * VEC] partial results as words, all-ones = not published
                                  // (more than one block per slab; the merger puts them back to all-ones)
     uint32_t* ws_error;          // set to 1 if a wait ran out
     uint32_t spin_limit;         // re-reads before a wait gives up
-    uint32_t merge_rows;         // row groups of threads the merger splits the slices over (512 / channels of a slab)
+    uint32_t merge_rows;         // row groups of threads the merger splits the slices over (512 / channels of a slab; 1 where a slab is one slice)
     uint32_t ragged;             // the channel count is not a whole number of vectors (the last vector is partial; RAGGED kernels)
     FastDiv div_cv;
     // a group normalisation in the prologue (U_GNORM): the statistics launch's partials

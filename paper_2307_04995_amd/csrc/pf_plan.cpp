@@ -1462,7 +1462,6 @@ pf_status plan_pool(pf_plan_s* p) {
         force();
     }
     const int64_t chunk_pos = (int64_t)nv * g.pos_per_step;
-    g.chunks = (uint32_t)chunks;
     g.pos_per_block = (uint32_t)(chunks * chunk_pos);
     g.blocks_per_sample = (uint32_t)((hw + chunks * chunk_pos - 1) / (chunks * chunk_pos));
     // A static call takes samples that one workgroup is enough for: eight steps of whole positions, or samples of any length where

@@ -3,10 +3,10 @@
 // epilogue on the pooled values.
 //
 // This is the reduce basic operator (paper section 6) along dimensions that are not contiguous in memory.  A
-// workgroup walks whole positions, so its HBM accesses are fully contiguous, and every lane owns one channel
-// vector, so the running reduction lives in registers and no value crosses lanes until the workgroup's slice
-// is done (one pass through LDS).  A sample's positions are spread over several workgroups: each publishes its
-// per-channel partial result; the sample's last workgroup waits for those words, merges them, runs the epilogue
+// workgroup walks a channel slab of each position of its slice (whole positions, fully contiguous, where a position is one
+// slab), and every lane owns one channel vector, so the running reduction lives in registers and no value crosses lanes
+// until the workgroup's slice is done (one pass through LDS).  A slab's positions are spread over several workgroups: each
+// publishes its per-channel partial result; the slab's last workgroup waits for those words, merges them, runs the epilogue
 // and stores -- the device-scope synchronisation of section 5.1.
 #pragma once
 #include "pf_group_kernels.hpp"
@@ -74,8 +74,10 @@ PF_DEVICE void hook_norm(const PoolNorm<VEC>& h, LaneState<DT, 1, Spec>& s) {
 // word per lane at most, and as many slices as fill the device.
 //
 // Bound: one trip to memory, the steps of the slice, then the exchange (3 us).  [32, 56, 56, 240] fp16 + SiLU, 48 MB: 12.7 us with
-// slices of one chunk, 12.1 with two chunks that refill; [24, 35, 35, 832] fp16 15.7 -> 11.6 us (two slabs of a position for one).
-// CHUNKED: false when a slice is NV steps at most.
+// slices of one chunk, 12.1 with two chunks that refill; [24, 35, 35, 832] fp16 15.7 us in one slab of 104 vectors, 11.6 in two, 12.3 in the thirteen that
+// the plan takes (whole memory lines).  CHUNKED: false when a slice is NV steps at most.
+// Registers for two workgroups to a unit: [32, 56, 56, 244] behind four steps 62 us, 81 with one (the plan takes shorter chunks where
+// vectors would not fit).
 template <int DT, int NV, class Spec, int OP, bool RAGGED = false, bool CHUNKED = true>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::kStatic ? 4 : 1))) pool_kernel(const ChainArgs a, const PoolGeom g) {
     using S = Storage<DT>;
@@ -105,7 +107,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
     const uint64_t total_elems = (uint64_t)g.samples * g.hw * g.channels;
     auto load_ragged = [&](const void* base, uint64_t elem) { return load_elems<DT>(base, elem, cnt, 0u, elem + (uint64_t)VEC <= total_elems); };
 
-    // ---- the slice in chunks of NV position steps.  No branch around a load: a lane without a position at step i reads the
+    // ---- the slice in chunks of NV position steps.  No branch around a whole vector's load (an element-aligned one has
+    // the branch of load_elems, and waits): a lane without a position at step i reads the
     // slice's first vector and leaves it out of the reduction.  (Behind guards the compiler loses count of what is in flight
     // and waits for all of the chunk's loads before the first vector is worked on.)  A vector's address is a scalar, the
     // step's, plus one offset of the lane's.
@@ -254,7 +257,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
     const uint32_t idx = t - r * row_words;
     const bool merges = r < g.merge_rows && idx < slab_channels;
     // Narrow slabs have many steps: merge_rows row groups of threads merge about eight each first (170 steps of a 24-channel slab,
-    // one after the other, were 2.5 us).  Plain loops, here and below: instructions come from memory at the start of a
+    // one after the other, were 2.5 us).  Slabs of several slices only: where a slab is one slice merge_rows is 1, and a thread per
+    // channel walks all steps.  Plain loops, here and below: instructions come from memory at the start of a
     // launch, and reads unrolled eight deep cost [32, 56, 56, 240] 2 us more than they saved.
     uint32_t rows_left = g.pos_per_step;
     if (g.pos_per_step > 16u && g.merge_rows > 2u) {
