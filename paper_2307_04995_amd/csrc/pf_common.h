@@ -187,7 +187,8 @@ struct PoolGeom {
                                  // (more than one block per slab; the merger puts them back to all-ones)
     uint32_t* ws_error;          // set to 1 if a wait ran out
     uint32_t spin_limit;         // re-reads before a wait gives up
-    uint32_t merge_rows;         // row groups of threads the merger splits the slices over (512 / channels of a slab; 1 where a slab is one slice)
+    uint32_t merge_rows;         // row groups of threads the merger splits the slices over (512 / channels of a slab)
+    uint32_t log2_lanes;         // log2 of the lanes that merge a channel's rows (at most 64 lanes, and 512 / channels of a slab)
     uint32_t ragged;             // the channel count is not a whole number of vectors (the last vector is partial; RAGGED kernels)
     FastDiv div_cv;
     // a group normalisation in the prologue (U_GNORM): the statistics launch's partials

@@ -1381,7 +1381,6 @@ pf_status plan_pool(pf_plan_s* p) {
     g.channels = (uint32_t)ch;
     g.ragged = ragged_c ? 1u : 0u;
     g.inv_hw = 1.0f / (float)hw;
-    g.merge_rows = 1;
     for (int f = 0; f < L.n_full; ++f)
         if (L.full_is_epi[f]) g.epi_full_mask |= 1u << f;
     for (int v = 0; v < L.n_vec; ++v)
@@ -1429,6 +1428,8 @@ pf_status plan_pool(pf_plan_s* p) {
     g.cv = (uint32_t)((cv + best_slabs - 1) / best_slabs);
     g.div_cv = make_fastdiv(g.cv);
     g.pos_per_step = 512u / g.cv;
+    g.merge_rows = 512u / (g.cv * (uint32_t)vec);
+    while (g.log2_lanes < 6u && (2u << g.log2_lanes) <= g.merge_rows) ++g.log2_lanes;
     // chunks of equal length, at most eight steps (four where more than two workgroups share a unit's registers)
     const int64_t best_pps = 512 / g.cv, best_blocks = n * best_slabs * ((hw + best_spb * best_pps - 1) / (best_spb * best_pps));
     const int64_t most = serial && best_blocks > 2 * (int64_t)n_cu ? 4 : 8;
@@ -1476,7 +1477,7 @@ pf_status plan_pool(pf_plan_s* p) {
     p->k = nv;
     p->block = dim3(512);
     p->grid = dim3((uint32_t)blocks);
-    p->lds_bytes = 512 * vec * 4 + 4;
+    p->lds_bytes = 512 * vec * 4 + 512 * 4;
     p->n_launches = 1;
     p->args.n_inner = (uint32_t)ch;
     p->args.rows = (uint64_t)(n * hw);
@@ -1490,7 +1491,6 @@ pf_status plan_pool(pf_plan_s* p) {
         g.ws_partial = reinterpret_cast<uint32_t*>(p->workspace);
         g.ws_error = reinterpret_cast<uint32_t*>(static_cast<char*>(p->workspace) + part_bytes);
         g.spin_limit = (uint32_t)env_int("PF_POOL_SPIN_LIMIT", 1 << 18);  // re-reads before a wait gives up (tests force it small)
-        g.merge_rows = 512u / (g.cv * (uint32_t)vec);
         p->ws_error = g.ws_error;
     }
     if (L.norm_op >= 0) {

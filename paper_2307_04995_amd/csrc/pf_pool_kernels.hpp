@@ -33,6 +33,32 @@ PF_DEVICE uint32_t pool_word(float x) {
     return w == kPoolEmpty ? 0x7fc00000u : w;
 }
 
+// log2 of the largest power of two that is at most v, and at most 64 lanes
+constexpr uint32_t floor_log2_64(uint32_t v) { return v >= 64u ? 6u : v >= 2u ? 1u + floor_log2_64(v / 2u) : 0u; }
+// One value per channel from `rows` rows of `words` channels in LDS, returned to lane t for channel t.  2^log2_lanes adjacent lanes share a
+// channel, each takes a strided subset of the rows, a shuffle tree merges them and the value is passed on through out[channel]
+// (another area); one lane to a channel (log2_lanes 0) needs no more than its own reads.  words << log2_lanes is at most the workgroup.
+// Callers put a barrier in front.  (Rows merged one LDS read after the other, then eight channels by one lane, were a chain
+// of 256 reads for 16 channels: mean over [5, 64, 64, 16] fp16 9.3 us, 5.4 so; [36, 28, 28, 64] bf16 7.2, 5.8.  A plain loop: instructions
+// come from memory at the start of a launch, and reads unrolled four deep cost [32, 56, 56, 240] + SiLU 0.4 us of 13.2.)
+template <int OP>
+PF_DEVICE float pool_reduce_rows(const float* rows_lds, float* out, uint32_t rows, uint32_t words, uint32_t log2_lanes) {
+    const uint32_t ch = threadIdx.x >> log2_lanes, lanes = 1u << log2_lanes, r = threadIdx.x & (lanes - 1u);
+    float m = pool_identity<OP>();
+    if (ch < words) {
+#pragma unroll 1
+        for (uint32_t q = r; q < rows; q += lanes) m = pool_combine<OP>(m, rows_lds[q * words + ch]);
+    }
+    if (log2_lanes != 0u) {
+#pragma unroll 1
+        for (uint32_t x = 1; x < lanes; x <<= 1) m = pool_combine<OP>(m, __shfl_xor(m, (int)x, 64));
+        if (ch < words && r == 0u) out[ch] = m;
+        __syncthreads();
+        if (threadIdx.x < words) m = out[threadIdx.x];
+    }
+    return m;
+}
+
 // A group normalisation in front of the pooling (U_GNORM in the prologue).  Its statistics come from an earlier launch (the
 // group family's statistics kernel); a workgroup lies in one sample and a lane owns its channels, so mean and scale of
 // the lane's channels are merged once and every element costs a subtraction and a multiply-add.  The normalised
@@ -83,6 +109,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
     using S = Storage<DT>;
     constexpr int VEC = S::VEC;
     __shared__ float lds[512 * VEC];
+    __shared__ float lds_ch[512];  // a value per channel of the slab
     const uint32_t t = threadIdx.x;
     const uint32_t pstep = fast_div(t, g.div_cv);
     const uint32_t unit = blockIdx.x / g.blocks_per_sample;  // (sample, slab)
@@ -248,35 +275,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
         }
     }
 
-    // ---- the position steps of the workgroup, through LDS: a thread per channel
+    // ---- the position steps of the workgroup, through LDS: a value per channel of the slab
 #pragma unroll
     for (int e = 0; e < VEC; ++e) lds[t * VEC + e] = acc[e];
     __syncthreads();
     const uint32_t row_words = g.cv * (uint32_t)VEC;
-    const uint32_t r = t / row_words;
-    const uint32_t idx = t - r * row_words;
-    const bool merges = r < g.merge_rows && idx < slab_channels;
-    // Narrow slabs have many steps: merge_rows row groups of threads merge about eight each first (170 steps of a 24-channel slab,
-    // one after the other, were 2.5 us).  Slabs of several slices only: where a slab is one slice merge_rows is 1, and a thread per
-    // channel walks all steps.  Plain loops, here and below: instructions come from memory at the start of a
-    // launch, and reads unrolled eight deep cost [32, 56, 56, 240] 2 us more than they saved.
-    uint32_t rows_left = g.pos_per_step;
-    if (g.pos_per_step > 16u && g.merge_rows > 2u) {
-        float m = pool_identity<OP>();
-        if (merges) {
-#pragma unroll 1
-            for (uint32_t q = r; q < g.pos_per_step; q += g.merge_rows) m = pool_combine<OP>(m, lds[q * row_words + idx]);
-        }
-        __syncthreads();
-        if (merges) lds[t] = m;
-        __syncthreads();
-        rows_left = g.merge_rows;
-    }
-    auto slice_value = [&](uint32_t ch) {
-        float m = lds[ch];
-        for (uint32_t q = 1; q < rows_left; ++q) m = pool_combine<OP>(m, lds[q * row_words + ch]);
-        return m;
-    };
+    float mine = pool_reduce_rows<OP>(lds, lds_ch, g.pos_per_step, row_words, g.log2_lanes);  // (channel t of the slab)
     // A slab split over several workgroups: every slice but the last publishes its per-channel partial result as
     // self-describing words (kPoolEmpty = not written in this launch; consecutive lanes, consecutive words); the slab's
     // LAST slice (dispatched after the others) reads them all, re-reading the ones still empty, puts them back to empty for
@@ -284,64 +288,68 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
     // for the stores' acknowledgement in between.
     if (bx + 1u != g.blocks_per_sample) {
         uint32_t* part = g.ws_partial + (uint64_t)blockIdx.x * row_words;
-        if (t < slab_channels) __hip_atomic_store(part + t, pool_word(slice_value(t)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t < slab_channels) __hip_atomic_store(part + t, pool_word(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
     // The merger (a slab that is one slice merges nothing): merge_rows row groups of threads, each a channel per lane
     // (consecutive lanes, consecutive words); row group r takes the slices r, r + merge_rows, ..., eight of them in flight
     // at a time.  Every wait is bounded: after spin_limit re-reads the error word is set and the missing slice is left out.
     const uint32_t others = g.blocks_per_sample - 1u;
-    uint32_t* base = g.ws_partial + (uint64_t)unit * g.blocks_per_sample * row_words;
-    uint32_t spins = 0;
-    float merged = pool_identity<OP>();
-    if (merges) {
-        if (r == 0u) merged = slice_value(idx);  // the merger's own slice
-        for (uint32_t b0 = r; b0 < others; b0 += 8u * g.merge_rows) {
-            uint32_t w[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
-                w[u] = b < others ? __hip_atomic_load(base + (uint64_t)b * row_words + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                  : pool_word(pool_identity<OP>());
-            }
-            // words still empty are re-read together (one trip to memory per round, not one per word)
-            for (;;) {
-                bool waiting = false;
-#pragma unroll
-                for (int u = 0; u < 8; ++u) waiting = waiting || w[u] == kPoolEmpty;
-                if (!waiting) break;
-                if (++spins > g.spin_limit) {
-                    __hip_atomic_store(g.ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(8);
+    if (others != 0u) {
+        const uint32_t r = t / row_words, idx = t - r * row_words;
+        uint32_t* base = g.ws_partial + (uint64_t)unit * g.blocks_per_sample * row_words;
+        uint32_t spins = 0;
+        float merged = pool_identity<OP>();
+        if (r < g.merge_rows && idx < slab_channels) {
+            if (r == 0u) merged = mine;  // the merger's own slice
+            for (uint32_t b0 = r; b0 < others; b0 += 8u * g.merge_rows) {
+                uint32_t w[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
-                    if (w[u] == kPoolEmpty) w[u] = __hip_atomic_load(base + (uint64_t)b * row_words + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    w[u] = b < others ? __hip_atomic_load(base + (uint64_t)b * row_words + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                      : pool_word(pool_identity<OP>());
+                }
+                // words still empty are re-read together (one trip to memory per round, not one per word)
+                for (;;) {
+                    bool waiting = false;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) waiting = waiting || w[u] == kPoolEmpty;
+                    if (!waiting) break;
+                    if (++spins > g.spin_limit) {
+                        __hip_atomic_store(g.ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(8);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
+                        if (w[u] == kPoolEmpty) w[u] = __hip_atomic_load(base + (uint64_t)b * row_words + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
+                    if (b >= others || w[u] == kPoolEmpty) continue;
+                    __hip_atomic_store(base + (uint64_t)b * row_words + idx, kPoolEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    merged = pool_combine<OP>(merged, __builtin_bit_cast(float, w[u]));
                 }
             }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
-                if (b >= others || w[u] == kPoolEmpty) continue;
-                __hip_atomic_store(base + (uint64_t)b * row_words + idx, kPoolEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                merged = pool_combine<OP>(merged, __builtin_bit_cast(float, w[u]));
-            }
         }
+        __syncthreads();  // (the positions' rows have been read)
+        if (r < g.merge_rows) lds[t] = merged;
+        __syncthreads();
+        mine = pool_reduce_rows<OP>(lds, lds_ch, g.merge_rows, row_words, g.log2_lanes);
     }
-    __syncthreads();  // (everyone has read its own slice's values)
-    if (merges) lds[t] = merged;
-    __syncthreads();
+    if (g.log2_lanes == 0u) {
+        if (t < row_words) lds_ch[t] = mine;
+        __syncthreads();
+    }
     // lane t: channel vector t of the slab's result
     const bool owner = t < g.cv && (slab_cv + t) * (uint32_t)VEC < g.channels;
     if (!owner) return;
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-        float m = lds[t * VEC + e];
-        for (uint32_t q = 1; q < g.merge_rows; ++q) m = pool_combine<OP>(m, lds[q * row_words + t * VEC + e]);
-        acc[e] = m;
-    }
+    for (int e = 0; e < VEC; ++e) acc[e] = lds_ch[t * VEC + e];
 
     // ---- epilogue on the pooled values of (sample, channel vector slab_cv + t), addressed in the result's layout [n, c]
     if (OP == POOL_MEAN) {
@@ -379,7 +387,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
 // M2) triples, one per group the vector touches.
 //
 // Bound: the arithmetic behind the normalisation, with few waves to cover its waits.  [32, 64, 64, 320] fp16, GroupNorm(32) + SiLU +
-// mean, 84 MB: 48.9 us in two launches, 44.6 in one.
+// mean, 84 MB: 48.9 us in two launches, 44.6 in one, 41.5 with a channel's rows merged by lanes (pool_reduce_rows).
 template <int DT, int NV, int CVS, class Spec, int OP>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 16 ? 2 : 4))) norm_pool_slab_kernel(const ChainArgs a, const SlabGeom g) {
     using S = Storage<DT>;
@@ -537,28 +545,20 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
         for (int e = 0; e < VEC; ++e) asm volatile("" : "+v"(acc[e]));
     }
 
-    // ---- the position steps, through LDS: row groups of threads, each a channel per lane, then a thread per vector
-    constexpr uint32_t row_words = (uint32_t)(CVS * VEC), rows = 512u / row_words;
+    // ---- the position steps, through LDS (the statistics' area has been read)
+    constexpr uint32_t row_words = (uint32_t)(CVS * VEC);
+    constexpr uint32_t log2_lanes = floor_log2_64(512u / row_words);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) lds[t * VEC + e] = acc[e];
     __syncthreads();
-    const uint32_t r = t / row_words, idx = t - r * row_words;
-    float m = pool_identity<OP>();
-    if (r < rows) {
-#pragma unroll 1
-        for (uint32_t q = r; q < PPS; q += rows) m = pool_combine<OP>(m, lds[q * row_words + idx]);
+    const float mine = pool_reduce_rows<OP>(lds, lds_stat, PPS, row_words, log2_lanes);
+    if (log2_lanes == 0u) {
+        if (t < row_words) lds_stat[t] = mine;
+        __syncthreads();
     }
-    __syncthreads();
-    if (r < rows) lds[t] = m;
-    __syncthreads();
     if (t >= (uint32_t)CVS || !active) return;
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-        m = lds[t * VEC + e];
-#pragma unroll 1
-        for (uint32_t q = 1; q < min(rows, PPS); ++q) m = pool_combine<OP>(m, lds[q * row_words + t * VEC + e]);
-        s.acc[e] = OP == POOL_MEAN ? m * g.inv_hw : m;
-    }
+    for (int e = 0; e < VEC; ++e) s.acc[e] = OP == POOL_MEAN ? lds_stat[t * VEC + e] * g.inv_hw : lds_stat[t * VEC + e];
 
     // ---- epilogue, addressed in the result's layout [n, c]
     constexpr uint32_t epi_full = list_operand_mask<typename Spec::Epi>(K_FULL), epi_vec = list_operand_mask<typename Spec::Epi>(K_VEC);
