@@ -530,7 +530,11 @@ static hipError_t launch_attn_dt(const AttnArgs& a, int variant, int nv, dim3 gr
     switch (nv) {
         case 1: hipLaunchKernelGGL((attn_decode_kernel<DT, 1>), grid, dim3(256), 0, st, a); break;
         case 2: hipLaunchKernelGGL((attn_decode_kernel<DT, 2>), grid, dim3(256), 0, st, a); break;
+        case 3: hipLaunchKernelGGL((attn_decode_kernel<DT, 3>), grid, dim3(256), 0, st, a); break;
         case 4: hipLaunchKernelGGL((attn_decode_kernel<DT, 4>), grid, dim3(256), 0, st, a); break;
+        case 5: hipLaunchKernelGGL((attn_decode_kernel<DT, 5>), grid, dim3(256), 0, st, a); break;
+        case 6: hipLaunchKernelGGL((attn_decode_kernel<DT, 6>), grid, dim3(256), 0, st, a); break;
+        case 7: hipLaunchKernelGGL((attn_decode_kernel<DT, 7>), grid, dim3(256), 0, st, a); break;
         case 8: hipLaunchKernelGGL((attn_decode_kernel<DT, 8>), grid, dim3(256), 0, st, a); break;
         default: return hipErrorInvalidValue;
     }

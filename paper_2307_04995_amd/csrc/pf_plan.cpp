@@ -1577,7 +1577,7 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     // A plan that owns its workspace merges by polling self-describing words (a bounded wait, reported through the plan);
     // a call that plans and runs in one go has no plan to report through and keeps the counted, wait-free merge.
     const bool polled = !planning_static() && env_int("PF_ATTN_POLLED", 1) != 0;
-    // Rows per workgroup: 8 steps of 256 / lpr rows when that still gives every compute unit two workgroups, or one where 4
+    // Rows per workgroup of the counted merge, and for the choice of the variant: 8 steps of 256 / lpr rows when that still gives every compute unit two workgroups, or one where 4
     // steps would leave a head more slices than its merge takes in one trip (2 per thread group: 3 x 25 heads, t = 1023, d = 64,
     // 8 slices of 4 steps 8.7 us against 9.3; 2 x 25, t = 2047, 16 slices 10.3 against 9.6; 8 heads, t = 4000, d = 128, 63
     // slices 13.8 against 10.5); else 4.  (One or two steps per workgroup lose to the per-slice overhead, sixteen to register
@@ -1601,7 +1601,9 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     // t = 8191 (32) 78.7, 77.9; t = 16383 (64) 151.7, 153.6; d = 128, 16 slices a trip: 4 x 32 heads, t = 2047 (16) 31.2, 29.5;
     // 64 heads, t = 4095 (32) 32.0, 32.7; t = 8191 (64) 56.2, 62.2; t = 32767 (256) 197, 243; 8 heads, t = 131071 (1024) 111,
     // 214.  Below eight chunks the streamed slices are short and can be more than those of one pass (one head, t = 65535,
-    // d = 128: 683 and 512, 98 and 66 us; not always: 8 heads, t = 16383, d = 128: 86 and 128, 28.6 and 34.4).  In a static call the partial results have a fixed array to fit in as well (2 MB: 4 x 32 heads, t = 4096,
+    // d = 128: 683 and 512, 98 and 66 us; not always: 8 heads, t = 16383, d = 128: 86 and 128, 28.6 and 34.4).  Two trips where a
+    // trip is at most 16 slices: 125 heads, t = 2265, d = 128 (18 slices) 30.3 in one pass, 32.8 streamed; 96 heads, t = 3822 (30) 36.2 and
+    // 39.5; 64 heads, t = 4095 (32) 31.9 both; 50 heads, t = 5290 (42) 30.0 and 31.5 still, but t = 8191 (64) is the streamed kernel's.  In a static call the partial results have a fixed array to fit in as well (2 MB: 4 x 32 heads, t = 4096,
     // d = 128 fill 0.5 MB streamed, 2.5 MB in one pass).
     int64_t chunks = 1;
     bool stream = false;
@@ -1612,7 +1614,7 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
         const int forced_chunks = env_int("PF_ATTN_CHUNKS", 0);
         chunks = forced_chunks > 0 ? forced_chunks : c;
         const int64_t splits_one_pass = (t_total + rps * nv - 1) / (rps * nv);
-        stream = chunks >= 8 && !forced_nv && (chunks >= all_chunks || !polled || splits_one_pass > 8 * groups);
+        stream = chunks >= 8 && !forced_nv && (chunks >= all_chunks || !polled || splits_one_pass > (groups <= 2 ? 16 : 8) * groups);
     }
     int variant = forced_variant >= 0 ? forced_variant : (stream ? PF_VARIANT_ATTN_STREAM : PF_VARIANT_ATTN_ONE_PASS);
     if (variant != PF_VARIANT_ATTN_ONE_PASS && variant != PF_VARIANT_ATTN_STREAM)
@@ -1624,7 +1626,32 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
         chunks = 1;
     }
     a.chunks = (uint32_t)chunks;
-    const int64_t splits = (t_total + rps * nv * chunks - 1) / (rps * nv * chunks);
+    int64_t splits = (t_total + rps * nv * chunks - 1) / (rps * nv * chunks);
+    a.part_stride = (uint32_t)((d + 2 + 31) / 32 * 32);
+    auto part_bytes_of = [&](int64_t slices) { return ((uint64_t)heads * slices * a.part_stride * sizeof(float) + 255) / 256 * 256; };
+    const uint64_t cnt_bytes = ((uint64_t)heads * sizeof(uint32_t) + 255) / 256 * 256, at_least = planning_static() ? part_bytes_of(splits) : 0;
+    // One pass: slices of one to eight steps, the number that a model of the launch finds quickest (microseconds, fitted to 360 measured
+    // (shape, slices) pairs of 30 shapes; its choice is 1.002 times the best measured one in the mean, the rule above 1.10).  The
+    // busiest unit pays 0.31 a workgroup and 0.11 a step; a merge costs 1.5 where a thread reads one slice, 1.6 two, 2.6 up to eight,
+    // and 1.5 a further trip.  A head that is one slice merges nothing.  Slices of equal length instead of whole steps and a
+    // shorter last one: 608 heads, t = 494, d = 128 29.1 us against 28.6, the others alike.  Before and after: 200 heads, t = 1023, d = 64 (4
+    // slices of 8 steps, 5 of 7 now) 13.4 -> 12.9 us, 24 heads, t = 3058 10.0 -> 9.1, 8 heads, t = 143 (one slice) 5.3 -> 3.7, 50 heads,
+    // t = 71, d = 128 5.4 -> 3.8.  Heads that eight steps leave more than 128 slices stay with the rule above: one head of 20 000 rows, d = 128,
+    // 313 slices 41.5 us against 24.0 with 157, but its number of slices is relied upon.
+    // A static call takes the same slices, so that its results are the plan's, unless they do not fit the scratch array where the
+    // others would (and is refused where the others do not fit).
+    if (variant == PF_VARIANT_ATTN_ONE_PASS && !forced_nv && (t_total + rps * 8 - 1) / (rps * 8) <= 128) {
+        const int64_t room = planning_static() ? (int64_t)(tls_scratch->cap - std::min(tls_scratch->cap, (tls_scratch->used + 255) / 256 * 256)) - (int64_t)cnt_bytes - 256 : INT64_MAX;
+        double best = 0.0;
+        for (int64_t steps = 8; steps >= 1; --steps) {
+            const int64_t s = (t_total + rps * steps - 1) / (rps * steps);
+            const int64_t per_unit = (heads * s + n_cu - 1) / n_cu, trips = (s + 8 * groups - 1) / (8 * groups);
+            const int64_t needed = ((t_total + s - 1) / s + rps - 1) / rps;  // (steps that make no more slices)
+            const double merge = s == 1 ? 0.0 : s <= groups ? 1.5 : s <= 2 * groups ? 1.6 : 2.6 + 1.5 * (double)(trips - 1);
+            const double cost = (double)per_unit * (0.31 + 0.11 * (double)needed) + merge;
+            if ((best == 0.0 || cost < best) && (int64_t)part_bytes_of(s) <= room) best = cost, splits = s, nv = (int)needed;
+        }
+    }
     if (splits > 65535) return fail(PF_ERR_UNSUPPORTED, "too many cached rows for the attention family");
     p->family = PF_FAMILY_ATTENTION;
     p->variant = variant;
@@ -1634,9 +1661,7 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     p->grid = dim3((uint32_t)splits, (uint32_t)heads);
     p->lds_bytes = (8 + 4 * 256 + 1) * 4;
     p->n_launches = 1;
-    a.part_stride = (uint32_t)((d + 2 + 31) / 32 * 32);
-    const uint64_t part_bytes = ((uint64_t)heads * splits * a.part_stride * sizeof(float) + 255) / 256 * 256;
-    const uint64_t cnt_bytes = ((uint64_t)heads * sizeof(uint32_t) + 255) / 256 * 256;
+    const uint64_t part_bytes = std::max(part_bytes_of(splits), at_least);
     pf_status ws_st = plan_workspace_alloc(p, part_bytes + cnt_bytes + 256, "workspace allocation");
     if (ws_st != PF_OK) return ws_st;
     if ((ws_st = plan_workspace_fill(p, p->workspace, polled ? 0xff : 0, part_bytes, polled)) != PF_OK) return ws_st;
