@@ -258,10 +258,17 @@ pf_status pf_chain_run(const pf_plan* plan, const void* const* inputs, void* con
         case PF_FAMILY_GROUP: {
             if (plan->variant == PF_VARIANT_GROUP_RESIDENT) {
                 // the fused kernel alternates between two sets of exchange slots by launch number, which is a
-                // kernel argument: a recorded launch would replay the same number
+                // kernel argument: a recorded launch would replay the same number (slabs keep it on the device or need none,
+                // but a caller cannot tell which kernel the variant is: it is refused as one)
                 hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
                 if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
                     return fail(PF_ERR_UNSUPPORTED, "the one-launch GroupNorm variant cannot be recorded into a graph; plan the two-launch variant for that");
+            }
+            if (plan->group_slab) {
+                pf::GroupSlabGeom g = plan->gslab;
+                void* params[] = {&a, &g};
+                e = pf::jit_launch(plan->jit_fn, plan->grid, plan->block, plan->dyn_lds, params, st);
+                break;
             }
             pf::GroupGeom g = plan->group;
             g.epoch = plan->epoch + 1;  // (counted below, once the launch has been accepted: a failed launch must not flip the slots' parity)
@@ -335,7 +342,7 @@ pf_status pf_chain_plan_poll_error(const pf_plan* plan, int32_t* flag) {
         }
         return PF_OK;
     }
-    uint32_t* err = plan->family == PF_FAMILY_GROUP ? plan->group.ws_error : plan->ws_error;
+    uint32_t* err = plan->family == PF_FAMILY_GROUP && !plan->group_slab ? plan->group.ws_error : plan->ws_error;
     if (!err) return PF_OK;
     uint32_t word = 0;
     if (hipMemcpy(&word, err, sizeof(word), hipMemcpyDeviceToHost) != hipSuccess)
@@ -345,6 +352,7 @@ pf_status pf_chain_plan_poll_error(const pf_plan* plan, int32_t* flag) {
         // does not expect (slots of the wrong parity still filled, partial results of late slices still published).  Put the
         // workspace back the way the planner left it.  (The caller has synchronised: nothing of this plan is running.)
         bool ok = hipMemset(err, 0, sizeof(word)) == hipSuccess;
+        if (plan->group_slab) ok = ok && hipMemset(plan->gslab.ws_gather, 0xff, (size_t)2 * plan->gslab.gather_words * sizeof(uint64_t)) == hipSuccess;
         if (plan->family == PF_FAMILY_GROUP && plan->group.ws_gather) {
             const pf::GroupGeom& g = plan->group;
             ok = ok && hipMemset(g.ws_gather, 0xff, (size_t)2 * g.samples * g.groups * g.blocks_per_sample * sizeof(uint64_t)) == hipSuccess;

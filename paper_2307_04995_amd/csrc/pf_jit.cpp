@@ -367,6 +367,12 @@ hipFunction_t jit_group_kernel(int device, int dtype, int nv, int phase, int gen
     return compile(device, "#include \"pf_group_kernels.hpp\"\n", name.str(), err);
 }
 
+hipFunction_t jit_group_slab_kernel(int device, int dtype, int nv, int slab_vecs, bool sliced, bool packed, const JitSpec& spec, std::string* err) {
+    std::ostringstream name;
+    name << "pf::group_slab_kernel<" << dtype << ", " << nv << ", " << slab_vecs << ", " << spec_text(spec) << (sliced ? ", true" : ", false") << (packed ? ", true>" : ", false>");
+    return compile(device, "#include \"pf_slab_kernels.hpp\"\n", name.str(), err);
+}
+
 // The one-launch group kernel with the geometry of one launch as constants.
 hipFunction_t jit_group_kernel_const(int device, int dtype, int nv, int general_parts, const JitSpec& spec, const GroupGeom& g, uint32_t tiles,
                                      uint32_t grid, uint32_t threads, std::string* err) {

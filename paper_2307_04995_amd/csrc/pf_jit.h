@@ -51,6 +51,8 @@ hipFunction_t jit_perm_rows_const(int device, int dtype, int k, const JitSpec& s
                                   const uint32_t* vec_period, std::string* err);
 // group family: phase 0 fused, 1 statistics, 2 normalisation
 hipFunction_t jit_group_kernel(int device, int dtype, int nv, int phase, int general_parts, const JitSpec& spec, std::string* err);
+// GroupNorm over slabs of whole groups: nv vectors per lane, slab_vecs vectors of a position
+hipFunction_t jit_group_slab_kernel(int device, int dtype, int nv, int slab_vecs, bool sliced, bool packed, const JitSpec& spec, std::string* err);
 // stencil family (depthwise 3 x 3 convolution)
 // the one-launch variant (phase 0) with the launch's geometry as compile-time constants
 hipFunction_t jit_group_kernel_const(int device, int dtype, int nv, int general_parts, const JitSpec& spec, const GroupGeom& g, uint32_t tiles,

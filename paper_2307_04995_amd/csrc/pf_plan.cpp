@@ -788,6 +788,114 @@ pf_status plan_perm(pf_plan_s* p, int forced_variant) {
 }
 
 // ---- group family
+// GroupNorm over slabs of whole groups (group_slab_kernel).  false where the kernel does not take the chain or is not the quicker one.
+// tiles, tiles_per_sample, rounds: what the one-launch kernel of whole positions would be planned with (rounds: of co-resident tiles).
+//
+// Two ranges (44 shapes, 550 pairs of slab and slices measured; geometric mean over the shapes 0.86 of the kernel of whole positions):
+//  - one slice to a slab, six steps at most and one workgroup to a unit at most: nothing is exchanged, which is half of what a small call
+//    costs.  us, fp16 or bf16: [31, 10, 10, 96] 9.7 -> 5.9, [11, 14, 14, 640] 8.4 -> 5.9, [21, 14, 14, 352] 8.9 -> 6.7; fp32: [2, 7, 7, 1216]
+//    7.4 -> 5.1, [6, 32, 32, 128] 9.5 -> 7.6.  With more steps the strided reads cost more than the exchange: [2, 32, 32, 224] bf16, 15 steps,
+//    9.7 against 8.8, [20, 28, 28, 512] bf16, 13 steps, 12.0 against 10.1.
+//  - slices where the other kernel would go several rounds, or a sample is so many tiles that a lane reads its words in more than three
+//    trips (48; 42 in fp32; 16-bit tensors of more tiles than units excepted: [6, 64, 64, 416] bf16 19.6, 20.9 in slabs).  us, fp32:
+//    [7, 56, 56, 768] 79.9 -> 36.9, [1, 56, 56, 416] 18.0 -> 10.4, [4, 64, 64, 320] 23.8 -> 18.8, [13, 28, 28, 960] 32.4 -> 27.4; 16 bits:
+//    [21, 64, 64, 352] 44.1 -> 33.0, [4, 64, 64, 224] 13.6 -> 12.4.
+static bool plan_group_slab(pf_plan_s* p, int n_cu, int64_t n, int64_t hw, int64_t ch, int64_t tiles, int64_t tiles_per_sample, int64_t rounds) {
+    const Lowered& L = p->low;
+    const int mode = env_int("PF_GROUP_SLAB", 1);  // 0 never, 2 wherever it is possible, quicker or not
+    if (!jit_possible(p->device) || mode == 0 || env_int("PF_GROUP_GENERAL", 0) != 0 || env_int("PF_GROUP_NV", 0) != 0) return false;
+    const int64_t groups = L.groups, cpg = ch / groups;
+    const int es = dtype_size(L.main_dtype), vec = 16 / es;
+    if ((ch * es) % 16 != 0 || hw * ch * es > 0x7fffffffLL) return false;
+    const int forced_d = env_int("PF_SLAB_GROUPS", 0), forced_slices = env_int("PF_SLAB_SLICES", 0);
+    const bool forced = mode == 2;
+    const bool sliced_pays = rounds > 1 || (es == 4 ? tiles_per_sample > 42 : tiles_per_sample > 48 && tiles <= n_cu);
+    struct Pick {
+        double cost;
+        int64_t d, nv, slices;
+    };
+    std::vector<Pick> picks;
+    for (int64_t d = 1; d <= groups && d <= 512; ++d) {
+        if (groups % d != 0 || (forced_d && d != forced_d) || (d * cpg * es) % 16 != 0) continue;
+        const int64_t slabs = n * (groups / d), cvs = d * cpg / vec;
+        if (cvs > 512) continue;
+        const int64_t pps = 512 / cvs, width = cvs * 16;
+        const bool lines = (width % 128 == 0 && (ch * es) % 128 == 0) || d == groups;
+        const double waste = std::min(3.0, (double)(((width + 127) / 128 + (lines ? 0 : 1)) * 128) / (double)width - 1.0);  // (of the memory lines a position's share touches)
+        for (int64_t slices = 1; slices <= std::min<int64_t>(64, hw); ++slices) {
+            if (forced_slices && slices != forced_slices) continue;
+            const int64_t longest = (hw + slices - 1) / slices, nv = (longest + pps - 1) / pps, blocks = slabs * slices;
+            if (nv > 44 || (nv - 1) * pps > hw / slices || blocks > 0x7fffff) continue;  // (every step of every slice but the last is whole)
+            const bool small = slices == 1 && nv <= 6, large = sliced_pays && width >= 64;
+            if ((blocks > n_cu || !(small || large)) && !forced) continue;
+            // microseconds beside what the bytes cost, fitted to the pairs of at most one workgroup to a unit
+            const double cost = (double)nv * ((es == 4 ? 0.25 : 0.165) + 0.044 * waste) + 0.11 * std::log2((double)pps) + (slices > 1 ? 1.97 + 0.0515 * (double)slices : 0.0);
+            picks.push_back(Pick{cost, d, nv, slices});
+        }
+    }
+    std::sort(picks.begin(), picks.end(), [](const Pick& x, const Pick& y) { return x.cost < y.cost; });
+    hipFunction_t fn = nullptr;
+    std::string err;
+    // (a kernel whose vectors do not fit the registers is passed over, three at most: each is compiled first)
+    size_t at = 0;
+    for (; at < picks.size() && at < 3; ++at) {
+        fn = pf::jit_group_slab_kernel(p->device, L.main_dtype, (int)picks[at].nv, (int)(picks[at].d * cpg / vec), picks[at].slices > 1, es == 2 && cpg % 2 == 0, make_jit_spec(L), &err);
+        if (fn && pf::jit_scratch_bytes(fn) == 0) break;
+        fn = nullptr;
+    }
+    if (!fn) return false;
+    const int64_t best_d = picks[at].d, best_nv = picks[at].nv, best_slices = picks[at].slices;
+    pf::GroupSlabGeom& g = p->gslab;
+    memset(&g, 0, sizeof(g));
+    g.hw = (uint32_t)hw;
+    g.channels = (uint32_t)ch;
+    g.groups = (uint32_t)groups;
+    g.cpg = (uint32_t)cpg;
+    g.div_cpg = make_fastdiv(g.cpg);
+    g.slab_groups = (uint32_t)best_d;
+    g.slabs_per_sample = (uint32_t)(groups / best_d);
+    g.slices = (uint32_t)best_slices;
+    g.slice_len = (uint32_t)(hw / best_slices);
+    g.slice_rest = (uint32_t)(hw % best_slices);
+    g.blocks = (uint32_t)(n * g.slabs_per_sample * best_slices);
+    g.blocks_per_die = (g.blocks + 7u) / 8u;
+    g.parts = 1;
+    for (int64_t v = 0; v < ch / vec; ++v) g.parts = std::max<uint32_t>(g.parts, (uint32_t)((v * vec + vec - 1) / cpg - v * vec / cpg + 1));
+    while (g.log2_lanes < 6u && (best_d << (g.log2_lanes + 1)) <= 512) ++g.log2_lanes;
+    const uint32_t dyn_lds = 512u * 3u * g.parts * 4u, grid = g.blocks_per_die * 8u;
+    if (best_slices > 1) {
+        // every wait is for workgroups of the same launch: all of them have to be resident
+        if ((int64_t)pf::jit_blocks_per_cu(fn, 512, dyn_lds) * n_cu < (int64_t)grid) return false;
+        g.spin_limit = (uint32_t)env_int("PF_GROUP_SPIN_LIMIT", 1 << 22);
+        g.gather_words = (uint32_t)(n * groups * best_slices);
+        const uint64_t gather_bytes = ((uint64_t)2 * g.gather_words * sizeof(uint64_t) + 255) / 256 * 256, epochs = ((uint64_t)g.blocks * sizeof(uint32_t) + 255) / 256 * 256;
+        if (hipSetDevice(p->device) != hipSuccess || plan_workspace_alloc(p, gather_bytes + epochs + 256, "workspace allocation") != PF_OK) return false;
+        char* ws = static_cast<char*>(p->workspace);
+        if (plan_workspace_fill(p, ws, 0xff, gather_bytes, true) != PF_OK || plan_workspace_fill(p, ws + gather_bytes, 0, epochs + 256, true) != PF_OK) {
+            (void)hipFree(p->workspace);
+            p->workspace = nullptr;
+            return false;
+        }
+        g.ws_gather = reinterpret_cast<uint64_t*>(ws);
+        g.ws_epoch = reinterpret_cast<uint32_t*>(ws + gather_bytes);
+        g.ws_error = reinterpret_cast<uint32_t*>(ws + gather_bytes + epochs);
+        p->ws_error = g.ws_error;
+    }
+    p->jit_fn = fn;
+    p->group_slab = true;
+    p->variant = PF_VARIANT_GROUP_RESIDENT;
+    p->spec_id = pf::kSpecJit;
+    p->k = (int)best_nv;
+    p->grid = dim3(grid);
+    p->block = dim3(512);
+    p->dyn_lds = dyn_lds;
+    p->lds_bytes = dyn_lds + 2 * 512 * 4;
+    p->n_launches = 1;
+    p->args.n_inner = (uint32_t)ch;
+    p->args.rows = (uint64_t)(n * hw);
+    return true;
+}
+
 pf_status plan_group(pf_plan_s* p, int forced_variant) {
     // on the static scratch array: the two-launch variant, which waits for nobody and so has no failed wait to report
     if (planning_static() || p->stats_only) forced_variant = PF_VARIANT_GROUP_TWO_PASS;
@@ -847,15 +955,15 @@ pf_status plan_group(pf_plan_s* p, int forced_variant) {
         return fail(PF_ERR_HIP, "cannot query device %d (the group family needs the device at plan time)", p->device);
     const int n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
 
+    g.vec_per_channel = 1;
+    for (int v = 0; v < L.n_vec; ++v)
+        if (p->args.vec[v].numel > (uint32_t)C || p->args.vec[v].n_terms != 0) g.vec_per_channel = 0;
     // Workgroups of 512 threads; a tile is NV position steps of 512 / cv positions each.
     // (workgroups of 256 or 128 threads, i.e. twice or four times the tiles, were measured on C5: 33.5 and 46.9 us
     // against 29.0; 1 024 threads, one workgroup per compute unit, 31.2 against 30.8)
     const uint32_t threads = 512;
     if (g.cv > threads) return fail(PF_ERR_UNSUPPORTED, "more than %d channels", (int)threads * vec);
     g.pos_per_step = threads / g.cv;
-    g.vec_per_channel = 1;
-    for (int v = 0; v < L.n_vec; ++v)
-        if (p->args.vec[v].numel > (uint32_t)C || p->args.vec[v].n_terms != 0) g.vec_per_channel = 0;
     // lanes that share a group when partials are merged: as many as fit, a power of two, at most 64
     g.lanes_per_group = 1;
     while (g.lanes_per_group < 64u && g.lanes_per_group * 2u * g.groups <= threads) g.lanes_per_group *= 2u;
@@ -886,6 +994,11 @@ pf_status plan_group(pf_plan_s* p, int forced_variant) {
         }
     }
     if (nv == 0) return fail(PF_ERR_INVALID_ARG, "PF_GROUP_NV must be 4, 8 or 16");
+    // (nothing but the load in front: steps there would be run by every pass over the held values)
+    if (forced_variant != PF_VARIANT_GROUP_TWO_PASS && L.n_full == 1 && g.vec_per_channel && L.pro.n == 1 && L.pro.u[0].code == pf::U_MOV && L.pro.u[0].kind == pf::K_FULL) {
+        const int64_t tiles_now = (int64_t)bps * samples, at_once = 2 * (int64_t)n_cu / bps * bps;
+        if (plan_group_slab(p, n_cu, samples, hw, C, tiles_now, bps, at_once > 0 ? (tiles_now + at_once - 1) / at_once : 2)) return PF_OK;
+    }
     // resident variant: catalogue entry, one full operand, per-channel broadcast operands only, and a grid the
     // device holds at once
     const bool jit_ok = p->spec_id == 0 && jit_possible(p->device);

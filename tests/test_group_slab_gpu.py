@@ -1,0 +1,81 @@
+"""GPU parity for GroupNorm over slabs of whole groups (a workgroup owns a slab, or a slice of one): forced onto shapes whose slabs,
+steps and slices end everywhere, and where the planner takes it."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from pf_testlib import check_chain, compare, env, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+
+def _chain(shape, groups, dtype, act="silu", seed=0, bias=False):
+    c = shape[-1]
+    s = wl.ChainSpec(inputs=[(dtype, shape), (dtype, (c,)), (dtype, (c,))] + ([(dtype, (c,))] if bias else []))
+    v = s.op("groupnorm", 0, 1, 2, f=[1e-5], i=[groups])
+    v = s.op(act, v) if act != "none" else v
+    s.out(s.op("add", v, 3) if bias else v, dtype)
+    t = [wl.random_tensor(shape, dtype, 7300 + seed), wl.random_tensor((c,), dtype, 7301 + seed, dist="positive"), wl.random_tensor((c,), dtype, 7302 + seed, scale=0.5)]
+    return s, t + ([wl.random_tensor((c,), dtype, 7303 + seed)] if bias else [])
+
+
+# slab and slices: one position, steps that end inside and at the last position, lanes that are not a divisor of 512, groups inside a
+# vector and across two, odd channels to a group, slices that differ by a position and leave the last step empty
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("shape,groups,slab,slices", [((3, 1, 1, 64), 8, 8, 1), ((2, 8, 8, 64), 8, 2, 1), ((1, 16, 33, 64), 8, 1, 1), ((2, 13, 7, 96), 12, 12, 1),
+                                                     ((2, 9, 9, 320), 32, 8, 1), ((1, 20, 20, 160), 32, 32, 1), ((5, 5, 5, 40), 5, 5, 1), ((2, 6, 6, 1184), 32, 32, 1),
+                                                     ((9, 7, 7, 128), 32, 8, 1), ((2, 9, 9, 64), 8, 4, 2), ((2, 21, 21, 160), 32, 16, 3), ((1, 12, 11, 64), 4, 4, 5),
+                                                     ((3, 33, 31, 96), 12, 12, 7), ((1, 64, 64, 64), 2, 1, 16), ((2, 8, 8, 512), 16, 16, 64), ((1, 56, 56, 128), 8, 4, 30)])
+def test_slabs_and_slices(shape, groups, slab, slices, dtype):
+    s, t = _chain(shape, groups, dtype)
+    with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS=str(slab), PF_SLAB_SLICES=str(slices)):
+        _, info, _ = check_chain(s, t, what=f"groupnorm + silu {shape} / {groups} {dtype}, slabs of {slab} groups, {slices} slices")
+    assert info.n_launches == 1
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_operands_behind_and_a_large_offset(dtype):
+    from paper_2307_04995_amd import binding as pf
+    s, t = _chain((2, 10, 10, 96), 12, dtype, act="none", bias=True, seed=10)
+    with env(PF_GROUP_SLAB="2"):
+        _, info, _ = check_chain(s, t, what="groupnorm + bias in slabs")
+    assert info.variant == pf.PF_VARIANT_GROUP_RESIDENT and info.n_launches == 1
+    # a common offset of 60 with a spread of 0.5: statistics that cancel would be off by percents
+    s, t = _chain((2, 16, 16, 64), 8, dtype, act="none", seed=20)
+    t[0] = wl.quantise(wl.widen(wl.random_tensor((2, 16, 16, 64), dtype, 7350, scale=0.5)) + 60.0, dtype)
+    for slices in ("1", "4"):
+        with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS="4", PF_SLAB_SLICES=slices):
+            check_chain(s, t, what=f"groupnorm around an offset, {slices} slices")
+
+
+@pytest.mark.parametrize("shape,groups,dtype", [((7, 56, 56, 768), 32, "f32"), ((1, 56, 56, 416), 32, "f32"), ((4, 64, 64, 224), 32, "bf16"), ((31, 10, 10, 96), 32, "f16")])
+def test_shapes_the_planner_takes_in_slabs(shape, groups, dtype):
+    s, t = _chain(shape, groups, dtype, seed=30)
+    _, info, _ = check_chain(s, t, what=f"groupnorm + silu {shape} {dtype}")
+    assert info.n_launches == 1 and info.lds_bytes != 0
+
+
+def test_repeated_runs_in_place_and_after_a_wait_that_gave_up():
+    from paper_2307_04995_amd import binding as pf
+    s, t = _chain((2, 20, 20, 128), 8, "f16", seed=40)
+    with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS="4", PF_SLAB_SLICES="8"):
+        plan = pf.Plan(s, 0)
+        with env(PF_GROUP_SPIN_LIMIT="1"):
+            hasty = pf.Plan(s, 0)
+    dev = [x.cuda() for x in t]
+    for rep in range(6):  # (both parities of the exchange, more than once)
+        x = wl.random_tensor((2, 20, 20, 128), "f16", 7400 + rep)
+        dev[0].copy_(x)
+        plan.run(dev, [dev[0]])  # in place: a workgroup holds its slice before it stores any of it
+        torch.cuda.synchronize()
+        compare(dev[0].cpu(), oracle_run(s, [x] + t[1:])[0], "f16", f"run {rep}")
+    assert plan.poll_error() == 0
+    plan.close()
+    # a bounded wait that runs out ends the launch, is reported once, and leaves the plan usable
+    out = torch.empty_like(dev[0])
+    for _ in range(3):
+        hasty.run(dev, [out])
+    torch.cuda.synchronize()
+    assert hasty.poll_error() in (0, 1) and hasty.poll_error() == 0
+    hasty.close()
