@@ -345,6 +345,29 @@ pf_status plan_row(pf_plan_s* p, int forced_variant) {
         }
         return PF_OK;
     }
+    // Rows that leave lanes of a wave idle above, or need several waves there, on as many lanes as three vectors each fill (with waves to
+    // fill the device, two to a SIMD).  Softmax of 129-192 vectors, us before and now: 1160 columns fp16, 46 400 rows 43.1 -> 36.1, causal
+    // 41.1 -> 29.5, [3, 12, 704, 704] fp32 causal 26.4 -> 19.8.  Of 33-48 and 65-80 vectors, several rows side by side in a wave, up to 32 768
+    // rows: 272 columns fp16, 32 640 rows 10.0 -> 8.7, 384, 12 288 rows 5.5 -> 4.7, 168 fp32, 26 880 rows, causal 9.2 -> 7.2; with more rows the
+    // waves above keep more loads in flight (376 columns fp16, 120 320 rows 31.9 against 36.4).  Normalisations of two full operands: a wave to
+    // a row, three or five to eight vectors a lane, where rows are ragged or fp32: 2639 columns fp16 23.1 -> 20.2, 1119 fp32 39.4 -> 31.0, 1532
+    // fp32 28.8 -> 26.5 (whole fp16 rows: 2640 columns 16.1 both, 3520 15.4 against 16.0; 1999 columns fp32, eight vectors, 30.3 against 30.9).
+    int wide_k = 0, wide_l = 6;
+    if (jit_ok && forced_variant < 0 && L.n_out == 1 && L.core == pf::CORE_SOFTMAX && L.n_full == 1 && L.n_vec == 0) {
+        for (int l = 4; l <= 6; ++l)
+            if (vpr > (2 << l) && vpr <= (l == 5 ? 80 : 3 << l) && (l == 6 || rows <= 32768)) wide_k = 3, wide_l = l;
+    } else if (jit_ok && forced_variant < 0 && L.n_out == 1 && (L.core == pf::CORE_LAYERNORM || L.core == pf::CORE_RMSNORM) && L.n_full == 2 && (p->ragged || es == 4)) {
+        if ((vpr > 128 && vpr <= 192) || (vpr > 256 && vpr <= 512)) wide_k = (int)((vpr + 63) / 64);
+        if (wide_k == 8 && p->ragged && es == 4) wide_k = 0;
+    }
+    if (rows < ((int64_t)2048 << (6 - wide_l)) || env_int("PF_ROW_WIDE", 1) == 0) wide_k = 0;
+    if (wide_k > 0) {
+        // (a kernel that does not fit the registers is not taken)
+        std::string err;
+        hipFunction_t fn = pf::jit_row_kernel(p->device, L.main_dtype, wide_k, 1, true, p->ragged, 256, wide_l, make_jit_spec(L), &err);
+        if (!fn || pf::jit_scratch_bytes(fn) != 0) wide_k = 0;
+    }
+    if (wide_k > 0) best_wpr = 1, best_k = wide_k;
     p->variant = best_wpr == 1 ? PF_VARIANT_ROW_WAVE : PF_VARIANT_ROW_BLOCK;
     p->k = best_k;
     p->row.waves_per_row = (uint32_t)best_wpr;
@@ -354,7 +377,7 @@ pf_status plan_row(pf_plan_s* p, int forced_variant) {
     // Rows per wave: a wave that owns short rows takes several at once, so that it has about 4 KB of loads
     // in flight (what it takes to cover the HBM latency at full occupancy), as long as enough waves remain
     // (16 per SIMD) to fill the device evenly and a specialised kernel exists for the combination.
-    if (best_wpr == 1 && (matched || jit_ok) && L.n_out == 1) {
+    if (best_wpr == 1 && (matched || jit_ok) && L.n_out == 1 && wide_k == 0) {
         const int64_t bytes_per_row_in_flight = (int64_t)L.n_full * best_k * 1024;
         int rpw = 1;
         while (rpw < 4 && bytes_per_row_in_flight * rpw < 4096 && best_k * rpw * 2 <= 4 && rows / (rpw * 2) >= 16384) rpw *= 2;
@@ -366,6 +389,8 @@ pf_status plan_row(pf_plan_s* p, int forced_variant) {
     // mask cuts off) do better two to a workgroup than four: C2 15.3 -> 14.7 us, a plain softmax of 512 columns 18.3 ->
     // 17.9 us; with 4 KB per wave (C3) four are better (17.7 against 17.9 us), eight and sixteen worse for all.
     if (best_wpr == 1 && env_int("PF_ROW_WAVES", 0) == 0 && (int64_t)L.n_full * best_k * p->row.rows_per_wave * 1024 <= 2048) p->row.rows_per_block = 2;
+    // (softmax of 40 vectors, two waves to a workgroup or four: 5.1 and 5.3 us, ragged 7.0 and 6.9; of 145 vectors 37.2 and 36.1)
+    if (wide_k > 0 && env_int("PF_ROW_WAVES", 0) == 0) p->row.rows_per_block = wide_l == 4 && !p->ragged ? 2u : 4u;
     p->block = dim3(64u * best_wpr * p->row.rows_per_block);
     p->lds_bytes = best_wpr > 1 ? 2 * 16 * 4 : 0;
     // Short rows (at most 32 vectors): several rows side by side in a wave, 8 / 16 / 32 lanes each, instead of
@@ -374,14 +399,22 @@ pf_status plan_row(pf_plan_s* p, int forced_variant) {
     if (best_wpr == 1 && best_k == 1 && vpr <= 32 && jit_ok && !reduce_only && L.n_out == 1 && rows >= 256) {
         log2l = 3;
         while ((1 << log2l) < vpr) ++log2l;
+        // A wave that serves several rows side by side has their loads in flight: two steps of rows, no more, for 32 lanes to a row (softmax of
+        // 256 columns fp16, 22 528 rows 6.0 us with one, 4.9 with two; 83 968 rows 16.4 with four, 15.4 with two; 244 columns 34.2 with
+        // four, 32.2 with two) and for ragged rows (61 columns 8.4 with four, 7.8 with two).
+        if (L.core == pf::CORE_SOFTMAX && L.n_full == 1 && L.n_vec == 0 && env_int("PF_ROWS_PER_WAVE", 0) == 0) {
+            if (log2l == 5 && rows >= 16384) p->row.rows_per_wave = 2;
+            else if (p->ragged && p->row.rows_per_wave > 2u) p->row.rows_per_wave = 2;
+        }
     }
+    if (wide_k > 0) log2l = wide_l;
     {
         const int forced_l = env_int("PF_ROW_LOG2_LANES", 0);
         if (forced_l >= 3 && forced_l <= 6 && best_wpr == 1 && best_k == 1 && vpr <= (1 << forced_l) && jit_ok && !reduce_only && L.n_out == 1) log2l = forced_l;
     }
     p->row_log2l = log2l;
     p->spec_id = (log2l == 6 && matched && pf::row_static_available(matched, p->k, (int)p->row.rows_per_wave, best_wpr == 1, p->block.x)) ? matched : 0;
-    if (!p->spec_id && jit_ok && have_static(p->k, (int)p->row.rows_per_wave, best_wpr == 1, p->block.x)) {
+    if (!p->spec_id && jit_ok && (wide_k > 0 || have_static(p->k, (int)p->row.rows_per_wave, best_wpr == 1, p->block.x))) {
         std::string err;
         if (reduce_only) p->jit_fn = pf::jit_row_reduce_kernel(p->device, L.main_dtype, p->k, p->ragged, make_jit_spec(L), &err);
         else p->jit_fn = pf::jit_row_kernel(p->device, L.main_dtype, p->k, (int)p->row.rows_per_wave, best_wpr == 1, p->ragged,
