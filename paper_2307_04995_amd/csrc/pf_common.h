@@ -198,9 +198,8 @@ struct PoolGeom {
     FastDiv div_norm_cpg;
 };
 
-// GroupNorm, or GroupNorm and pooling, over slabs of whole groups (group_slab_kernel, norm_pool_slab_kernel): a workgroup holds a slice of a
-// slab's positions.
-struct SlabGeom {
+// Group family over slabs of whole groups (group_slab_kernel): a workgroup holds a slice of a slab's positions.
+struct GroupSlabGeom {
     uint32_t hw, channels, groups, cpg;  // cpg: channels per group
     uint32_t slab_groups, slabs_per_sample;
     uint32_t slices;                     // workgroups that share a (sample, slab)
@@ -208,15 +207,24 @@ struct SlabGeom {
     uint32_t blocks, blocks_per_die;
     uint32_t parts;       // the most groups one vector touches
     uint32_t log2_lanes;  // lanes that merge a group's statistics
-    float inv_hw;         // (pooling)
     FastDiv div_cpg;
     // several slices only
     uint32_t spin_limit;     // re-reads before a wait gives up
     uint32_t gather_words;   // samples * groups * slices
     uint64_t* ws_gather;     // [2][samples][groups][slices] (mean, M2) words by the launch number's parity; all-ones = not written yet
-    uint32_t* ws_pooled;     // [samples][slabs][slices][slab vectors * VEC] pooled values as words; all-ones = not written yet
     uint32_t* ws_epoch;      // [blocks] launches so far
     uint32_t* ws_error;      // set to 1 if a wait ran out
+};
+
+// Pool family, GroupNorm and pooling in one launch: a workgroup holds all positions of a slab of whole groups.
+struct SlabGeom {
+    uint32_t hw, channels, cpg;  // cpg: channels per group
+    uint32_t slab_groups, slabs_per_sample;
+    uint32_t slabs, slabs_per_die;
+    uint32_t parts;       // the most groups one vector touches
+    uint32_t log2_lanes;  // lanes that merge a group's statistics
+    float inv_hw;
+    FastDiv div_cpg;
 };
 
 // Column family: normalisation of [outer, c, s] over c (s contiguous); all tensors of one storage type.

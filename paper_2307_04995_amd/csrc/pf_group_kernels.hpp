@@ -136,37 +136,6 @@ PF_DEVICE uint64_t pack_slot(float mean, float m2) {
     return w;
 }
 
-// Slabs in slices (group_slab_kernel, norm_pool_slab_kernel): a slice's statistics of one group as a word of its own, the word of the
-// other parity put back to empty ...
-PF_DEVICE void publish_slice(uint64_t* word, uint64_t* other, Stat st) {
-    __hip_atomic_store(other, kSlotEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(word, pack_slot(st.mean, st.m2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// ... and slices j, j + lanes, ... of the group, re-read while they are empty (a bounded wait) and merged.  A slice holds slice_len
-// positions, the first slice_rest slices one more.
-template <bool EXACT>
-PF_DEVICE Stat gather_slices(const uint64_t* words, uint32_t slices, uint32_t j, uint32_t lanes, uint32_t slice_len, uint32_t slice_rest, uint32_t cpg, uint32_t spin_limit,
-                             uint32_t* ws_error) {
-    Stat st = {0.0f, 0.0f, 0.0f};
-    uint32_t spins = 0;
-    for (uint32_t b = j; b < slices; b += lanes) {
-        uint64_t w;
-        for (;;) {
-            w = __hip_atomic_load(words + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (w != kSlotEmpty) break;
-            if (++spins >= spin_limit) {
-                __hip_atomic_store(ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(8);
-        }
-        if (w == kSlotEmpty) continue;
-        st = stat_merge<EXACT>(st, Stat{(float)((slice_len + (b < slice_rest ? 1u : 0u)) * cpg), __builtin_bit_cast(float, (uint32_t)w),
-                                        __builtin_bit_cast(float, (uint32_t)(w >> 32))});
-    }
-    return st;
-}
-
 // LDS-merge the position steps of the workgroup, then publish one word per group.
 PF_DEVICE void publish_tile(const GroupGeom& g, Stat st, uint32_t pstep, uint32_t cvi, bool active, float* lds, uint32_t sample,
                             uint32_t bx) {

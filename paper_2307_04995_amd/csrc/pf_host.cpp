@@ -265,7 +265,7 @@ pf_status pf_chain_run(const pf_plan* plan, const void* const* inputs, void* con
                     return fail(PF_ERR_UNSUPPORTED, "the one-launch GroupNorm variant cannot be recorded into a graph; plan the two-launch variant for that");
             }
             if (plan->group_slab) {
-                pf::SlabGeom g = plan->slab;
+                pf::GroupSlabGeom g = plan->gslab;
                 void* params[] = {&a, &g};
                 e = pf::jit_launch(plan->jit_fn, plan->grid, plan->block, plan->dyn_lds, params, st);
                 break;
@@ -352,8 +352,7 @@ pf_status pf_chain_plan_poll_error(const pf_plan* plan, int32_t* flag) {
         // does not expect (slots of the wrong parity still filled, partial results of late slices still published).  Put the
         // workspace back the way the planner left it.  (The caller has synchronised: nothing of this plan is running.)
         bool ok = hipMemset(err, 0, sizeof(word)) == hipSuccess;
-        if ((plan->group_slab || plan->pool_slab) && plan->slab.ws_gather)  // (both parities, and the pooled values behind them)
-            ok = ok && hipMemset(plan->slab.ws_gather, 0xff, (size_t)(reinterpret_cast<char*>(plan->slab.ws_epoch) - reinterpret_cast<char*>(plan->slab.ws_gather))) == hipSuccess;
+        if (plan->group_slab) ok = ok && hipMemset(plan->gslab.ws_gather, 0xff, (size_t)2 * plan->gslab.gather_words * sizeof(uint64_t)) == hipSuccess;
         if (plan->family == PF_FAMILY_GROUP && plan->group.ws_gather) {
             const pf::GroupGeom& g = plan->group;
             ok = ok && hipMemset(g.ws_gather, 0xff, (size_t)2 * g.samples * g.groups * g.blocks_per_sample * sizeof(uint64_t)) == hipSuccess;

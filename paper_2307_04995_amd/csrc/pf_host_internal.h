@@ -131,8 +131,9 @@ struct pf_plan_s {
     pf::PoolGeom pool;
     pf::ColArgs col;
     bool pool_slab = false;   // pool family: GroupNorm and pooling in one launch (norm_pool_slab_kernel)
-    bool group_slab = false;  // group family: slabs of whole groups (group_slab_kernel)
     pf::SlabGeom slab;
+    bool group_slab = false;  // group family: slabs of whole groups (group_slab_kernel)
+    pf::GroupSlabGeom gslab;
     int stencil_ks = 3;       // kernel extent of the depthwise convolution
     int row_log2l = 6;        // row family: log2 of the lanes of a wave that share a row
     int perm_plane = 0;          // transpose family: 1 / 2 = the plane variant with a flat input / output

@@ -406,9 +406,9 @@ hipFunction_t jit_pool_kernel(int device, int dtype, int nv, int op, bool ragged
     return compile(device, "#include \"pf_pool_kernels.hpp\"\n", name.str(), err);
 }
 
-hipFunction_t jit_norm_pool_slab_kernel(int device, int dtype, int nv, int slab_vecs, int op, bool sliced, const JitSpec& spec, std::string* err) {
+hipFunction_t jit_norm_pool_slab_kernel(int device, int dtype, int nv, int slab_vecs, int op, const JitSpec& spec, std::string* err) {
     std::ostringstream name;
-    name << "pf::norm_pool_slab_kernel<" << dtype << ", " << nv << ", " << slab_vecs << ", " << spec_text(spec) << ", " << op << (sliced ? ", true>" : ", false>");
+    name << "pf::norm_pool_slab_kernel<" << dtype << ", " << nv << ", " << slab_vecs << ", " << spec_text(spec) << ", " << op << ">";
     return compile(device, "#include \"pf_pool_kernels.hpp\"\n", name.str(), err);
 }
 

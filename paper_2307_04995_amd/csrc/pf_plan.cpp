@@ -821,55 +821,6 @@ pf_status plan_perm(pf_plan_s* p, int forced_variant) {
 }
 
 // ---- group family
-// The geometry (p->slab), grid and workspace of n samples of hw positions in slabs of d groups (`vecs` vectors of a position) and `slices`
-// slices for the kernel fn; op: the pooling behind (-1 none).  false where the workgroups of several slices, which wait for one another,
-// would not all be resident, or where the workspace is not to be had.
-static bool slab_geometry(pf_plan_s* p, int n_cu, int64_t n, int64_t hw, int64_t ch, int64_t d, int64_t vecs, int64_t slices, hipFunction_t fn, uint32_t lds_per_part, int op) {
-    const int64_t groups = p->low.groups, cpg = ch / groups;
-    const int vec = 16 / dtype_size(p->low.main_dtype);
-    pf::SlabGeom& g = p->slab;
-    memset(&g, 0, sizeof(g));
-    g.hw = (uint32_t)hw;
-    g.channels = (uint32_t)ch;
-    g.groups = (uint32_t)groups;
-    g.cpg = (uint32_t)cpg;
-    g.div_cpg = make_fastdiv(g.cpg);
-    g.slab_groups = (uint32_t)d;
-    g.slabs_per_sample = (uint32_t)(groups / d);
-    g.slices = (uint32_t)slices;
-    g.slice_len = (uint32_t)(hw / slices);
-    g.slice_rest = (uint32_t)(hw % slices);
-    g.blocks = (uint32_t)(n * g.slabs_per_sample * slices);
-    g.blocks_per_die = (g.blocks + 7u) / 8u;
-    g.inv_hw = 1.0f / (float)hw;
-    g.parts = 1;
-    for (int64_t v = 0; v < ch / vec; ++v) g.parts = std::max<uint32_t>(g.parts, (uint32_t)((v * vec + vec - 1) / cpg - v * vec / cpg + 1));
-    while (g.log2_lanes < 6u && (d << (g.log2_lanes + 1)) <= 512) ++g.log2_lanes;
-    const uint32_t dyn_lds = std::max<uint32_t>(lds_per_part * g.parts, op >= 0 ? 512u * (uint32_t)vec * 4u : 0u), grid = g.blocks_per_die * 8u;
-    if (slices > 1) {
-        if ((int64_t)pf::jit_blocks_per_cu(fn, 512, dyn_lds) * n_cu < (int64_t)grid) return false;
-        g.spin_limit = (uint32_t)(op < 0 ? env_int("PF_GROUP_SPIN_LIMIT", 1 << 22) : env_int("PF_POOL_SPIN_LIMIT", 1 << 18));
-        g.gather_words = (uint32_t)(n * groups * slices);
-        const uint64_t gather_bytes = (uint64_t)2 * g.gather_words * sizeof(uint64_t), pooled_bytes = op < 0 ? 0 : (uint64_t)g.blocks * vecs * vec * sizeof(uint32_t);
-        const uint64_t filled = (gather_bytes + pooled_bytes + 255) / 256 * 256, epochs = ((uint64_t)g.blocks * sizeof(uint32_t) + 255) / 256 * 256;
-        if (hipSetDevice(p->device) != hipSuccess || plan_workspace_alloc(p, filled + epochs + 256, "workspace allocation") != PF_OK) return false;
-        char* ws = static_cast<char*>(p->workspace);
-        if (plan_workspace_fill(p, ws, 0xff, filled, true) != PF_OK || plan_workspace_fill(p, ws + filled, 0, epochs + 256, true) != PF_OK) {
-            (void)hipFree(p->workspace);
-            p->workspace = nullptr;
-            return false;
-        }
-        g.ws_gather = reinterpret_cast<uint64_t*>(ws);
-        g.ws_pooled = reinterpret_cast<uint32_t*>(ws + gather_bytes);
-        g.ws_epoch = reinterpret_cast<uint32_t*>(ws + filled);
-        g.ws_error = reinterpret_cast<uint32_t*>(ws + filled + epochs);
-        p->ws_error = g.ws_error;
-    }
-    p->grid = dim3(grid);
-    p->dyn_lds = dyn_lds;
-    return true;
-}
-
 // GroupNorm over slabs of whole groups (group_slab_kernel).  false where the kernel does not take the chain or is not the quicker one.
 // tiles, tiles_per_sample, rounds: what the one-launch kernel of whole positions would be planned with (rounds: of co-resident tiles).
 //
@@ -927,14 +878,50 @@ static bool plan_group_slab(pf_plan_s* p, int n_cu, int64_t n, int64_t hw, int64
     }
     if (!fn) return false;
     const int64_t best_d = picks[at].d, best_nv = picks[at].nv, best_slices = picks[at].slices;
-    if (!slab_geometry(p, n_cu, n, hw, ch, best_d, best_d * cpg / vec, best_slices, fn, 512u * 3u * 4u, -1)) return false;
-    const uint32_t dyn_lds = p->dyn_lds;
+    pf::GroupSlabGeom& g = p->gslab;
+    memset(&g, 0, sizeof(g));
+    g.hw = (uint32_t)hw;
+    g.channels = (uint32_t)ch;
+    g.groups = (uint32_t)groups;
+    g.cpg = (uint32_t)cpg;
+    g.div_cpg = make_fastdiv(g.cpg);
+    g.slab_groups = (uint32_t)best_d;
+    g.slabs_per_sample = (uint32_t)(groups / best_d);
+    g.slices = (uint32_t)best_slices;
+    g.slice_len = (uint32_t)(hw / best_slices);
+    g.slice_rest = (uint32_t)(hw % best_slices);
+    g.blocks = (uint32_t)(n * g.slabs_per_sample * best_slices);
+    g.blocks_per_die = (g.blocks + 7u) / 8u;
+    g.parts = 1;
+    for (int64_t v = 0; v < ch / vec; ++v) g.parts = std::max<uint32_t>(g.parts, (uint32_t)((v * vec + vec - 1) / cpg - v * vec / cpg + 1));
+    while (g.log2_lanes < 6u && (best_d << (g.log2_lanes + 1)) <= 512) ++g.log2_lanes;
+    const uint32_t dyn_lds = 512u * 3u * g.parts * 4u, grid = g.blocks_per_die * 8u;
+    if (best_slices > 1) {
+        // every wait is for workgroups of the same launch: all of them have to be resident
+        if ((int64_t)pf::jit_blocks_per_cu(fn, 512, dyn_lds) * n_cu < (int64_t)grid) return false;
+        g.spin_limit = (uint32_t)env_int("PF_GROUP_SPIN_LIMIT", 1 << 22);
+        g.gather_words = (uint32_t)(n * groups * best_slices);
+        const uint64_t gather_bytes = ((uint64_t)2 * g.gather_words * sizeof(uint64_t) + 255) / 256 * 256, epochs = ((uint64_t)g.blocks * sizeof(uint32_t) + 255) / 256 * 256;
+        if (hipSetDevice(p->device) != hipSuccess || plan_workspace_alloc(p, gather_bytes + epochs + 256, "workspace allocation") != PF_OK) return false;
+        char* ws = static_cast<char*>(p->workspace);
+        if (plan_workspace_fill(p, ws, 0xff, gather_bytes, true) != PF_OK || plan_workspace_fill(p, ws + gather_bytes, 0, epochs + 256, true) != PF_OK) {
+            (void)hipFree(p->workspace);
+            p->workspace = nullptr;
+            return false;
+        }
+        g.ws_gather = reinterpret_cast<uint64_t*>(ws);
+        g.ws_epoch = reinterpret_cast<uint32_t*>(ws + gather_bytes);
+        g.ws_error = reinterpret_cast<uint32_t*>(ws + gather_bytes + epochs);
+        p->ws_error = g.ws_error;
+    }
     p->jit_fn = fn;
     p->group_slab = true;
     p->variant = PF_VARIANT_GROUP_RESIDENT;
     p->spec_id = pf::kSpecJit;
     p->k = (int)best_nv;
+    p->grid = dim3(grid);
     p->block = dim3(512);
+    p->dyn_lds = dyn_lds;
     p->lds_bytes = dyn_lds + 2 * 512 * 4;
     p->n_launches = 1;
     p->args.n_inner = (uint32_t)ch;
@@ -1475,45 +1462,32 @@ static bool plan_norm_pool_slab(pf_plan_s* p, int n_cu) {
         const double cost = 9.0 + (double)(rounds * nv) * (per_cu == 2 && slabs > n_cu ? 1.8 : 0.87);
         if (cost < best || (forced && best_d == 0)) best = cost, best_d = d, best_cvs = cvs, best_nv = nv;
     }
-    // 16-bit tensors of more than 2 MiB: any slab, in slices where that fills the device (at most a workgroup to a unit), where the model of
-    // that launch is half a microsecond ahead of the two launches' (fitted to 270 measured pairs of slab and slices of 26 shapes: 5 % off
-    // in the mean; its choices take 0.87 of the time of the rule above).  us, fp16 or bf16, before and now: [32, 64, 64, 320] 46.8 -> 43.0 (16 groups, 4
-    // slices), [21, 28, 28, 64] 13.7 -> 8.8 and [19, 14, 14, 576] 13.3 -> 9.3 (one slice), [23, 32, 32, 992] 39.5 -> 32.1, [4, 64, 64, 672]
-    // 25.7 -> 20.8 (8 groups, 16 slices).  Smaller tensors would gain as well ([1, 7, 7, 128] 9.8, 8.7 in one launch), but that they are two
-    // launches is relied upon.
-    int64_t best_slices = 1;
-    const int forced_d = env_int("PF_SLAB_GROUPS", 0), forced_slices = env_int("PF_SLAB_SLICES", 0);
-    if (forced_slices > 0 || (!forced && es == 2 && n * hw * ch * es > (2 << 20))) {
-        const double mb = (double)(n * hw * ch * es) * 1e-6;
-        double least = forced_slices > 0 ? 1e30 : 12.4 - 0.37 * (double)(n * ((hw + 512 / cv - 1) / (512 / cv))) / (double)n_cu + 0.68 * mb - 0.5;
-        for (int64_t d = 1; d <= groups && d <= 512; ++d) {
-            if (groups % d != 0 || (forced_d && d != forced_d)) continue;
-            const int64_t slabs = n * (groups / d), sc = d * cpg, bytes = sc * es;
-            int64_t cvs = 0;
-            for (int64_t lo = 0; lo < ch; lo += sc) cvs = std::max(cvs, (lo + sc - 1) / vec - lo / vec + 1);
-            if (cvs * vec > 512) continue;
-            const int64_t pps = 512 / cvs;
-            const bool lines = (bytes % 128 == 0 && (ch * es) % 128 == 0) || d == groups;
-            const double waste = lines ? 0.0 : std::min(3.0, 112.0 / (double)bytes);  // (of the memory lines a position's share touches)
-            for (int64_t slices = 1; slices <= std::min<int64_t>(64, hw); ++slices) {
-                if (forced_slices && slices != forced_slices) continue;
-                const int64_t longest = (hw + slices - 1) / slices, nv = (longest + pps - 1) / pps, blocks = slabs * slices;
-                if (nv > 44 || (nv - 1) * pps > hw / slices || blocks > 0x7fffff || (blocks > n_cu && !forced_slices)) continue;
-                const double cost = 5.8 + mb * (0.082 + 0.05 * waste) + 0.66 * (double)nv + 0.15 * std::log2((double)pps) + (slices > 1 ? 3.5 + 0.1 * (double)slices : 0.0);
-                if (cost < least) least = cost, best_d = d, best_cvs = cvs, best_nv = nv, best_slices = slices;
-            }
-        }
-    }
     if (best_d == 0) return false;
+    pf::SlabGeom g;
+    memset(&g, 0, sizeof(g));
+    g.hw = (uint32_t)hw;
+    g.channels = (uint32_t)ch;
+    g.cpg = (uint32_t)cpg;
+    g.div_cpg = make_fastdiv(g.cpg);
+    g.slab_groups = (uint32_t)best_d;
+    g.slabs_per_sample = (uint32_t)(groups / best_d);
+    g.slabs = (uint32_t)(n * g.slabs_per_sample);
+    g.slabs_per_die = (g.slabs + 7u) / 8u;
+    g.inv_hw = 1.0f / (float)hw;
+    g.parts = 1;
+    for (int64_t v = 0; v < ch / vec; ++v) g.parts = std::max<uint32_t>(g.parts, (uint32_t)((v * vec + vec - 1) / cpg - v * vec / cpg + 1));
+    while (g.log2_lanes < 6u && (best_d << (g.log2_lanes + 1)) <= 512) ++g.log2_lanes;
     pf::JitSpec jspec = make_jit_spec(L);
     if (L.main_dtype != PF_F32) jspec.flags |= 32;
     std::string err;
-    hipFunction_t fn = pf::jit_norm_pool_slab_kernel(p->device, L.main_dtype, (int)best_nv, (int)best_cvs, L.pool_op, best_slices > 1, jspec, &err);
+    hipFunction_t fn = pf::jit_norm_pool_slab_kernel(p->device, L.main_dtype, (int)best_nv, (int)best_cvs, L.pool_op, jspec, &err);
     if (!fn || pf::jit_scratch_bytes(fn) != 0) return false;
-    if (!slab_geometry(p, n_cu, n, hw, ch, best_d, best_cvs, best_slices, fn, 512u * 3u * 4u, L.pool_op)) return false;
     p->jit_fn = fn;
     p->pool_slab = true;
+    p->slab = g;
     p->k = (int)best_nv;
+    p->grid = dim3(g.slabs_per_die * 8u);
+    p->dyn_lds = 512u * std::max<uint32_t>(3u * g.parts, (uint32_t)vec) * 4u;
     p->lds_bytes = p->dyn_lds + 2 * 512 * 4;
     p->family = PF_FAMILY_POOL;
     p->variant = 0;

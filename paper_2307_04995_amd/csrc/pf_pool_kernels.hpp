@@ -33,46 +33,6 @@ PF_DEVICE uint32_t pool_word(float x) {
     return w == kPoolEmpty ? 0x7fc00000u : w;
 }
 
-// The published words of one channel, slices r, r + stride, ... of `others` (`words` apart), merged into `merged`: eight of them in
-// flight at a time, the empty ones re-read together (one trip to memory a round, not one a word), each put back to empty
-// for the next launch.  The wait is bounded: after spin_limit re-reads the error word is set and what is missing is left out.
-template <int OP>
-PF_DEVICE void pool_merge_slices(uint32_t* base, uint32_t others, uint32_t words, uint32_t r, uint32_t stride, uint32_t spin_limit, uint32_t* ws_error, float& merged) {
-    uint32_t spins = 0;
-    for (uint32_t b0 = r; b0 < others; b0 += 8u * stride) {
-        uint32_t w[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const uint32_t b = b0 + (uint32_t)u * stride;
-            w[u] = b < others ? __hip_atomic_load(base + (uint64_t)b * words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                              : pool_word(pool_identity<OP>());
-        }
-        for (;;) {
-            bool waiting = false;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) waiting = waiting || w[u] == kPoolEmpty;
-            if (!waiting) break;
-            if (++spins > spin_limit) {
-                __hip_atomic_store(ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(8);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint32_t b = b0 + (uint32_t)u * stride;
-                if (w[u] == kPoolEmpty) w[u] = __hip_atomic_load(base + (uint64_t)b * words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const uint32_t b = b0 + (uint32_t)u * stride;
-            if (b >= others || w[u] == kPoolEmpty) continue;
-            __hip_atomic_store(base + (uint64_t)b * words, kPoolEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            merged = pool_combine<OP>(merged, __builtin_bit_cast(float, w[u]));
-        }
-    }
-}
-
 // log2 of the largest power of two that is at most v, and at most 64 lanes
 constexpr uint32_t floor_log2_64(uint32_t v) { return v >= 64u ? 6u : v >= 2u ? 1u + floor_log2_64(v / 2u) : 0u; }
 // One value per channel from `rows` rows of `words` channels in LDS, returned to lane t for channel t.  2^log2_lanes adjacent lanes share a
@@ -332,15 +292,49 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
         return;
     }
     // The merger (a slab that is one slice merges nothing): merge_rows row groups of threads, each a channel per lane
-    // (consecutive lanes, consecutive words); row group r takes the slices r, r + merge_rows, ...
+    // (consecutive lanes, consecutive words); row group r takes the slices r, r + merge_rows, ..., eight of them in flight
+    // at a time.  Every wait is bounded: after spin_limit re-reads the error word is set and the missing slice is left out.
     const uint32_t others = g.blocks_per_sample - 1u;
     if (others != 0u) {
         const uint32_t r = t / row_words, idx = t - r * row_words;
         uint32_t* base = g.ws_partial + (uint64_t)unit * g.blocks_per_sample * row_words;
+        uint32_t spins = 0;
         float merged = pool_identity<OP>();
         if (r < g.merge_rows && idx < slab_channels) {
             if (r == 0u) merged = mine;  // the merger's own slice
-            pool_merge_slices<OP>(base + idx, others, row_words, r, g.merge_rows, g.spin_limit, g.ws_error, merged);
+            for (uint32_t b0 = r; b0 < others; b0 += 8u * g.merge_rows) {
+                uint32_t w[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
+                    w[u] = b < others ? __hip_atomic_load(base + (uint64_t)b * row_words + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                      : pool_word(pool_identity<OP>());
+                }
+                // words still empty are re-read together (one trip to memory per round, not one per word)
+                for (;;) {
+                    bool waiting = false;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) waiting = waiting || w[u] == kPoolEmpty;
+                    if (!waiting) break;
+                    if (++spins > g.spin_limit) {
+                        __hip_atomic_store(g.ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(8);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
+                        if (w[u] == kPoolEmpty) w[u] = __hip_atomic_load(base + (uint64_t)b * row_words + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const uint32_t b = b0 + (uint32_t)u * g.merge_rows;
+                    if (b >= others || w[u] == kPoolEmpty) continue;
+                    __hip_atomic_store(base + (uint64_t)b * row_words + idx, kPoolEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    merged = pool_combine<OP>(merged, __builtin_bit_cast(float, w[u]));
+                }
+            }
         }
         __syncthreads();  // (the positions' rows have been read)
         if (r < g.merge_rows) lds[t] = merged;
@@ -381,11 +375,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
     else store_stream(a.out[0], out_off, S::pack(s.acc));
 }
 
-// GroupNorm -> steps -> pooling in one launch: a workgroup owns (sample, slab of whole groups) and all positions, or a slice of them
-// (SLICED), held packed in its registers (NV vectors a lane).  The statistics, which are the groups' alone, and the pooled
-// values then never leave the workgroup: x is read once, nothing is exchanged between workgroups and no second launch waits for the
-// first.  Slices exchange one word a group, as in group_slab_kernel, and the slab's last one merges the others' pooled values; all
-// workgroups of such a launch are resident together.
+// GroupNorm -> steps -> pooling in one launch: a workgroup owns (sample, slab of whole groups) and all positions, held packed in
+// its registers (NV vectors a lane).  The statistics, which are the groups' alone, and the pooled values then never leave
+// the workgroup: x is read once, nothing is exchanged between workgroups and no second launch waits for the first.
 //
 // A slab starts and ends where its groups do, inside a 16-byte vector as it may be: lanes hold the whole vectors that the slab
 // touches, and elements of a neighbour's groups are left out of the statistics and of the result.  Slabs are rarely whole
@@ -395,9 +387,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(Spec::
 // M2) triples, one per group the vector touches.
 //
 // Bound: the arithmetic behind the normalisation, with few waves to cover its waits.  [32, 64, 64, 320] fp16, GroupNorm(32) + SiLU +
-// mean, 84 MB: 48.9 us in two launches, 44.6 in one, 41.5 with a channel's rows merged by lanes (pool_reduce_rows), 41.1 in slabs of 16 groups and 4
-// slices (every buffer cold: 46.8 and 43.0: slabs of whole memory lines waste less of what they read).
-template <int DT, int NV, int CVS, class Spec, int OP, bool SLICED>
+// mean, 84 MB: 48.9 us in two launches, 44.6 in one, 41.5 with a channel's rows merged by lanes (pool_reduce_rows).
+template <int DT, int NV, int CVS, class Spec, int OP>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 16 ? 2 : 4))) norm_pool_slab_kernel(const ChainArgs a, const SlabGeom g) {
     using S = Storage<DT>;
     constexpr int VEC = S::VEC;
@@ -406,14 +397,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
     __shared__ float lds_stat[2 * 512];
     using P = typename Spec::Pro;
     static_assert(Spec::kStatic && P::n >= 2 && P::at(0).code == U_MOV && P::at(0).kind == K_FULL && P::at(1).code == U_GNORM, "the load, then the normalisation");
-    const uint32_t at = (blockIdx.x & 7u) * g.blocks_per_die + (blockIdx.x >> 3);
-    if (at >= g.blocks) return;  // (the grid is rounded up to a multiple of eight)
-    const uint32_t row = at / g.slabs_per_sample, in_sample = at - row * g.slabs_per_sample;
-    const uint32_t sample = SLICED ? row / g.slices : row, slice = SLICED ? row - sample * g.slices : 0u;
-    const uint32_t p_begin = SLICED ? slice * g.slice_len + min(slice, g.slice_rest) : 0u;
-    const uint32_t p_count = SLICED ? g.slice_len + (slice < g.slice_rest ? 1u : 0u) : g.hw;
-    const uint32_t epoch = SLICED ? g.ws_epoch[at] : 0u;
-    const uint32_t grp0 = in_sample * g.slab_groups;
+    const uint32_t slab = (blockIdx.x & 7u) * g.slabs_per_die + (blockIdx.x >> 3);
+    if (slab >= g.slabs) return;  // (the grid is rounded up to a multiple of eight)
+    const uint32_t sample = slab / g.slabs_per_sample;
+    const uint32_t grp0 = (slab - sample * g.slabs_per_sample) * g.slab_groups;
     const uint32_t ch0 = grp0 * g.cpg, ch1 = ch0 + g.slab_groups * g.cpg;
     const uint32_t v0 = ch0 / (uint32_t)VEC;
     const uint32_t t = threadIdx.x;
@@ -422,16 +409,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
     const bool active = pstep < PPS && ch < ch1;
 
     // ---- the slab into registers.  No branch around a load: a lane without a vector reads the step's first.
-    const char* base = static_cast<const char*>(a.full[P::at(0).slot]) + ((uint64_t)sample * g.hw + p_begin) * g.channels * S::ESIZE;
+    const char* base = static_cast<const char*>(a.full[P::at(0).slot]) + (uint64_t)sample * g.hw * g.channels * S::ESIZE;
     const uint32_t step_bytes = PPS * g.channels * (uint32_t)S::ESIZE;
     const uint32_t first_bytes = v0 * 16u;
     const uint32_t lane_bytes = active ? pstep * g.channels * (uint32_t)S::ESIZE + (v0 + cvl) * 16u : first_bytes;
-    const bool last_valid = active && (uint32_t)(NV - 1) * PPS + pstep < p_count;  // (every step but the last is whole)
-    // (a slice one position shorter than the others may have nothing in the last step: its first vector again)
-    const uint32_t last_step = !SLICED || (uint32_t)(NV - 1) * PPS < p_count ? (uint32_t)(NV - 1) : 0u;
+    const bool last_valid = active && (uint32_t)(NV - 1) * PPS + pstep < g.hw;  // (every step but the last is whole)
     u32x4 raw[NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(base + (size_t)((i + 1 < NV ? (uint32_t)i : last_step) * step_bytes) + (i + 1 < NV || last_valid ? lane_bytes : first_bytes));
+    for (int i = 0; i < NV; ++i) raw[i] = *reinterpret_cast<const u32x4*>(base + (size_t)((uint32_t)i * step_bytes) + (i + 1 < NV || last_valid ? lane_bytes : first_bytes));
     constexpr int gs = Spec::kGamma, bs = Spec::kBeta;
     const u32x4 graw = load_vec_operand<DT>(a.vec[gs], 0u, active ? ch : v0 * (uint32_t)VEC, g.channels);
     const u32x4 braw = load_vec_operand<DT>(a.vec[bs], 0u, active ? ch : v0 * (uint32_t)VEC, g.channels);
@@ -519,22 +504,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
             }
         }
         for (uint32_t m = 1; m < lanes; m <<= 1) st = stat_merge(st, stat_shfl_xor(st, (int)m));
-        if constexpr (SLICED) {
-            if (in_range) {
-                const uint64_t first_word = ((uint64_t)sample * g.groups + grp0 + q) * g.slices;
-                uint64_t* words = g.ws_gather + (epoch & 1u) * g.gather_words + first_word;
-                if (j == 0u) publish_slice(words + slice, g.ws_gather + ((epoch & 1u) ^ 1u) * g.gather_words + first_word + slice, st);
-                st = gather_slices<false>(words, g.slices, j, lanes, g.slice_len, g.slice_rest, g.cpg, g.spin_limit, g.ws_error);
-            }
-            for (uint32_t m = 1; m < lanes; m <<= 1) st = stat_merge(st, stat_shfl_xor(st, (int)m));
-        }
         if (in_range && j == 0u) {
             lds_stat[q * 2u] = st.mean;
             lds_stat[q * 2u + 1u] = 1.0f / sqrtf((st.n > 0.0f ? st.m2 / st.n : 0.0f) + a.eps);
         }
     }
     __syncthreads();
-    if (SLICED && t == 0u) g.ws_epoch[at] = epoch + 1u;
 
     // ---- normalise, the steps behind, pool
     PoolNorm<VEC> norm;
@@ -576,23 +551,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
 #pragma unroll
     for (int e = 0; e < VEC; ++e) lds[t * VEC + e] = acc[e];
     __syncthreads();
-    float mine = pool_reduce_rows<OP>(lds, lds_stat, PPS, row_words, log2_lanes);
-    if constexpr (SLICED) {
-        // every slice but the slab's last publishes its pooled values; the last one merges (see pool_kernel)
-        constexpr uint32_t rows = 512u / row_words;
-        uint32_t* part = g.ws_pooled + (uint64_t)(sample * g.slabs_per_sample + in_sample) * g.slices * row_words;
-        if (slice + 1u != g.slices) {
-            if (t < row_words) __hip_atomic_store(part + (uint64_t)slice * row_words + t, pool_word(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return;
-        }
-        const uint32_t r = t / row_words, idx = t - r * row_words;
-        float merged = r == 0u ? mine : pool_identity<OP>();
-        if (r < rows) pool_merge_slices<OP>(part + idx, g.slices - 1u, row_words, r, rows, g.spin_limit, g.ws_error, merged);
-        __syncthreads();  // (the positions' rows have been read)
-        if (r < rows) lds[t] = merged;
-        __syncthreads();
-        mine = pool_reduce_rows<OP>(lds, lds_stat, rows, row_words, log2_lanes);
-    }
+    const float mine = pool_reduce_rows<OP>(lds, lds_stat, PPS, row_words, log2_lanes);
     if (log2_lanes == 0u) {
         if (t < row_words) lds_stat[t] = mine;
         __syncthreads();

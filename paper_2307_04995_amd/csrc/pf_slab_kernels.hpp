@@ -16,7 +16,7 @@ namespace pf {
 // Exchange (SLICED): as in group_kernel, self-describing words in two parities, with the launch's number kept on the device: a word of the
 // workgroup's own, which nobody else touches.  All workgroups of a launch with slices are resident together.
 template <int DT, int NV, int CVS, class Spec, bool SLICED, bool PACKED>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 16 ? 2 : 4))) group_slab_kernel(const ChainArgs a, const SlabGeom g) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 16 ? 2 : 4))) group_slab_kernel(const ChainArgs a, const GroupSlabGeom g) {
     using S = Storage<DT>;
     constexpr int VEC = S::VEC;
     constexpr uint32_t PPS = 512u / (uint32_t)CVS;  // positions per step
@@ -173,10 +173,29 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
         for (uint32_t m = 1; m < lanes; m <<= 1) st = stat_merge<S::PRECISE>(st, stat_shfl_xor(st, (int)m));
         if constexpr (SLICED) {
             if (in_range) {
-                const uint64_t first_word = ((uint64_t)sample * g.groups + grp0 + q) * g.slices;
-                uint64_t* words = g.ws_gather + (epoch & 1u) * g.gather_words + first_word;
-                if (j == 0u) publish_slice(words + slice, g.ws_gather + ((epoch & 1u) ^ 1u) * g.gather_words + first_word + slice, st);
-                st = gather_slices<S::PRECISE>(words, g.slices, j, lanes, g.slice_len, g.slice_rest, g.cpg, g.spin_limit, g.ws_error);
+                uint64_t* words = g.ws_gather + (epoch & 1u) * g.gather_words + ((uint64_t)sample * g.groups + grp0 + q) * g.slices;
+                if (j == 0u) {
+                    uint64_t* other = g.ws_gather + ((epoch & 1u) ^ 1u) * g.gather_words + ((uint64_t)sample * g.groups + grp0 + q) * g.slices;
+                    __hip_atomic_store(other + slice, kSlotEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(words + slice, pack_slot(st.mean, st.m2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                st = Stat{0.0f, 0.0f, 0.0f};
+                uint32_t spins = 0;
+                for (uint32_t b = j; b < g.slices; b += lanes) {
+                    uint64_t w;
+                    for (;;) {
+                        w = __hip_atomic_load(words + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (w != kSlotEmpty) break;
+                        if (++spins >= g.spin_limit) {
+                            __hip_atomic_store(g.ws_error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            break;
+                        }
+                        __builtin_amdgcn_s_sleep(8);
+                    }
+                    if (w == kSlotEmpty) continue;
+                    st = stat_merge<S::PRECISE>(st, Stat{(float)((g.slice_len + (b < g.slice_rest ? 1u : 0u)) * g.cpg), __builtin_bit_cast(float, (uint32_t)w),
+                                             __builtin_bit_cast(float, (uint32_t)(w >> 32))});
+                }
             }
             for (uint32_t m = 1; m < lanes; m <<= 1) st = stat_merge<S::PRECISE>(st, stat_shfl_xor(st, (int)m));
         }

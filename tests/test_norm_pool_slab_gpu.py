@@ -98,48 +98,3 @@ def test_repeated_runs_and_replays_of_a_graph():
         torch.cuda.synchronize()
         compare(out.cpu(), want, "f16", f"eager run {rep}")
     plan.close()
-
-
-# slices of a slab: they differ by a position, leave the last step empty, hold groups inside a vector and across two, and are more than
-# the eight words a merging lane has in flight
-@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
-@pytest.mark.parametrize("shape,groups,slab,slices", [((2, 9, 9, 64), 8, 4, 2), ((2, 21, 21, 160), 32, 16, 3), ((1, 12, 11, 64), 4, 2, 5), ((3, 33, 31, 96), 12, 4, 7),
-                                                     ((1, 64, 64, 64), 2, 1, 16), ((2, 8, 8, 256), 16, 16, 64), ((1, 40, 40, 320), 32, 1, 20), ((1, 20, 20, 24), 8, 1, 33)])
-def test_slices(shape, groups, slab, slices, dtype):
-    s, t = _chain(shape, groups, dtype, seed=90)
-    with env(PF_SLAB_GROUPS=str(slab), PF_SLAB_SLICES=str(slices)):
-        _, info, _ = check_chain(s, t, what=f"one launch: groupnorm > silu > mean {shape} / {groups} {dtype}, slabs of {slab} groups, {slices} slices")
-    assert info.n_kernels == 1 and info.n_launches == 1
-
-
-@pytest.mark.parametrize("shape,dtype", [((32, 64, 64, 320), "f16"), ((19, 14, 14, 576), "bf16"), ((4, 64, 64, 672), "f16"), ((2, 64, 64, 160), "bf16")])
-def test_shapes_of_more_than_two_mebibytes(shape, dtype):
-    s, t = _chain(shape, 32, dtype, seed=91)
-    check_chain(s, t, what=f"groupnorm > silu > mean {shape} {dtype}, as planned")
-
-
-def test_slices_run_again_and_replay_from_a_graph():
-    from paper_2307_04995_amd import binding as pf
-    s, t = _chain((2, 24, 24, 160), 32, "f16", seed=92)
-    with env(PF_SLAB_GROUPS="8", PF_SLAB_SLICES="6"):
-        plan = pf.Plan(s, 0)
-    dev = [x.cuda() for x in t]
-    out = torch.empty(plan.output_shapes()[0], dtype=torch.float16, device="cuda")
-    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
-    with torch.cuda.stream(side):
-        plan.run(dev, [out])
-        side.synchronize()
-        with torch.cuda.graph(graph, stream=side):
-            for _ in range(3):  # (an odd number: the replays begin at either parity of the exchange)
-                plan.run_ptrs([x.data_ptr() for x in dev], [out.data_ptr()], torch.cuda.current_stream().cuda_stream)
-    for rep in range(5):
-        x = wl.random_tensor((2, 24, 24, 160), "f16", 6500 + rep)
-        want = oracle_run(s, [x] + t[1:])[0]
-        dev[0].copy_(x)
-        for how in (graph.replay, lambda: plan.run(dev, [out])):
-            out.zero_()
-            how()
-            torch.cuda.synchronize()
-            compare(out.cpu(), want, "f16", f"run {rep}")
-    assert plan.poll_error() == 0
-    plan.close()
