@@ -1029,8 +1029,9 @@ pf_status plan_group(pf_plan_s* p, int forced_variant) {
     if (nv == 0) return fail(PF_ERR_INVALID_ARG, "PF_GROUP_NV must be 4, 8 or 16");
     // (nothing but the load in front: steps there would be run by every pass over the held values)
     if (forced_variant != PF_VARIANT_GROUP_TWO_PASS && L.n_full == 1 && g.vec_per_channel && L.pro.n == 1 && L.pro.u[0].code == pf::U_MOV && L.pro.u[0].kind == pf::K_FULL) {
+        // (a sample of more tiles than are resident at once is two launches, which can be recorded and wait for nobody: it stays so)
         const int64_t tiles_now = (int64_t)bps * samples, at_once = 2 * (int64_t)n_cu / bps * bps;
-        if (plan_group_slab(p, n_cu, samples, hw, C, tiles_now, bps, at_once > 0 ? (tiles_now + at_once - 1) / at_once : 2)) return PF_OK;
+        if (at_once > 0 && plan_group_slab(p, n_cu, samples, hw, C, tiles_now, bps, (tiles_now + at_once - 1) / at_once)) return PF_OK;
     }
     // resident variant: catalogue entry, one full operand, per-channel broadcast operands only, and a grid the
     // device holds at once
