@@ -1463,6 +1463,30 @@ static bool plan_norm_pool_slab(pf_plan_s* p, int n_cu) {
         const double cost = 9.0 + (double)(rounds * nv) * (per_cu == 2 && slabs > n_cu ? 1.8 : 0.87);
         if (cost < best || (forced && best_d == 0)) best = cost, best_d = d, best_cvs = cvs, best_nv = nv;
     }
+    // 16-bit tensors of more than 2 MiB: slabs that leave units idle as well, at most one to a unit, where a model of that launch is 8 %
+    // ahead of the two launches' (fitted to 270 measured slabs of 26 shapes, 5 % off in the mean; [13, 50, 50, 576] bf16 30.8 in one launch, 28.3
+    // in two, 7 % ahead by the models).  us, fp16 or bf16, before and
+    // now: [21, 28, 28, 64] 13.7 -> 8.8, [19, 14, 14, 576] 13.3 -> 9.3, [28, 18, 18, 416] 15.4 -> 10.6, [23, 32, 32, 992] 39.5 -> 32.0, [8, 56, 56,
+    // 256] 18.0 -> 14.0.  Smaller tensors would gain as well ([1, 7, 7, 128] 9.8, 8.7 in one launch), but that they are two launches is
+    // relied upon.  (Slices of a slab that exchange their statistics gain more where slabs are few -- [4, 64, 64, 672] 25.7 -> 20.8 -- but all
+    // workgroups of a launch then wait for one another: two such launches on two streams, each with half of the units, would wait in vain.)
+    if (!forced && es == 2 && n * hw * ch * es > (2 << 20)) {
+        const double mb = (double)(n * hw * ch * es) * 1e-6;
+        double least = 0.92 * (12.4 - 0.37 * (double)(n * ((hw + 512 / cv - 1) / (512 / cv))) / (double)n_cu + 0.68 * mb);
+        for (int64_t d = 1; d <= groups && d <= 512; ++d) {
+            if (groups % d != 0) continue;
+            const int64_t slabs = n * (groups / d), sc = d * cpg, bytes = sc * es;
+            int64_t cvs = 0;
+            for (int64_t lo = 0; lo < ch; lo += sc) cvs = std::max(cvs, (lo + sc - 1) / vec - lo / vec + 1);
+            if (cvs * vec > 512 || slabs > n_cu) continue;
+            const int64_t pps = 512 / cvs, nv = (hw + pps - 1) / pps;
+            if (nv > 44) continue;
+            const bool lines = (bytes % 128 == 0 && (ch * es) % 128 == 0) || d == groups;
+            const double waste = lines ? 0.0 : std::min(3.0, 112.0 / (double)bytes);  // (of the memory lines a position's share touches)
+            const double us = 5.8 + mb * (0.082 + 0.05 * waste) + 0.66 * (double)nv + 0.15 * std::log2((double)pps);
+            if (us < least) least = us, best_d = d, best_cvs = cvs, best_nv = nv;
+        }
+    }
     if (best_d == 0) return false;
     pf::SlabGeom g;
     memset(&g, 0, sizeof(g));

@@ -98,3 +98,10 @@ def test_repeated_runs_and_replays_of_a_graph():
         torch.cuda.synchronize()
         compare(out.cpu(), want, "f16", f"eager run {rep}")
     plan.close()
+
+
+@pytest.mark.parametrize("shape,dtype", [((32, 64, 64, 320), "f16"), ((19, 14, 14, 576), "bf16"), ((21, 28, 28, 64), "f16"), ((23, 32, 32, 992), "bf16"), ((8, 56, 56, 256), "bf16")])
+def test_shapes_of_more_than_two_mebibytes(shape, dtype):
+    s, t = _chain(shape, 32, dtype, seed=91)
+    _, info, _ = check_chain(s, t, what=f"groupnorm > silu > mean {shape} {dtype}, as planned")
+    assert info.n_kernels == 1 and info.workspace_bytes == 0
