@@ -203,7 +203,8 @@ typedef struct {
 #define PF_VARIANT_ROW_BLOCK 1        /* row family: one workgroup owns a row                                */
 #define PF_VARIANT_ROW_STREAM 2       /* row family: a workgroup owns a long row: held packed, else walked twice */
 #define PF_VARIANT_GROUP_TWO_PASS 0   /* group family: statistics pass, then normalise pass (re-reads x)     */
-#define PF_VARIANT_GROUP_RESIDENT 1   /* group family: x held in registers across a device-scope exchange    */
+#define PF_VARIANT_GROUP_RESIDENT 1   /* group family: x held in registers, in one launch: across a device-scope exchange, or
+                                         (small calls, no workspace) a slab of whole groups to a workgroup    */
 #define PF_VARIANT_T_ROWS 0           /* transpose family: innermost dim kept, 16-byte vectors re-addressed  */
 #define PF_VARIANT_T_LDS_ROWS 1       /* transpose family: innermost dim kept, LDS tile makes both sides long*/
 #define PF_VARIANT_T_TILE 2           /* transpose family: innermost dim changes, square tiles, blocks of elements

@@ -224,7 +224,7 @@ pf_status partition_chain(const pf_chain_desc* user, const Checked& c, const std
 // instead of nine times its bytes ([32, 64, 64, 320] fp16, GroupNorm + SiLU + mean over positions).  Their element-wise steps
 // stay as exact as the fp32 kernels' that the general split runs (StaticSpec::kPrecise: the 16-bit kernels' quick forms, which
 // a rounding to 16 bits would hide where it follows at once, are off by 1e-3 of a tanh near zero): that call 262 us split, 46.8
-// with the quick forms, 70.0 with the library's, 48.9 with pf_sigmoid_reduced; 44.6 where one launch does both.  Needs kernels specialised for the chain.  PF_ERR_UNSUPPORTED leaves the chain to the general split.
+// with the quick forms, 70.0 with the library's, 48.9 with pf_sigmoid_reduced; 41.5 where one launch does both.  Needs kernels specialised for the chain.  PF_ERR_UNSUPPORTED leaves the chain to the general split.
 static pf_status plan_norm_pool(const pf_chain_desc* user, const Checked& c, int32_t device, pf_plan_s* p) {
     int norm = -1, core2 = -1;
     for (int k = 0; k < user->n_ops; ++k) {
