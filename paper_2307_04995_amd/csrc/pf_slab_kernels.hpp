@@ -232,6 +232,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
     for (int i = 0; i < NV; ++i) {
         float x[VEC];
         S::unpack(raw[i], x);
+        s.fraw[P::at(0).slot][0] = raw[i];  // (the steps behind may read the input again: x + norm(x))
 #pragma unroll
         for (int e = 0; e < VEC; ++e) s.acc[e] = __builtin_fmaf(kCentre ? x[e] - M[e] : x[e], A[e], B[e]);
         run_program<DT, 1, Spec>(ProgView<typename Spec::Epi>{a.epi}, s, NoStore{});

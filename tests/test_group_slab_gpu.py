@@ -20,6 +20,20 @@ def _chain(shape, groups, dtype, act="silu", seed=0, bias=False):
     return s, t + ([wl.random_tensor((c,), dtype, 7303 + seed)] if bias else [])
 
 
+def _slabs(shape, groups, dtype, slab, slices):
+    """(vectors per lane, workgroups, bytes of workspace) of a plan of these slabs and slices; the kernel of whole positions has a
+    workspace of 256 bytes at least, and 4, 8, 12 or 16 vectors a lane."""
+    vec, samples, positions = (4 if dtype == "f32" else 8), shape[0], int(np.prod(shape[1:-1]))
+    per_step = 512 // (slab * (shape[-1] // groups) // vec)
+    up = lambda n: (n + 255) // 256 * 256
+    blocks = samples * (groups // slab) * slices
+    return -(-(-(-positions // slices)) // per_step), -(-blocks // 8) * 8, up(16 * samples * groups * slices) + up(4 * blocks) + 256 if slices > 1 else 0
+
+
+def _taken(info):
+    return info.vectors_per_lane, info.grid[0], info.workspace_bytes
+
+
 # slab and slices: one position, steps that end inside and at the last position, lanes that are not a divisor of 512, groups inside a
 # vector and across two, odd channels to a group, slices that differ by a position and leave the last step empty
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
@@ -79,3 +93,28 @@ def test_repeated_runs_in_place_and_after_a_wait_that_gave_up():
     torch.cuda.synchronize()
     assert hasty.poll_error() in (0, 1) and hasty.poll_error() == 0
     hasty.close()
+
+
+# the input behind its own normalisation: the value that the kernel holds, for each of its vectors (inputs of a quarter: no result
+# reaches 8, from where half a unit of bf16's last place, 2^-5, is more than the bar of 2e-2)
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("behind", ["add", "gate"])
+@pytest.mark.parametrize("shape,groups,slab,slices", [((3, 10, 10, 96), 8, 8, 1), ((2, 13, 7, 64), 8, 2, 1), ((2, 21, 21, 160), 32, 16, 3), ((1, 33, 31, 64), 8, 4, 8)])
+def test_the_input_behind_its_own_normalisation(shape, groups, slab, slices, behind, dtype):
+    c = shape[-1]
+    s = wl.ChainSpec(inputs=[(dtype, shape), (dtype, (c,)), (dtype, (c,))])
+    v = s.op("groupnorm", 0, 1, 2, f=[1e-5], i=[groups])
+    s.out(s.op("add", v, 0) if behind == "add" else s.op("mul", s.op("sigmoid", v), 0), dtype)
+    t = [wl.random_tensor(shape, dtype, 7500, scale=0.25), wl.random_tensor((c,), dtype, 7501, dist="positive"), wl.random_tensor((c,), dtype, 7502, scale=0.5)]
+    with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS=str(slab), PF_SLAB_SLICES=str(slices)):
+        _, info, _ = check_chain(s, t, what=f"{behind} of x and groupnorm(x) {shape} {dtype}, {slices} slices")
+    assert _taken(info) == _slabs(shape, groups, dtype, slab, slices)
+
+
+@pytest.mark.parametrize("shape,dtype", [((31, 10, 10, 96), "f16"), ((1, 56, 56, 416), "f32"), ((4, 64, 64, 224), "bf16")])
+def test_the_input_behind_its_own_normalisation_as_planned(shape, dtype):
+    c = shape[-1]
+    s = wl.ChainSpec(inputs=[(dtype, shape), (dtype, (c,)), (dtype, (c,))])
+    s.out(s.op("add", 0, s.op("groupnorm", 0, 1, 2, f=[1e-5], i=[32])), dtype)
+    t = [wl.random_tensor(shape, dtype, 7510, scale=0.25), wl.random_tensor((c,), dtype, 7511, dist="positive"), wl.random_tensor((c,), dtype, 7512, scale=0.5)]
+    check_chain(s, t, what=f"x + groupnorm(x) {shape} {dtype}")
