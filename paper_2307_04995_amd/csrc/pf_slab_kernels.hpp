@@ -54,7 +54,6 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
         raw[i] = *reinterpret_cast<const u32x4*>(base + (size_t)((i + 1 < NV ? (uint32_t)i : last_step) * step_bytes) + (i + 1 < NV || last_valid ? lane_bytes : first_bytes));
     LaneState<DT, 1, Spec> s;
     s.col[0] = ch;
-    s.row[0] = 0u;
     constexpr int gs = Spec::kGamma, bs = Spec::kBeta;
 #pragma unroll
     for (int v = 0; v < Spec::NV; ++v) s.vraw[v][0] = load_vec_operand<DT, Spec::kVecMode>(a.vec[v], 0u, active ? ch : v0 * (uint32_t)VEC, g.channels);
@@ -233,6 +232,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
         float x[VEC];
         S::unpack(raw[i], x);
         s.fraw[P::at(0).slot][0] = raw[i];  // (the steps behind may read the input again: x + norm(x))
+        s.row[0] = sample * g.hw + p_begin + (uint32_t)i * PPS + pstep;  // (a mask reads the position)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) s.acc[e] = __builtin_fmaf(kCentre ? x[e] - M[e] : x[e], A[e], B[e]);
         run_program<DT, 1, Spec>(ProgView<typename Spec::Epi>{a.epi}, s, NoStore{});

@@ -118,3 +118,16 @@ def test_the_input_behind_its_own_normalisation_as_planned(shape, dtype):
     s.out(s.op("add", 0, s.op("groupnorm", 0, 1, 2, f=[1e-5], i=[32])), dtype)
     t = [wl.random_tensor(shape, dtype, 7510, scale=0.25), wl.random_tensor((c,), dtype, 7511, dist="positive"), wl.random_tensor((c,), dtype, 7512, scale=0.5)]
     check_chain(s, t, what=f"x + groupnorm(x) {shape} {dtype}")
+
+
+# a mask behind the normalisation: the position of each vector
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("shape,groups,slab,slices", [((3, 10, 40, 96), 8, 8, 1), ((2, 91, 64), 8, 2, 1), ((2, 9, 49, 160), 32, 16, 3), ((1, 33, 31, 64), 8, 4, 8)])
+def test_a_mask_behind_the_normalisation(shape, groups, slab, slices, dtype):
+    c = shape[-1]
+    s = wl.ChainSpec(inputs=[(dtype, shape), (dtype, (c,)), (dtype, (c,))])
+    s.out(s.op("causal_mask", s.op("groupnorm", 0, 1, 2, f=[1e-5], i=[groups])), dtype)
+    t = [wl.random_tensor(shape, dtype, 7520), wl.random_tensor((c,), dtype, 7521, dist="positive"), wl.random_tensor((c,), dtype, 7522, scale=0.5)]
+    with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS=str(slab), PF_SLAB_SLICES=str(slices)):
+        _, info, _ = check_chain(s, t, what=f"causal mask of groupnorm {shape} {dtype}, {slices} slices")
+    assert _taken(info) == _slabs(shape, groups, dtype, slab, slices)
