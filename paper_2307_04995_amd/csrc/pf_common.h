@@ -79,6 +79,11 @@ struct FastDiv {
     uint32_t m, s1, s2, d;
 };
 
+constexpr uint32_t quotient(uint32_t n, const FastDiv& f) {
+    const uint32_t t = (uint32_t)(((uint64_t)f.m * n) >> 32);
+    return (t + ((n - t) >> f.s1)) >> f.s2;
+}
+
 // A broadcast operand with `numel` elements laid over a value whose innermost extent is n_inner:
 //   numel >= n_inner (numel = m * n_inner): element (row, col) reads vec[(row % m) * n_inner + col]
 //   numel <  n_inner (n_inner % numel == 0): reads vec[col % numel]; numel == 1 is a scalar.
@@ -203,6 +208,7 @@ struct GroupSlabGeom {
     uint32_t hw, channels, groups, cpg;  // cpg: channels per group
     uint32_t slab_groups, slabs_per_sample;
     uint32_t slices;                     // workgroups that share a (sample, slab)
+    FastDiv div_run, div_sample, div_run_slabs;  // workgroups of a run, runs of a sample, slabs of a run (group_slab_place)
     uint32_t slice_len, slice_rest;      // positions of a slice; the first slice_rest slices have one more
     uint32_t blocks, blocks_per_die;
     uint32_t parts;       // the most groups one vector touches
@@ -215,6 +221,25 @@ struct GroupSlabGeom {
     uint32_t* ws_epoch;      // [blocks] launches so far
     uint32_t* ws_error;      // set to 1 if a wait ran out
 };
+
+// Its workgroups in dispatch order: consecutive ones go to the eight dies in turn, a die's range is contiguous, and within it come runs of
+// run_slabs slabs of a sample, slice by slice (neighbouring slabs share memory lines).  So a die whose units are shared with other
+// launches holds at most one run of this launch that waits for workgroups not yet dispatched.
+struct GroupSlabPlace {
+    uint32_t at, sample, slab, slice;  // at >= blocks: nothing to do (the grid is rounded up to a multiple of eight)
+};
+template <bool SLICED, class Div>
+constexpr GroupSlabPlace group_slab_place(uint32_t block, uint32_t blocks_per_die, const Div& per_run, const Div& per_sample, const Div& run_slabs) {
+    const uint32_t at = (block & 7u) * blocks_per_die + (block >> 3), run = SLICED ? quotient(at, per_run) : at, in_run = SLICED ? at - run * per_run.d : 0u;
+    const uint32_t sample = quotient(run, per_sample), slice = SLICED ? quotient(in_run, run_slabs) : 0u;
+    return GroupSlabPlace{at, sample, (run - sample * per_sample.d) * (SLICED ? run_slabs.d : 1u) + in_run - slice * run_slabs.d, slice};
+}
+// Whether two such launches that share the device always end: an incomplete run holds all but one of its workgroups in a die's places at most
+// (and no more than the launch has there), so two of them leave a place free, which completes the one or the other; or both fit whole.
+constexpr bool group_slab_shares(uint32_t run_blocks, uint32_t blocks_per_die, uint32_t places_per_die) {
+    const uint32_t held = run_blocks - 1u < blocks_per_die ? run_blocks - 1u : blocks_per_die;
+    return 2u * held < places_per_die || 2u * blocks_per_die <= places_per_die;
+}
 
 // Pool family, GroupNorm and pooling in one launch: a workgroup holds all positions of a slab of whole groups.
 struct SlabGeom {

@@ -845,7 +845,7 @@ static bool plan_group_slab(pf_plan_s* p, int n_cu, int64_t n, int64_t hw, int64
     const bool sliced_pays = rounds > 1 || (es == 4 ? tiles_per_sample > 42 : tiles_per_sample > 48 && tiles <= n_cu);
     struct Pick {
         double cost;
-        int64_t d, nv, slices;
+        int64_t d, nv, slices, blocks;
     };
     std::vector<Pick> picks;
     for (int64_t d = 1; d <= groups && d <= 512; ++d) {
@@ -861,25 +861,39 @@ static bool plan_group_slab(pf_plan_s* p, int n_cu, int64_t n, int64_t hw, int64
             if (nv > 44 || (nv - 1) * pps > hw / slices || blocks > 0x7fffff) continue;  // (every step of every slice but the last is whole)
             const bool small = slices == 1 && nv <= 6, large = sliced_pays && width >= 64;
             if ((blocks > n_cu || !(small || large)) && !forced) continue;
+            // (more than 16 vectors a lane are taken for one workgroup to a unit: not compiled where two launches could not share the device)
+            if (slices > 1 && nv > 16 && !pf::group_slab_shares((uint32_t)slices, (uint32_t)((blocks + 7) / 8), (uint32_t)n_cu / 8)) continue;
             // microseconds beside what the bytes cost, fitted to the pairs of at most one workgroup to a unit
             const double cost = (double)nv * ((es == 4 ? 0.25 : 0.165) + 0.044 * waste) + 0.11 * std::log2((double)pps) + (slices > 1 ? 1.97 + 0.0515 * (double)slices : 0.0);
-            picks.push_back(Pick{cost, d, nv, slices});
+            picks.push_back(Pick{cost, d, nv, slices, blocks});
         }
     }
     std::sort(picks.begin(), picks.end(), [](const Pick& x, const Pick& y) { return x.cost < y.cost; });
+    pf::GroupSlabGeom& g = p->gslab;
+    memset(&g, 0, sizeof(g));
     hipFunction_t fn = nullptr;
     std::string err;
-    // (a kernel whose vectors do not fit the registers is passed over, three at most: each is compiled first)
+    g.parts = 1;
+    for (int64_t v = 0; v < ch / vec; ++v) g.parts = std::max<uint32_t>(g.parts, (uint32_t)((v * vec + vec - 1) / cpg - v * vec / cpg + 1));
+    const uint32_t dyn_lds = 512u * 3u * g.parts * 4u;
+    // A kernel whose vectors do not fit the registers is passed over, three at most: each is compiled first.  Slices wait for one another:
+    // all workgroups of the launch have to be resident, and two such launches on two streams must not hold the device in vain.  Any order
+    // of the workgroups does where both fit; else as many slabs of a sample are dispatched together as may be (neighbours share memory lines:
+    // in runs of one slab [1, 56, 56, 416] fp32 takes 12.2 us, 10.3 in runs of 32).  That leaves 16 slices to a launch that fills the units
+    // one to each: [5, 128, 128, 416] fp16 45.4 us, 38.1 in 25 slices, [3, 96, 96, 1120] 40.2, 35.2 in 21 (65.0 and 76.2 by whole positions).
     size_t at = 0;
+    uint32_t run_slabs = 1;
     for (; at < picks.size() && at < 3; ++at) {
         fn = pf::jit_group_slab_kernel(p->device, L.main_dtype, (int)picks[at].nv, (int)(picks[at].d * cpg / vec), picks[at].slices > 1, es == 2 && cpg % 2 == 0, make_jit_spec(L), &err);
-        if (fn && pf::jit_scratch_bytes(fn) == 0) break;
+        const uint32_t per_die = (uint32_t)((picks[at].blocks + 7) / 8), places = fn ? (uint32_t)(std::max(pf::jit_blocks_per_cu(fn, 512, dyn_lds), 0) * n_cu / 8) : 0u;
+        const uint32_t slabs = (uint32_t)(groups / picks[at].d), slices = (uint32_t)picks[at].slices;
+        run_slabs = slices == 1u ? 1u : slabs;
+        while (run_slabs > 1u && (slabs % run_slabs != 0u || !pf::group_slab_shares(run_slabs * slices, per_die, places))) --run_slabs;
+        if (fn && pf::jit_scratch_bytes(fn) == 0 && (slices == 1u || (per_die <= places && pf::group_slab_shares(run_slabs * slices, per_die, places)))) break;
         fn = nullptr;
     }
     if (!fn) return false;
     const int64_t best_d = picks[at].d, best_nv = picks[at].nv, best_slices = picks[at].slices;
-    pf::GroupSlabGeom& g = p->gslab;
-    memset(&g, 0, sizeof(g));
     g.hw = (uint32_t)hw;
     g.channels = (uint32_t)ch;
     g.groups = (uint32_t)groups;
@@ -888,17 +902,16 @@ static bool plan_group_slab(pf_plan_s* p, int n_cu, int64_t n, int64_t hw, int64
     g.slab_groups = (uint32_t)best_d;
     g.slabs_per_sample = (uint32_t)(groups / best_d);
     g.slices = (uint32_t)best_slices;
+    g.div_run = make_fastdiv(run_slabs * g.slices);
+    g.div_sample = make_fastdiv(g.slabs_per_sample / run_slabs);
+    g.div_run_slabs = make_fastdiv(run_slabs);
     g.slice_len = (uint32_t)(hw / best_slices);
     g.slice_rest = (uint32_t)(hw % best_slices);
     g.blocks = (uint32_t)(n * g.slabs_per_sample * best_slices);
     g.blocks_per_die = (g.blocks + 7u) / 8u;
-    g.parts = 1;
-    for (int64_t v = 0; v < ch / vec; ++v) g.parts = std::max<uint32_t>(g.parts, (uint32_t)((v * vec + vec - 1) / cpg - v * vec / cpg + 1));
     while (g.log2_lanes < 6u && (best_d << (g.log2_lanes + 1)) <= 512) ++g.log2_lanes;
-    const uint32_t dyn_lds = 512u * 3u * g.parts * 4u, grid = g.blocks_per_die * 8u;
+    const uint32_t grid = g.blocks_per_die * 8u;
     if (best_slices > 1) {
-        // every wait is for workgroups of the same launch: all of them have to be resident
-        if ((int64_t)pf::jit_blocks_per_cu(fn, 512, dyn_lds) * n_cu < (int64_t)grid) return false;
         g.spin_limit = (uint32_t)env_int("PF_GROUP_SPIN_LIMIT", 1 << 22);
         g.gather_words = (uint32_t)(n * groups * best_slices);
         const uint64_t gather_bytes = ((uint64_t)2 * g.gather_words * sizeof(uint64_t) + 255) / 256 * 256, epochs = ((uint64_t)g.blocks * sizeof(uint32_t) + 255) / 256 * 256;
@@ -1469,7 +1482,8 @@ static bool plan_norm_pool_slab(pf_plan_s* p, int n_cu) {
     // now: [21, 28, 28, 64] 13.7 -> 8.8, [19, 14, 14, 576] 13.3 -> 9.3, [28, 18, 18, 416] 15.4 -> 10.6, [23, 32, 32, 992] 39.5 -> 32.0, [8, 56, 56,
     // 256] 18.0 -> 14.0.  Smaller tensors would gain as well ([1, 7, 7, 128] 9.8, 8.7 in one launch), but that they are two launches is
     // relied upon.  (Slices of a slab that exchange their statistics gain more where slabs are few -- [4, 64, 64, 672] 25.7 -> 20.8 -- but all
-    // workgroups of a launch then wait for one another: two such launches on two streams, each with half of the units, would wait in vain.)
+    // workgroups of a launch then wait for one another: two such launches on two streams, each with half of the units, would wait in vain,
+    // dispatched as they were; in runs of slabs, as the slices of the group family are now, they were not tried.)
     if (!forced && es == 2 && n * hw * ch * es > (2 << 20)) {
         const double mb = (double)(n * hw * ch * es) * 1e-6;
         double least = 0.92 * (12.4 - 0.37 * (double)(n * ((hw + 512 / cv - 1) / (512 / cv))) / (double)n_cu + 0.68 * mb);

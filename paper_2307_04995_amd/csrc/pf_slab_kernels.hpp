@@ -14,7 +14,8 @@ namespace pf {
 // general group kernels.  They are merged as (count, mean, M2) triples, one per group the vector touches.
 //
 // Exchange (SLICED): as in group_kernel, self-describing words in two parities, with the launch's number kept on the device: a word of the
-// workgroup's own, which nobody else touches.  All workgroups of a launch with slices are resident together.
+// workgroup's own, which nobody else touches.  All workgroups of a launch with slices are resident together on an idle device; where
+// two such launches share it, the order of the workgroups (group_slab_place) lets runs of slabs complete and make room.
 template <int DT, int NV, int CVS, class Spec, bool SLICED, bool PACKED>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 16 ? 2 : 4))) group_slab_kernel(const ChainArgs a, const GroupSlabGeom g) {
     using S = Storage<DT>;
@@ -24,10 +25,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
     __shared__ float lds_stat[2 * 512];
     using P = typename Spec::Pro;
     static_assert(Spec::kStatic && P::n == 1 && P::at(0).code == U_MOV && P::at(0).kind == K_FULL, "nothing but the load in front");
-    const uint32_t at = (blockIdx.x & 7u) * g.blocks_per_die + (blockIdx.x >> 3);
+    // What the address of the first load takes of the arguments, asked for together: where the compiler places them they are up to four
+    // trips to memory, one behind the other (0.2 to 0.4 us of every call: [1, 64, 64, 448] fp32 11.4 -> 11.0, [2, 72, 72, 544] bf16 16.4 -> 15.7)
+    asm volatile("" ::"s"(a.full[P::at(0).slot]), "s"(g.hw), "s"(g.channels), "s"(g.cpg), "s"(g.slab_groups), "s"(g.blocks), "s"(g.blocks_per_die), "s"(g.div_sample.m));
+    if (SLICED) asm volatile("" ::"s"(g.slice_len), "s"(g.slice_rest), "s"(g.div_run.m), "s"(g.div_run_slabs.m), "s"(g.ws_epoch));
+    const GroupSlabPlace place = group_slab_place<SLICED>(blockIdx.x, g.blocks_per_die, g.div_run, g.div_sample, g.div_run_slabs);
+    const uint32_t at = place.at, sample = place.sample, in_sample = place.slab, slice = place.slice;
     if (at >= g.blocks) return;  // (the grid is rounded up to a multiple of eight)
-    const uint32_t row = at / g.slabs_per_sample, in_sample = at - row * g.slabs_per_sample;
-    const uint32_t sample = SLICED ? row / g.slices : row, slice = SLICED ? row - sample * g.slices : 0u;
     const uint32_t p_begin = SLICED ? slice * g.slice_len + min(slice, g.slice_rest) : 0u;
     const uint32_t p_count = SLICED ? g.slice_len + (slice < g.slice_rest ? 1u : 0u) : g.hw;
     const uint32_t epoch = SLICED ? g.ws_epoch[at] : 0u;
@@ -227,6 +231,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
         }
     }
     char* out_base = static_cast<char*>(a.out[0]) + slice_bytes;
+    // (multiplied anew: kept from the loads, the steps' offsets need more scalar registers than there are)
+    uint32_t out_step_bytes = step_bytes;
+    asm volatile("" : "+s"(out_step_bytes));
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         float x[VEC];
@@ -236,7 +243,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
 #pragma unroll
         for (int e = 0; e < VEC; ++e) s.acc[e] = __builtin_fmaf(kCentre ? x[e] - M[e] : x[e], A[e], B[e]);
         run_program<DT, 1, Spec>(ProgView<typename Spec::Epi>{a.epi}, s, NoStore{});
-        if (i + 1 < NV ? active : last_valid) *reinterpret_cast<u32x4*>(out_base + (size_t)((uint32_t)i * step_bytes) + lane_bytes) = S::pack(s.acc);
+        if (i + 1 < NV ? active : last_valid) *reinterpret_cast<u32x4*>(out_base + (size_t)((uint32_t)i * out_step_bytes) + lane_bytes) = S::pack(s.acc);
     }
 }
 

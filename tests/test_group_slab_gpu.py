@@ -48,6 +48,15 @@ def test_slabs_and_slices(shape, groups, slab, slices, dtype):
     assert info.n_launches == 1
 
 
+def test_runs_of_slabs():
+    # more than 16 vectors a lane, nearly as many workgroups as units: the slices of four slabs of eight are dispatched together
+    shape = (10, 53, 60, 512)
+    s, t = _chain(shape, 8, "f16", seed=5)
+    with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS="1", PF_SLAB_SLICES="3"):
+        _, info, _ = check_chain(s, t, what="groupnorm + silu in runs of four slabs")
+    assert _taken(info) == _slabs(shape, 8, "f16", 1, 3) == (17, 240, info.workspace_bytes)
+
+
 @pytest.mark.parametrize("dtype", ["f16", "f32"])
 def test_operands_behind_and_a_large_offset(dtype):
     from paper_2307_04995_amd import binding as pf
