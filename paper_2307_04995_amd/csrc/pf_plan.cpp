@@ -1040,12 +1040,18 @@ pf_status plan_group(pf_plan_s* p, int forced_variant) {
         }
     }
     if (nv == 0) return fail(PF_ERR_INVALID_ARG, "PF_GROUP_NV must be 4, 8 or 16");
-    // (nothing but the load in front: steps there would be run by every pass over the held values)
-    if (forced_variant != PF_VARIANT_GROUP_TWO_PASS && L.n_full == 1 && g.vec_per_channel && L.pro.n == 1 && L.pro.u[0].code == pf::U_MOV && L.pro.u[0].kind == pf::K_FULL) {
-        // (a sample of more tiles than are resident at once is two launches, which can be recorded and wait for nobody: it stays so)
+    // Slabs of whole groups: nothing but the load in front (steps there would be run by every pass over the held values), and a sample that the
+    // one-launch kernel holds at once, two workgroups to a unit.  (Larger ones are two launches, which can be recorded and wait for nobody: they
+    // stay so.)  Tiles of 16 steps become tiles of 12 where the kernel spills: with samples that do not fit as such, that kernel decides first.
+    auto try_slabs = [&]() {
         const int64_t tiles_now = (int64_t)bps * samples, at_once = 2 * (int64_t)n_cu / bps * bps;
-        if (at_once > 0 && plan_group_slab(p, n_cu, samples, hw, C, tiles_now, bps, (tiles_now + at_once - 1) / at_once)) return PF_OK;
-    }
+        return at_once > 0 && plan_group_slab(p, n_cu, samples, hw, C, tiles_now, bps, (tiles_now + at_once - 1) / at_once);
+    };
+    const bool slabs_may = forced_variant != PF_VARIANT_GROUP_TWO_PASS && L.n_full == 1 && g.vec_per_channel && L.pro.n == 1 && L.pro.u[0].code == pf::U_MOV && L.pro.u[0].kind == pf::K_FULL;
+    uint32_t bps_of_12;
+    tiling(12, &bps_of_12);
+    const bool tiles_settled = nv != 16 || p->spec_id != 0 || bps_of_12 <= 2u * (uint32_t)n_cu;
+    if (slabs_may && tiles_settled && try_slabs()) return PF_OK;
     // resident variant: catalogue entry, one full operand, per-channel broadcast operands only, and a grid the
     // device holds at once
     const bool jit_ok = p->spec_id == 0 && jit_possible(p->device);
@@ -1072,6 +1078,7 @@ pf_status plan_group(pf_plan_s* p, int forced_variant) {
         }
         if (!fused_fn) resident_ok = false;
     }
+    if (slabs_may && !tiles_settled && resident_ok && try_slabs()) return PF_OK;
     const uint64_t tiles = (uint64_t)bps * samples;
     if (tiles > 0x7fffffffull) return fail(PF_ERR_UNSUPPORTED, "tensor too large for the group family");
     uint32_t res_grid = 0;

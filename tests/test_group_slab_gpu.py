@@ -140,3 +140,15 @@ def test_a_mask_behind_the_normalisation(shape, groups, slab, slices, dtype):
     with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS=str(slab), PF_SLAB_SLICES=str(slices)):
         _, info, _ = check_chain(s, t, what=f"causal mask of groupnorm {shape} {dtype}, {slices} slices")
     assert _taken(info) == _slabs(shape, groups, dtype, slab, slices)
+
+
+def test_a_sample_that_does_not_fit_at_once_stays_two_launches():
+    # 400 tiles of 16 steps, but the kernel of these steps needs more registers than it has with 16: 534 tiles of 12 are more than two to a
+    # unit, so the call is two launches, which can be recorded
+    shape, groups = (1, 160, 160, 512), 32
+    s = wl.ChainSpec(inputs=[("f32", shape)] + [("f32", (512,))] * 4)
+    v = s.op("groupnorm", 0, 1, 2, f=[1e-5], i=[groups])
+    s.out(s.op("gelu_erf", s.op("add", s.op("mul", v, 3), 4)), "f32")
+    t = [wl.random_tensor(shape, "f32", 7600)] + [wl.random_tensor((512,), "f32", 7601 + k, dist="positive", scale=0.5) for k in range(4)]
+    _, info, _ = check_chain(s, t, what="groupnorm, scale, shift, gelu of a sample of 400 tiles")
+    assert info.n_launches == 2
