@@ -9,7 +9,7 @@
 
 namespace pf {
 
-// Statistics: per element slot the mean over the lane's positions, then the squared deviations from it; PACKED (16-bit storage, an even
+// Statistics: per element slot the mean over the lane's positions (its first value and the mean distance from that), then the squared deviations from it; PACKED (16-bit storage, an even
 // number of channels to a group, nothing but the load in front): sums and sums of squares per pair of elements, as in the
 // general group kernels.  They are merged as (count, mean, M2) triples, one per group the vector touches.
 //
@@ -104,17 +104,21 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
                 m2_e[j] = fmaxf(m2_e[j] - sum * mean_e[j], 0.0f);
             }
         } else {
+            // From the lane's first value on: a sum times the rounded reciprocal of seven is off the same way in every lane (fp32 around 1000: the
+            // mean by 0.7 of its last place), and equal values would not be their own mean.
+            float first_x[VEC];
+            S::unpack(raw[0], first_x);
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
                 float x[VEC];
                 S::unpack(raw[i], x);
                 if (i + 1 < NV || last_valid) {
 #pragma unroll
-                    for (int e = 0; e < SLOTS; ++e) mean_e[e] += x[e];
+                    for (int e = 0; e < SLOTS; ++e) mean_e[e] += x[e] - first_x[e];
                 }
             }
 #pragma unroll
-            for (int e = 0; e < SLOTS; ++e) mean_e[e] *= inv;
+            for (int e = 0; e < SLOTS; ++e) mean_e[e] = npos > 0.0f ? __builtin_fmaf(mean_e[e], inv, first_x[e]) : 0.0f;
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
                 keep_packed(i);

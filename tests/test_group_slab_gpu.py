@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import workloads as wl
-from pf_testlib import check_chain, compare, env, oracle_run
+from pf_testlib import check_chain, compare, env, gpu_run, oracle_run
 
 pytestmark = pytest.mark.gpu
 
@@ -152,3 +152,28 @@ def test_a_sample_that_does_not_fit_at_once_stays_two_launches():
     t = [wl.random_tensor(shape, "f32", 7600)] + [wl.random_tensor((512,), "f32", 7601 + k, dist="positive", scale=0.5) for k in range(4)]
     _, info, _ = check_chain(s, t, what="groupnorm, scale, shift, gelu of a sample of 400 tiles")
     assert info.n_launches == 2
+
+
+# seven, three and fourteen positions to a lane; a group of equal values is centred to zero exactly, so the result is beta
+@pytest.mark.parametrize("shape,groups,slab,slices", [((4, 64, 64, 224), 32, 4, 8), ((1, 56, 56, 416), 32, 4, 26), ((2, 21, 21, 64), 8, 8, 1)])
+def test_equal_values_are_their_own_mean(shape, groups, slab, slices):
+    c = shape[-1]
+    s, t = _chain(shape, groups, "f32", act="none", seed=50)
+    level = np.random.default_rng(7700).uniform(500.0, 1000.0, (shape[0], 1, 1, groups, 1)).astype(np.float32)
+    t[0] = torch.from_numpy(np.broadcast_to(level, shape[:-1] + (groups, c // groups)).reshape(shape).copy())
+    with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS=str(slab), PF_SLAB_SLICES=str(slices)):
+        outs, info = gpu_run(s, t)
+    assert _taken(info) == _slabs(shape, groups, "f32", slab, slices)
+    assert torch.equal(outs[0], t[2].expand(shape))
+
+
+@pytest.mark.parametrize("shape,slices", [((4, 64, 64, 224), 8), ((16, 7, 73, 224), 1)])
+def test_means_are_not_off_all_the_same_way(shape, slices):
+    # Values around 1000, whose last place is 2^-14.  A group's mean is rounded at each level of a tree: 0.41 of that (rms), and the average over
+    # 128 groups and more 0.04.  A seventh rounded once for all lanes would put every mean off by 0.7.
+    s, t = _chain(shape, 32, "f32", act="none", seed=60)
+    t[0], t[1], t[2] = wl.random_tensor(shape, "f32", 7710) + 1000.0, torch.ones(224), torch.zeros(224)
+    with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS="4", PF_SLAB_SLICES=str(slices)):
+        outs, info = gpu_run(s, t)
+    assert _taken(info) == _slabs(shape, 32, "f32", 4, slices)
+    assert abs((outs[0].double().numpy() - oracle_run(s, t)[0]).mean()) <= 0.25 * 2.0 ** -14
