@@ -438,7 +438,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
             }
         }
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) mean_e[e] *= inv;
+        for (int e = 0; e < VEC; ++e) {
+            // (a quotient with its remainder: a sum times the rounded reciprocal of seven is not the mean of equal values)
+            const float q = mean_e[e] * inv;
+            mean_e[e] = __builtin_fmaf(__builtin_fmaf(-npos, q, mean_e[e]), inv, q);
+        }
         auto keep_packed = [&](int i) {  // (the widened values are not kept from pass to pass)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {

@@ -105,3 +105,16 @@ def test_shapes_of_more_than_two_mebibytes(shape, dtype):
     s, t = _chain(shape, 32, dtype, seed=91)
     _, info, _ = check_chain(s, t, what=f"groupnorm > silu > mean {shape} {dtype}, as planned")
     assert info.n_kernels == 1 and info.workspace_bytes == 0
+
+
+# 28, 14 and 7 positions to a lane: a group of equal values is centred to zero exactly, so its pooled value is beta
+@pytest.mark.parametrize("shape,groups", [((8, 28, 64, 64), 1), ((8, 28, 32, 128), 2), ((8, 7, 64, 64), 1)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_equal_values_are_their_own_mean(shape, groups, dtype):
+    s, t = _chain(shape, groups, dtype, mid="none", seed=98)
+    level = wl.random_tensor((shape[0], 1, 1, groups, 1), dtype, 6500, dist="uniform", scale=250.0) + 750.0
+    t[0] = level.expand(shape[:-1] + (groups, shape[-1] // groups)).reshape(shape).contiguous()
+    with env(PF_NORM_POOL_SLAB="2"):
+        outs, info = gpu_run(s, t)
+    assert info.n_launches == 1
+    assert torch.equal(outs[0].reshape(shape[0], -1), t[2].expand(shape[0], -1))
