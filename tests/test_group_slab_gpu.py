@@ -177,3 +177,18 @@ def test_means_are_not_off_all_the_same_way(shape, slices):
         outs, info = gpu_run(s, t)
     assert _taken(info) == _slabs(shape, 32, "f32", 4, slices)
     assert abs((outs[0].double().numpy() - oracle_run(s, t)[0]).mean()) <= 0.25 * 2.0 ** -14
+
+
+@pytest.mark.parametrize("shape,slices", [((8, 32, 14, 512), 1), ((2, 53, 60, 512), 7)])
+def test_packed_variances_around_an_offset(shape, slices):
+    # Sums of squares around M = 300 with a spread of 1: a rounding of a lane's sum is up to 2^-24 M^2 of the variance, averaged over the lanes of
+    # a group.  Half of that for all lanes alike is the bar, a quarter in the scale of the result: 1.3e-3.  Seven positions to a lane, divided by a
+    # rounded reciprocal, would be off by 2.3e-3 and more.
+    s, t = _chain(shape, 8, "f16", act="none", seed=70)
+    t[0] = wl.quantise(wl.widen(wl.random_tensor(shape, "f16", 7720)) + 300.0, "f16")
+    t[1], t[2] = torch.ones(512, dtype=torch.float16), torch.zeros(512, dtype=torch.float16)
+    with env(PF_GROUP_SLAB="2", PF_SLAB_GROUPS="1", PF_SLAB_SLICES=str(slices)):
+        outs, info = gpu_run(s, t)
+    assert _taken(info) == _slabs(shape, 8, "f16", 1, slices)
+    got, want = outs[0].double().numpy(), oracle_run(s, t)[0]
+    assert abs((got * want).sum() / (want * want).sum() - 1.0) <= 300.0 ** 2 * 2.0 ** -26
