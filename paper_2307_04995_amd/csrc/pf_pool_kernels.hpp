@@ -437,12 +437,6 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
                 for (int e = 0; e < VEC; ++e) mean_e[e] += x[e];
             }
         }
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            // (a quotient with its remainder: a sum times the rounded reciprocal of seven is not the mean of equal values)
-            const float q = mean_e[e] * inv;
-            mean_e[e] = __builtin_fmaf(__builtin_fmaf(-npos, q, mean_e[e]), inv, q);
-        }
         auto keep_packed = [&](int i) {  // (the widened values are not kept from pass to pass)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -459,13 +453,17 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NV > 1
             if (i + 1 < NV || last_valid) {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
-                    const float d = x[e] - mean_e[e];
+                    const float d = __builtin_fmaf(-mean_e[e], inv, x[e]);  // (the sum still; straight from the packed value in fp16)
                     m2_e[e] = __builtin_fmaf(d, d, m2_e[e]);
                 }
             }
         }
 #pragma unroll
         for (int i = 0; i < NV; ++i) keep_packed(i);
+        // (the mean with what the reciprocal was rounded by: a sum times the rounded one of seven is not the mean of equal values)
+        const float inv_rest = __builtin_fmaf(-npos, inv, 1.0f) * inv;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) mean_e[e] = __builtin_fmaf(mean_e[e], inv, mean_e[e] * inv_rest);
         // one triple per group the vector touches, adjacent slots merged
         const uint32_t first = fast_div(min(ch, g.channels - 1u), g.div_cpg);
         Stat cur = {npos, mean_e[0], m2_e[0]};
