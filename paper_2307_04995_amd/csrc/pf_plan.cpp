@@ -446,7 +446,8 @@ pf_status plan_row(pf_plan_s* p, int forced_variant) {
         std::string err;
         hipFunction_t fn = pf::jit_row_kernel_const(p->device, L.main_dtype, p->k, (int)p->row.rows_per_wave, best_wpr == 1, p->ragged,
                                                    p->block.x <= 256 ? 256 : 1024, p->row_log2l, make_jit_spec(L), sh, &err);
-        if (fn) {
+        // (rows taken on three or more vectors a lane for fitting the registers: only where this kernel fits them too)
+        if (fn && (wide_k == 0 || pf::jit_scratch_bytes(fn) == 0)) {
             p->jit_fn = fn;
             p->spec_id = pf::kSpecJit;
         }
