@@ -192,3 +192,10 @@ def test_packed_variances_around_an_offset(shape, slices):
     assert _taken(info) == _slabs(shape, 8, "f16", 1, slices)
     got, want = outs[0].double().numpy(), oracle_run(s, t)[0]
     assert abs((got * want).sum() / (want * want).sum() - 1.0) <= 300.0 ** 2 * 2.0 ** -26
+
+
+@pytest.mark.parametrize("shape,dtype,slab,slices", [((31, 10, 10, 96), "f16", 8, 1), ((7, 56, 56, 768), "f32", 8, 9), ((1, 56, 56, 416), "f32", 4, 21), ((4, 64, 64, 224), "bf16", 8, 15)])
+def test_the_slabs_that_the_planner_takes(shape, dtype, slab, slices):
+    s, t = _chain(shape, 32, dtype, seed=30)
+    _, info = gpu_run(s, t)
+    assert _taken(info) == _slabs(shape, 32, dtype, slab, slices)
