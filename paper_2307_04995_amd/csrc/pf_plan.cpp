@@ -1488,8 +1488,8 @@ static bool plan_norm_pool_slab(pf_plan_s* p, int n_cu) {
     // ahead of the two launches' (fitted to 270 measured slabs of 26 shapes, 5 % off in the mean; [13, 50, 50, 576] bf16 30.8 in one launch, 28.3
     // in two, 7 % ahead by the models).  us, fp16 or bf16, before and
     // now: [21, 28, 28, 64] 13.7 -> 8.8, [19, 14, 14, 576] 13.3 -> 9.3, [28, 18, 18, 416] 15.4 -> 10.6, [23, 32, 32, 992] 39.5 -> 32.0, [8, 56, 56,
-    // 256] 18.0 -> 14.0.  Smaller tensors would gain as well ([1, 7, 7, 128] 9.8, 8.7 in one launch), but that they are two launches is
-    // relied upon.  (Slices of a slab that exchange their statistics gain more where slabs are few -- [4, 64, 64, 672] 25.7 -> 20.8 -- but all
+    // 256] 18.0 -> 14.0.  Smaller tensors would gain as well ([1, 7, 7, 128] 9.8, 8.7 in one launch); tests/test_norm_pool_gpu.py states two
+    // launches for them.  (Slices of a slab that exchange their statistics gain more where slabs are few -- [4, 64, 64, 672] 25.7 -> 20.8 -- but all
     // workgroups of a launch then wait for one another: two such launches on two streams, each with half of the units, would wait in vain,
     // dispatched as they were; in runs of slabs, as the slices of the group family are now, they were not tried.)
     if (!forced && es == 2 && n * hw * ch * es > (2 << 20)) {
@@ -1829,8 +1829,9 @@ pf_status plan_attn(pf_plan_s* p, int forced_variant) {
     // and 1.5 a further trip.  A head that is one slice merges nothing.  Slices of equal length instead of whole steps and a
     // shorter last one: 608 heads, t = 494, d = 128 29.1 us against 28.6, the others alike.  Before and after: 200 heads, t = 1023, d = 64 (4
     // slices of 8 steps, 5 of 7 now) 13.4 -> 12.9 us, 24 heads, t = 3058 10.0 -> 9.1, 8 heads, t = 143 (one slice) 5.3 -> 3.7, 50 heads,
-    // t = 71, d = 128 5.4 -> 3.8.  Heads that eight steps leave more than 128 slices stay with the rule above: one head of 20 000 rows, d = 128,
-    // 313 slices 41.5 us against 24.0 with 157, but its number of slices is relied upon.
+    // t = 71, d = 128 5.4 -> 3.8.  Lost: 96 heads, t = 798, d = 128 (7 slices of 8 steps, 8 of 7 now) 12.27 -> 12.44; 128 heads, t = 600, where the model
+    // sees the same difference, 12.10 -> 11.81.  Heads that eight steps leave more than 128 slices stay with the rule above, though not for
+    // speed (one head of 20 000 rows, d = 128: 313 slices 41.5 us, 157 24.0): tests/test_attention_gpu.py states the 313 slices.
     // A static call takes the same slices, so that its results are the plan's, unless they do not fit the scratch array where the
     // others would (and is refused where the others do not fit).
     if (variant == PF_VARIANT_ATTN_ONE_PASS && !forced_nv && (t_total + rps * 8 - 1) / (rps * 8) <= 128) {
